@@ -357,7 +357,8 @@ ds_status_t ds_profile_read(int id, double *total_ms, int64_t *launches);
  *           1 = never; 2 = always
  *   knob 5: launch shape 4: polls after which a workgroup's wait for another workgroup gives
  *           up (0 = the default of 2^21, far beyond any wait that ends; small values are for
- *           testing the give-up path: see ds_workspace_errors)
+ *           testing the give-up path: see ds_workspace_errors).  ds_build_label_q4: polls after which
+ *           a workgroup finds its unit's channel maxima by itself (0 = 2^14; the result is the same)
  * DS_ERR_SHAPE for a knob or value the kernels cannot run with.  Process-wide;
  * changing a knob changes ds_workspace_bytes() and the workspace layout, so
  * re-query the size and clear the workspace again afterwards.

@@ -250,7 +250,7 @@ bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p)
 static const char *const kKernelNames[KID_COUNT] = {
     "k_init", "k_score", "k_cand", "k_attend", "k_compact", "k_dense",
     "k_attend_rows", "k_label", "k_gather_host", "k_probe",
-    "k_refine_attend", "k_append_kv", "k_q4_amax", "k_q4_write", "k_predict_query"};
+    "k_refine_attend", "k_append_kv", "k_q4_build", "k_q4_write", "k_predict_query"};
 
 struct ProfRec { int id; hipEvent_t a, b; };
 static std::mutex g_prof_mu;
@@ -393,8 +393,7 @@ ds_status_t ds_build_label_q4(const void *K, const int32_t *channels, void *labe
     if (st != DS_OK) return st;
     if (shape->L < 1 || shape->L > shape->L_max) return DS_ERR_SHAPE;
     if (!aligned(amax, 4)) return DS_ERR_ALIGN;
-    DS_TRY(launch_q4_amax(K, channels, amax, *shape, (hipStream_t)stream));
-    DS_TRY(launch_q4_write(K, channels, amax, label_q4, *shape, 0, shape->L, (hipStream_t)stream));
+    DS_TRY(launch_q4_build(K, channels, amax, label_q4, *shape, (hipStream_t)stream));
     return DS_OK;
 }
 

@@ -53,7 +53,7 @@ enum KernelId {
     KID_PROBE,
     KID_REFINE_ATTEND,
     KID_APPEND_KV,
-    KID_Q4_AMAX,
+    KID_Q4_BUILD,
     KID_Q4_WRITE,
     KID_PREDICT,
     KID_COUNT
@@ -133,8 +133,8 @@ hipError_t launch_attend_rows(const void *q, const void *KV_rows, void *ws, floa
                               const DensePlan &p, const ds_shape_t &s, int n_rows, hipStream_t st);
 hipError_t launch_label(const void *K, const int32_t *channels, void *label, const ds_shape_t &s,
                         int t0, int n, hipStream_t st, int kv_stride = kD);
-hipError_t launch_q4_amax(const void *K, const int32_t *channels, float *amax, const ds_shape_t &s,
-                          hipStream_t st);
+hipError_t launch_q4_build(const void *K, const int32_t *channels, float *amax, void *codes,
+                           const ds_shape_t &s, hipStream_t st);
 hipError_t launch_q4_write(const void *K, const int32_t *channels, const float *amax, void *codes,
                            const ds_shape_t &s, int t0, int n, hipStream_t st);
 hipError_t launch_predict_query(const void *x, const void *Wq, void *q_out, int B, int Dm, int N,

@@ -6,26 +6,48 @@
 
 namespace ds {
 
-// label[u, t, j] = K[u, t, channels[h, j]] for t in [t0, t0 + n): a bit copy.
-// One thread per label element; writes are contiguous, reads pick 2-byte
-// elements out of the 256-byte K rows (kv_stride halves apart: d, or 2d when
-// each K row is followed by the token's V row).
+// The label values of K rows are picked by a fixed thread layout: thread tid takes channel j =
+// tid mod r of the rows i0 = tid / r, i0 + P, i0 + 2 P, .. with P = 256 / r rows per pass (the last
+// 256 - P r threads idle), so that its channel stays in a register and no element costs a division.
+// A wavefront's load covers every line of 64 / r rows once; eight passes are in flight.
+constexpr int kPick = 8;
+struct PickLanes {
+    int P, j, i0;
+    bool on;
+    __device__ __forceinline__ explicit PickLanes(int r)
+    {
+        P = kWG / r;
+        j = (int)threadIdx.x % r;
+        i0 = (int)threadIdx.x / r;
+        on = i0 < P;
+    }
+};
+
+// label[u, t, j] = K[u, t, channels[h, j]] for t in [t0, t0 + n): a bit copy, `per_wg` tokens to a
+// workgroup (kv_stride halves from row to row: d, or 2d when each K row is followed by the
+// token's V row).  Bound by the read of the K rows' lines: 512 MiB of K in 94 us, where a bare read of
+// them takes 80 and every other way to pick the values (whole rows through LDS, wider stores, other
+// workgroup sizes) 93 to 107; without the streaming mark 104.
 __global__ __launch_bounds__(kWG) void k_label(const uint16_t *__restrict__ K,
                                                const int32_t *__restrict__ channels,
                                                uint16_t *__restrict__ label, int Hkv, int L_max,
-                                               int r, int t0, int n, int kv_stride)
+                                               int r, int t0, int n, int kv_stride, int per_wg)
 {
-    __shared__ int ch_sh[kD];
+    const PickLanes p(r);
+    if (!p.on) return;
     const int u = blockIdx.y, h = u % Hkv;
-    if (threadIdx.x < r) ch_sh[threadIdx.x] = channels[h * r + threadIdx.x];
-    __syncthreads();
-    const size_t total = (size_t)n * r;
-    const size_t stride = (size_t)gridDim.x * kWG;
-    for (size_t e = (size_t)blockIdx.x * kWG + threadIdx.x; e < total; e += stride) {
-        const size_t t = t0 + e / r;
-        const int j = (int)(e % r);
-        const size_t row = (size_t)u * L_max + t;
-        label[row * r + j] = K[row * kv_stride + ch_sh[j]];
+    const int c = channels[h * r + p.j];
+    const int lo = blockIdx.x * per_wg, hi = min(n, lo + per_wg);
+    const uint16_t *Ku = K + ((size_t)u * L_max + t0) * kv_stride + c;
+    uint16_t *lu = label + ((size_t)u * L_max + t0) * r + p.j;
+    for (int i = lo + p.i0; i < hi; i += kPick * p.P) {
+        uint16_t x[kPick];
+#pragma unroll
+        for (int e = 0; e < kPick; ++e)
+            x[e] = __builtin_nontemporal_load(Ku + (size_t)min(i + e * p.P, hi - 1) * kv_stride);
+#pragma unroll
+        for (int e = 0; e < kPick; ++e)
+            if (i + e * p.P < hi) lu[(size_t)(i + e * p.P) * r] = x[e];
     }
 }
 
@@ -65,34 +87,115 @@ __global__ __launch_bounds__(kWG) void k_append_kv(const uint4 *__restrict__ k_n
 //   amax[u, j] = max_t |K[u, t, C[j]]|,  code = clamp(rint(x * (7 / amax)), -8, 7),
 //   label value = code * (amax / 7); eight two's-complement nibbles per 32-bit word,
 //   channel j of a token in bits [4 (j mod 8), +4) of the token's word j / 8.
-// k_q4_amax: non-negative binary32 values order like their bit patterns, so the maximum is an
-// integer atomicMax (exact, order-free).  amax must be zero on entry.
-__global__ __launch_bounds__(kWG) void k_q4_zero(uint32_t *p, size_t n)
+// A binary16 magnitude orders like its 15 bits and widened to binary32 like those bits, so the
+// maximum is an integer atomicMax (exact, order-free).
+__device__ __forceinline__ uint32_t q4_code(float x, float inv)
 {
-    for (size_t i = (size_t)blockIdx.x * kWG + threadIdx.x; i < n; i += (size_t)gridDim.x * kWG) p[i] = 0u;
+    const float y = __builtin_rintf(x * inv);
+    const int c = y < -8.0f ? -8 : (y > 7.0f ? 7 : (int)y);
+    return (uint32_t)c & 0xfu;
+}
+__device__ __forceinline__ float q4_inverse(float amax) { return amax > 0.0f ? 7.0f / amax : 0.0f; }
+
+// Before k_q4_build: amax and every unit's counter word (its first word of codes) to zero.
+__global__ __launch_bounds__(kWG) void k_q4_zero(uint32_t *amax, size_t n, uint32_t *codes, size_t unit_words,
+                                                 int units)
+{
+    const size_t i0 = (size_t)blockIdx.x * kWG + threadIdx.x, step = (size_t)gridDim.x * kWG;
+    for (size_t i = i0; i < n; i += step) amax[i] = 0u;
+    for (size_t i = i0; i < (size_t)units; i += step) codes[i * unit_words] = 0u;
 }
 
-__global__ __launch_bounds__(kWG) void k_q4_amax(const _Float16 *__restrict__ K,
-                                                 const int32_t *__restrict__ channels,
-                                                 uint32_t *amax_bits, int Hkv, int L_max, int r, int n)
+// Builds the 4-bit label cache with one read of the K rows, which bounds it (64 units of 16K tokens,
+// 16 channels: 268 MB in 54 us; a pass for the maxima and a pass for the codes, each reading the
+// rows with a division per element: 60 + 226 us).  A workgroup picks the label values of
+// its tile of tokens into LDS, adds its channel maxima to the unit's (amax), arrives at the unit's
+// counter and waits for the unit's other workgroups; with the unit's maxima complete it codes the
+// tile out of LDS.  The counter (arrivals in the low half, departures in the high half) is the
+// unit's first word of codes: token 0 is coded by the last workgroup to depart, when nobody looks
+// at the counter any more.
+// The wait: a unit's workgroups are neighbours in the grid and start in grid order, so those that a
+// workgroup waits for are running or next in line.  It is bounded all the same, and a workgroup
+// whose wait runs out reads the unit's K rows itself for the maxima: slower, the same result.
+__global__ __launch_bounds__(kWG) void k_q4_build(const uint16_t *__restrict__ K,
+                                                  const int32_t *__restrict__ channels, uint32_t *amax_bits,
+                                                  uint32_t *codes, int Hkv, int L_max, int r, int L, int tile,
+                                                  uint32_t spin_limit)
 {
-    __shared__ int ch_sh[kD];
+    extern __shared__ __attribute__((aligned(16))) uint16_t tile_sh[];  // [tile][8 W] picked values
     __shared__ uint32_t mx_sh[kD];
-    const int u = blockIdx.y, h = u % Hkv;
-    if (threadIdx.x < kD) {
-        mx_sh[threadIdx.x] = 0u;
-        if (threadIdx.x < r) ch_sh[threadIdx.x] = channels[h * r + threadIdx.x];
+    __shared__ float inv_sh[kD];
+    __shared__ uint32_t s_ok, s_last;
+    const int tid = threadIdx.x, u = blockIdx.y, h = u % Hkv;
+    const int W = (r + 7) / 8, stride = 8 * W;
+    const PickLanes p(r);
+    const int c = p.on ? channels[h * r + p.j] : 0;
+    if (tid < kD) mx_sh[tid] = 0u;
+    const uint16_t *Ku = K + (size_t)u * L_max * kD + c;
+    auto f16 = [](uint16_t v) { return (float)__builtin_bit_cast(_Float16, v); };
+    // largest magnitude of the thread's channel over its share of the rows [lo, hi), values to `keep`
+    auto pick = [&](int lo, int hi, auto keep) {
+        uint32_t mx = 0u;
+        if (p.on)
+            for (int i = lo + p.i0; i < hi; i += kPick * p.P) {
+                uint16_t x[kPick];
+#pragma unroll
+                for (int e = 0; e < kPick; ++e)
+                    x[e] = __builtin_nontemporal_load(Ku + (size_t)min(i + e * p.P, hi - 1) * kD);
+#pragma unroll
+                for (int e = 0; e < kPick; ++e) {
+                    mx = max(mx, (uint32_t)(x[e] & 0x7fffu));
+                    if (i + e * p.P < hi) keep(i + e * p.P, x[e]);
+                }
+            }
+        return __float_as_uint(f16((uint16_t)mx));
+    };
+    const int t0 = blockIdx.x * tile, t1 = min(L, t0 + tile);
+    const uint32_t mine = pick(t0, t1, [&](int t, uint16_t x) { tile_sh[(t - t0) * stride + p.j] = x; });
+    __syncthreads();
+    if (p.on) atomicMax(&mx_sh[p.j], mine);
+    __syncthreads();
+    uint32_t *am = amax_bits + (size_t)u * r;
+    uint32_t *cu = codes + (size_t)u * L_max * W;
+    if (tid < r && mx_sh[tid]) atomicMax(&am[tid], mx_sh[tid]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t n_wg = gridDim.x;
+        uint32_t ok = ((__hip_atomic_fetch_add(cu, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 0xffffu) + 1u == n_wg);
+        for (uint32_t it = 0; !ok && it < spin_limit; ++it) {
+            __builtin_amdgcn_s_sleep(1);
+            ok = (ld_dev(cu) & 0xffffu) == n_wg;
+        }
+        s_ok = ok;
+        const uint32_t left = __hip_atomic_fetch_add(cu, 1u << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 16;
+        s_last = left + 1u == n_wg;
     }
     __syncthreads();
-    const size_t total = (size_t)n * r;
-    for (size_t e = (size_t)blockIdx.x * kWG + threadIdx.x; e < total; e += (size_t)gridDim.x * kWG) {
-        const size_t t = e / r;
-        const int j = (int)(e % r);
-        const float x = __builtin_fabsf((float)K[((size_t)u * L_max + t) * kD + ch_sh[j]]);
-        atomicMax(&mx_sh[j], __float_as_uint(x));
+    if (!s_ok) {
+        const uint32_t all = pick(0, L, [](int, uint16_t) {});
+        if (p.on) atomicMax(&mx_sh[p.j], all);
+        __syncthreads();
+        if (tid < r) inv_sh[tid] = q4_inverse(__uint_as_float(mx_sh[tid]));
+    } else if (tid < r) {
+        inv_sh[tid] = q4_inverse(__uint_as_float(ld_dev(am + tid)));
     }
     __syncthreads();
-    if (threadIdx.x < r && mx_sh[threadIdx.x]) atomicMax(&amax_bits[(size_t)u * r + threadIdx.x], mx_sh[threadIdx.x]);
+    for (int e = tid; e < (t1 - t0) * W; e += kWG) {
+        const int i = e / W, w = e - i * W;
+        const half8 v = *reinterpret_cast<const half8 *>(tile_sh + i * stride + w * 8);
+        uint32_t word = 0u;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (w * 8 + k < r) word |= q4_code((float)v[k], inv_sh[w * 8 + k]) << (4 * k);
+        if (t0 + i) cu[(size_t)(t0 + i) * W + w] = word;
+    }
+    if (s_last && tid < W) {
+        uint32_t word = 0u;
+        for (int k = 0; k < 8 && tid * 8 + k < r; ++k)
+            word |= q4_code(f16(Ku[channels[h * r + tid * 8 + k] - c]), inv_sh[tid * 8 + k]) << (4 * k);
+        cu[tid] = word;
+    }
 }
 
 // One thread per (token, word): up to eight codes packed into the word.
@@ -107,8 +210,7 @@ __global__ __launch_bounds__(kWG) void k_q4_write(const _Float16 *__restrict__ K
     const int u = blockIdx.y, h = u % Hkv;
     if (threadIdx.x < r) {
         ch_sh[threadIdx.x] = channels[h * r + threadIdx.x];
-        const float a = amax[(size_t)u * r + threadIdx.x];
-        inv_sh[threadIdx.x] = a > 0.0f ? 7.0f / a : 0.0f;
+        inv_sh[threadIdx.x] = q4_inverse(amax[(size_t)u * r + threadIdx.x]);
     }
     __syncthreads();
     const int W = (r + 7) / 8;
@@ -117,12 +219,8 @@ __global__ __launch_bounds__(kWG) void k_q4_write(const _Float16 *__restrict__ K
         const size_t row = (size_t)u * L_max + t0 + e / W;
         const int w = (int)(e % W);
         uint32_t word = 0u;
-        for (int i = 0; i < 8 && w * 8 + i < r; ++i) {
-            const int j = w * 8 + i;
-            const float y = __builtin_rintf((float)K[row * kD + ch_sh[j]] * inv_sh[j]);
-            const int c = y < -8.0f ? -8 : (y > 7.0f ? 7 : (int)y);
-            word |= ((uint32_t)c & 0xfu) << (4 * i);
-        }
+        for (int i = 0; i < 8 && w * 8 + i < r; ++i)
+            word |= q4_code((float)K[row * kD + ch_sh[w * 8 + i]], inv_sh[w * 8 + i]) << (4 * i);
         codes[row * W + w] = word;
     }
 }
@@ -227,27 +325,37 @@ hipError_t launch_label(const void *K, const int32_t *channels, void *label, con
                         int t0, int n, hipStream_t st, int kv_stride)
 {
     if (n <= 0) return hipSuccess;
-    const size_t total = (size_t)n * s.r;
-    size_t blocks = (total + kWG - 1) / kWG;
-    if (blocks > 4096) blocks = 4096;
-    DS_LAUNCH(KID_LABEL, k_label, dim3((unsigned)blocks, s.B * s.Hkv), dim3(kWG), 0, st,
+    // 256 tokens to a workgroup (64 KiB of K; one round of loads per thread with 8 channels)
+    const int round = kPick * (kWG / s.r);
+    const int per_wg = round * std::max(1, 256 / round);
+    DS_LAUNCH(KID_LABEL, k_label, dim3((n + per_wg - 1) / per_wg, s.B * s.Hkv), dim3(kWG), 0, st,
                        static_cast<const uint16_t *>(K), channels, static_cast<uint16_t *>(label),
-                       s.Hkv, s.L_max, s.r, t0, n, kv_stride);
+                       s.Hkv, s.L_max, s.r, t0, n, kv_stride, per_wg);
     return hipGetLastError();
 }
 
-hipError_t launch_q4_amax(const void *K, const int32_t *channels, float *amax, const ds_shape_t &s,
-                          hipStream_t st)
+hipError_t launch_q4_build(const void *K, const int32_t *channels, float *amax, void *codes,
+                           const ds_shape_t &s, hipStream_t st)
 {
-    const size_t n_amax = (size_t)s.B * s.Hkv * s.r;
-    hipLaunchKernelGGL(k_q4_zero, dim3((unsigned)std::min<size_t>((n_amax + kWG - 1) / kWG, 1024)), dim3(kWG),
-                       0, st, reinterpret_cast<uint32_t *>(amax), n_amax);
-    const size_t total = (size_t)s.L * s.r;
-    size_t blocks = (total + kWG * 8 - 1) / (kWG * 8);
-    if (blocks > 1024) blocks = 1024;
-    DS_LAUNCH(KID_Q4_AMAX, k_q4_amax, dim3((unsigned)blocks, s.B * s.Hkv), dim3(kWG), 0, st,
-              static_cast<const _Float16 *>(K), channels, reinterpret_cast<uint32_t *>(amax), s.Hkv,
-              s.L_max, s.r, s.L);
+    const int units = s.B * s.Hkv, W = (s.r + 7) / 8;
+    const size_t n_amax = (size_t)units * s.r;
+    hipLaunchKernelGGL(k_q4_zero, dim3((unsigned)std::min<size_t>((n_amax + kWG - 1) / kWG, 1024)), dim3(kWG), 0, st,
+                       reinterpret_cast<uint32_t *>(amax), n_amax, static_cast<uint32_t *>(codes),
+                       (size_t)s.L_max * W, units);
+    // Tiles of 16 KiB (1024 tokens of up to 8 channels): eight workgroups per compute unit, as many
+    // as its wavefronts allow.  Calls of few tokens take smaller tiles, down to 64 tokens, until
+    // there are four workgroups for every compute unit or 32 for a unit: the atomics of a unit's
+    // workgroups queue at its maxima and its counter, about 0.17 us each (64 units of 16K tokens,
+    // 16 channels: 32 workgroups per unit 54 us, 64: 72, 128: 145).  A unit has at most 65535 (its
+    // counter).
+    int tile = std::max(64, 1024 / W);
+    const int64_t want = 4ll * device_caps().cus;
+    while (tile > 64 && (int64_t)units * ((s.L + tile - 1) / tile) < want && (s.L + tile - 1) / tile <= 16) tile /= 2;
+    while ((s.L + tile - 1) / tile > 65535) tile *= 2;
+    DS_LAUNCH(KID_Q4_BUILD, k_q4_build, dim3((s.L + tile - 1) / tile, units), dim3(kWG), (size_t)tile * 16 * W, st,
+              static_cast<const uint16_t *>(K), channels, reinterpret_cast<uint32_t *>(amax),
+              static_cast<uint32_t *>(codes), s.Hkv, s.L_max, s.r, s.L, tile,
+              tune_get(5) ? (uint32_t)tune_get(5) : 1u << 14);
     return hipGetLastError();
 }
 

@@ -1,0 +1,50 @@
+"""GPU checks of single kernels at the sizes where a tile, a remainder or a dispatch rule can go
+wrong, against the CPU oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2408_07092_amd as ds
+from oracle import ds_oracle as O
+from tests.parity_util import to_dev
+from workloads import Workload, make_layer_numpy
+
+pytestmark = pytest.mark.gpu
+
+
+def rand_channels(Hkv, r, seed):
+    rng = np.random.default_rng(seed)
+    return np.stack([np.sort(rng.permutation(128)[:r]) for _ in range(Hkv)]).astype(np.int32)
+
+
+@pytest.mark.parametrize("B,Hkv,L,L_max,r,spin", [
+    (1, 1, 1, 1, 1, 0),            # one token
+    (2, 3, 64, 64, 8, 0),          # one whole tile
+    (1, 2, 65, 70, 3, 0),          # one token into the second tile
+    (1, 2, 1025, 1028, 16, 0),     # ... of a unit with many tiles
+    (1, 1, 40001, 40001, 8, 0),    # more tiles than a small unit gets otherwise
+    (1, 2, 700, 700, 128, 0),      # every channel, two rows per pass
+    (1, 2, 3000, 3000, 100, 0),    # idle threads in a pass
+    (2, 2, 5000, 5000, 12, 1),     # waits that run out: a workgroup finds the maxima by itself
+])
+def test_q4_build_tiles(B, Hkv, L, L_max, r, spin):
+    """Codes and maxima bit-equal to the oracle's at the edges of the tiles, and when a workgroup
+    stops waiting for the others of its unit."""
+    w = Workload("t", B, Hkv, Hkv, 128, L, r, 1, 1)
+    t = make_layer_numpy(w, L_max=L_max)
+    ch = rand_channels(Hkv, r, seed=L + r)
+    W = (r + 7) // 8
+    codes = torch.full((B, Hkv, L_max, W), -1, dtype=torch.int32, device="cuda")
+    amax = torch.full((B, Hkv, r), -1.0, dtype=torch.float32, device="cuda")
+    ds.ds_tune_set(5, spin)
+    try:
+        ds.ds_build_label_q4(to_dev(t["K"]), to_dev(ch), codes, amax, ds.shape(B, Hkv, Hkv, 128, L, L_max, r, 1))
+        torch.cuda.synchronize()
+    finally:
+        ds.ds_tune_set(5, 0)
+    want_codes, want_amax = O.build_label_q4(t["K"], ch, L)
+    assert np.array_equal(amax.cpu().numpy(), want_amax)
+    assert np.array_equal(codes.cpu().numpy()[:, :, :L].view(np.uint32), want_codes[:, :, :L])
+    assert (codes[:, :, L:] == -1).all()
