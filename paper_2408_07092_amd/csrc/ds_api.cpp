@@ -230,8 +230,30 @@ bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p)
     p->G = s.Hq / s.Hkv;
     int ch = tune_get(2);
     if (ch == 0) {
-        const int64_t tokens = (int64_t)p->units * n_tokens;
-        ch = (tokens >= (1 << 20)) ? 1024 : (tokens >= (1 << 18)) ? 256 : 64;
+        // Chunks per unit: the number n with the least estimated time among those that fill the
+        // device w = 1/4, 1/2, 1 .. 8 times.  In rows of a compute unit, which streams about
+        // 50 of them per us:  the busiest one's share, at least the average one; a start and an end
+        // of each workgroup (150 on the matrix cores, where three fit at a time, 25 on the vector
+        // path); and the merge of n partials of G heads by the unit's last workgroup, 1.5 each.
+        // A unit with one workgroup draws less than one with two or more (24 against 29 GB/s).
+        // (Measured against chunks of 64 / 256 / 1024 tokens by the number of tokens alone: 32 units
+        // of 32K tokens in groups of 4 heads 105 -> 83 us, 12 units of 20K in groups of 7 116 -> 30,
+        // 8 units of 32K in groups of 8 66 -> 33, 32 single heads of 64K 179 -> 165, of 4K 19.6 -> 15.8.)
+        const int cus = device_caps().cus;
+        const bool matrix = p->G > 2;
+        double best = 0.0;
+        for (int w4 = 1; w4 <= 32; w4 += w4 < 4 ? w4 : 4) {
+            const int n_want = std::min(std::max(1, (int)((int64_t)w4 * cus / 4 / p->units)), std::max(1, n_tokens / 32));
+            const int c = ((n_tokens + n_want - 1) / n_want + 15) & ~15, n = (n_tokens + c - 1) / c;
+            const int busiest = (int)(((int64_t)p->units * n + cus - 1) / cus);
+            const double rows = std::max((double)p->units * n_tokens / cus,
+                                         (double)busiest * c / (busiest > 1 ? 1.2 : 1.0));
+            const double cost = rows + busiest * (matrix ? 150.0 : 25.0) + 1.5 * n * p->G;
+            if (ch == 0 || cost < best) {
+                best = cost;
+                ch = c;
+            }
+        }
     }
     p->ch = ch;
     p->n_ch = (n_tokens + ch - 1) / ch;

@@ -8,7 +8,7 @@ import torch
 
 import paper_2408_07092_amd as ds
 from oracle import ds_oracle as O
-from tests.parity_util import to_dev
+from tests.parity_util import check_output, to_dev
 from workloads import Workload, make_layer_numpy
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +48,25 @@ def test_q4_build_tiles(B, Hkv, L, L_max, r, spin):
     assert np.array_equal(amax.cpu().numpy(), want_amax)
     assert np.array_equal(codes.cpu().numpy()[:, :, :L].view(np.uint32), want_codes[:, :, :L])
     assert (codes[:, :, L:] == -1).all()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,L_max", [
+    (1, 1, 1, 1, 1),
+    (1, 1, 1, 33, 40),           # one row more than the smallest chunk of a device full of chunks
+    (1, 8, 1, 4099, 4100),       # one unit in groups of 8: many chunks, a ragged last one
+    (3, 28, 4, 2003, 2048),      # groups of 7
+    (2, 40, 40, 700, 700),       # single heads, several workgroups per compute unit
+    (9, 64, 32, 130, 130),       # more units than compute units, pairs
+    (5, 64, 64, 65, 65),         # the same, single heads
+    (1, 32, 1, 1000, 1000),      # groups of 32: two passes over the rows
+])
+def test_dense_decode_chunk_rule(B, Hq, Hkv, L, L_max):
+    """Dense decode at both ends of the rule that cuts a unit into chunks."""
+    w = Workload("t", B, Hq, Hkv, 128, L, 8, 1, 1)
+    t = make_layer_numpy(w, L_max=L_max)
+    shp = ds.shape(B, Hq, Hkv, 128, L, L_max, 8, 1)
+    ws = ds.ds_workspace_alloc(shp)
+    out = torch.full((B, Hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+    ds.ds_dense_decode(to_dev(t["q"]), to_dev(t["K"]), to_dev(t["V"]), out, ws, shp)
+    torch.cuda.synchronize()
+    check_output(out.cpu().numpy(), O.dense_decode(t["q"], t["K"], t["V"], L), f"dense {(B, Hq, Hkv, L)}")
