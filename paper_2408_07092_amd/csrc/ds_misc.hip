@@ -232,7 +232,10 @@ __global__ __launch_bounds__(kWG) void k_q4_write(const _Float16 *__restrict__ K
 // split m in 16-byte pieces, products are exact (fp16 x fp16) and accumulated in binary32, the
 // lanes are summed in a fixed butterfly, the result is rounded once to fp16.  Up to four batch
 // rows share a pass over Wq (x sits in LDS); larger batches take several passes.
+// Eight pieces of a row are in flight per lane and the first are asked for before x is staged (a
+// piece of two rows in turn at a time: 14.4 us for 4096 x 4096, now 9.1; 8192 x 8192 42.7, now 24.8).
 constexpr int kPredBatch = 4;
+constexpr int kPredPieces = 8;
 
 __global__ __launch_bounds__(kWG) void k_predict_query(const _Float16 *__restrict__ x,
                                                        const _Float16 *__restrict__ Wq,
@@ -242,26 +245,40 @@ __global__ __launch_bounds__(kWG) void k_predict_query(const _Float16 *__restric
     extern __shared__ __attribute__((aligned(16))) _Float16 x_sh[];  // [min(B, kPredBatch)][Dm]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_lo = blockIdx.x * rows_per_wg, n_hi = min(N, n_lo + rows_per_wg);
+    half8 wv[kPredPieces];
+    // (pieces past the end of the row re-read its last one; they are not used)
+    auto issue = [&](int n, int m0) {
+        const _Float16 *wrow = Wq + (size_t)min(n, N - 1) * Dm;
+#pragma unroll
+        for (int i = 0; i < kPredPieces; ++i)
+            if (m0 - lane * 8 + i * 512 < Dm)
+                wv[i] = __builtin_nontemporal_load(reinterpret_cast<const half8 *>(wrow + min(m0 + i * 512, Dm - 8)));
+    };
     for (int b0 = 0; b0 < B; b0 += kPredBatch) {
         const int nb = min(kPredBatch, B - b0);
+        issue(n_lo + wave, lane * 8);
         __syncthreads();
         for (int i = tid * 8; i < nb * Dm; i += kWG * 8)
             *reinterpret_cast<uint4 *>(x_sh + i) = *reinterpret_cast<const uint4 *>(x + (size_t)b0 * Dm + i);
         __syncthreads();
         for (int n = n_lo + wave; n < n_hi; n += 4) {
-            const _Float16 *wrow = Wq + (size_t)n * Dm;
             float acc[kPredBatch] = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int m = lane * 8; m < Dm; m += 64 * 8) {
-                const half8 wv = *reinterpret_cast<const half8 *>(wrow + m);
+            for (int m0 = lane * 8; m0 - lane * 8 < Dm; m0 += 512 * kPredPieces) {
+                if (m0 >= 512 * kPredPieces || n != n_lo + wave) issue(n, m0);
 #pragma unroll
-                for (int b = 0; b < kPredBatch; ++b) {
-                    if (b < nb) {
-                        const half8 xv = *reinterpret_cast<const half8 *>(x_sh + b * Dm + m);
+                for (int i = 0; i < kPredPieces; ++i) {
+                    const int m = m0 + i * 512;
+                    if (m >= Dm) continue;
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const half2v a2 = {wv[2 * e], wv[2 * e + 1]};
-                            const half2v b2 = {xv[2 * e], xv[2 * e + 1]};
-                            acc[b] = __builtin_amdgcn_fdot2(a2, b2, acc[b], false);
+                    for (int b = 0; b < kPredBatch; ++b) {
+                        if (b < nb) {
+                            const half8 xv = *reinterpret_cast<const half8 *>(x_sh + b * Dm + m);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) {
+                                const half2v a2 = {wv[i][2 * e], wv[i][2 * e + 1]};
+                                const half2v b2 = {xv[2 * e], xv[2 * e + 1]};
+                                acc[b] = __builtin_amdgcn_fdot2(a2, b2, acc[b], false);
+                            }
                         }
                     }
                 }
@@ -278,25 +295,40 @@ __global__ __launch_bounds__(kWG) void k_predict_query(const _Float16 *__restric
 
 // rows[u, i, 0, :] = K_host[u, idx[u, i], :], rows[u, i, 1, :] = V_host[...]:
 // 16 lanes move one 256-byte row; K_host / V_host are pinned host memory read
-// over the host link by the kernel itself.
+// over the host link by the kernel itself.  Bound by the link (about 55 GB/s), which 0.5 to 0.75 MiB
+// of loads in flight keep full.  More in flight only fills the queues that the other streams'
+// kernels share: with a workgroup for every 16 rows the query prediction of the next layer took
+// 200 us beside the gather and the gather 340; with 64 workgroups 109 and 304, with 24 of them 33
+// and 302, with 12 21 and 315 (alone: 20).
+constexpr int kGatherRows = 4;   // rows of a 16-lane slot in flight
+constexpr int kGatherWgs = 24;   // 24 x 16 slots x 4 rows of 512 bytes: 768 KiB
 __global__ __launch_bounds__(kWG) void k_gather_host(const uint4 *__restrict__ Kh,
                                                      const uint4 *__restrict__ Vh,
                                                      const int32_t *__restrict__ idx,
-                                                     uint4 *__restrict__ rows, int L_max, int k)
+                                                     uint4 *__restrict__ rows, int L_max, int k, int total)
 {
-    const int u = blockIdx.y;
-    const int i = blockIdx.x * 16 + (threadIdx.x >> 4), p = threadIdx.x & 15;
-    if (i >= k) return;
-    const int tok = idx[(size_t)u * k + i];
-    uint4 kv = make_uint4(0, 0, 0, 0), vv = kv;
-    if (tok >= 0) {
-        const size_t src = ((size_t)u * L_max + tok) * 16 + p;
-        kv = Kh[src];
-        vv = Vh[src];
+    const int p = threadIdx.x & 15, step = gridDim.x * 16;
+    for (int i0 = blockIdx.x * 16 + (threadIdx.x >> 4); i0 < total; i0 += step * kGatherRows) {
+        uint4 kv[kGatherRows], vv[kGatherRows];
+#pragma unroll
+        for (int e = 0; e < kGatherRows; ++e) {
+            const int i = i0 + e * step;
+            kv[e] = vv[e] = make_uint4(0, 0, 0, 0);
+            const int tok = i < total ? idx[i] : -1;
+            if (tok >= 0) {
+                const size_t src = ((size_t)(i / k) * L_max + tok) * 16 + p;
+                kv[e] = Kh[src];
+                vv[e] = Vh[src];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < kGatherRows; ++e) {
+            const int i = i0 + e * step;
+            if (i >= total) break;
+            rows[(size_t)i * 32 + p] = kv[e];
+            rows[(size_t)i * 32 + p + 16] = vv[e];
+        }
     }
-    const size_t dst = ((size_t)u * k + i) * 32 + p;
-    rows[dst] = kv;
-    rows[dst + 16] = vv;
 }
 
 // Plain streaming read: every workgroup reads 64 KiB as 16-byte loads marked as streaming (the
@@ -375,8 +407,9 @@ hipError_t launch_q4_write(const void *K, const int32_t *channels, const float *
 hipError_t launch_predict_query(const void *x, const void *Wq, void *q_out, int B, int Dm, int N,
                                 hipStream_t st)
 {
-    // about two workgroups per CU; every workgroup re-reads x once per batch pass
-    int rows_per_wg = (N + 511) / 512;
+    // a row per wavefront up to four workgroups per compute unit; every workgroup re-reads x once
+    // per batch pass
+    int rows_per_wg = (N + 1023) / 1024;
     rows_per_wg = (rows_per_wg + 3) & ~3;
     const int blocks = (N + rows_per_wg - 1) / rows_per_wg;
     const size_t shmem = (size_t)std::min(B, kPredBatch) * Dm * sizeof(_Float16);
@@ -403,9 +436,10 @@ hipError_t launch_append_kv(const void *k_new, const void *v_new, void *K, void 
 hipError_t launch_gather_host(const void *Kh, const void *Vh, const int32_t *idx, void *rows,
                               const ds_shape_t &s, hipStream_t st)
 {
-    DS_LAUNCH(KID_GATHER_HOST, k_gather_host, dim3((s.k + 15) / 16, s.B * s.Hkv), dim3(kWG), 0, st,
+    const int total = s.B * s.Hkv * s.k;
+    DS_LAUNCH(KID_GATHER_HOST, k_gather_host, dim3(std::min(kGatherWgs, (total + 15) / 16)), dim3(kWG), 0, st,
                        static_cast<const uint4 *>(Kh), static_cast<const uint4 *>(Vh), idx,
-                       static_cast<uint4 *>(rows), s.L_max, s.k);
+                       static_cast<uint4 *>(rows), s.L_max, s.k, total);
     return hipGetLastError();
 }
 

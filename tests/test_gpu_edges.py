@@ -70,3 +70,36 @@ def test_dense_decode_chunk_rule(B, Hq, Hkv, L, L_max):
     ds.ds_dense_decode(to_dev(t["q"]), to_dev(t["K"]), to_dev(t["V"]), out, ws, shp)
     torch.cuda.synchronize()
     check_output(out.cpu().numpy(), O.dense_decode(t["q"], t["K"], t["V"], L), f"dense {(B, Hq, Hkv, L)}")
+
+
+@pytest.mark.parametrize("B,Dm,N", [(1, 8, 5), (1, 512, 4), (3, 520, 1025), (5, 4096, 65), (1, 4104, 33), (2, 8192, 4100)])
+def test_predict_query_pieces(B, Dm, N):
+    """Row lengths at the edges of the pieces in flight and feature counts at the edges of the
+    workgroups: one fp16 step plus the binary32 error of Dm products from the float64 oracle."""
+    rng = np.random.default_rng(Dm + N)
+    x = rng.standard_normal((B, Dm)).astype(np.float16)
+    Wq = (rng.standard_normal((N, Dm)) / np.sqrt(Dm)).astype(np.float16)
+    q = torch.full((B, N), float("nan"), dtype=torch.float16, device="cuda")
+    ds.ds_predict_query(to_dev(x), to_dev(Wq), q)
+    torch.cuda.synchronize()
+    got, ref = q.cpu().numpy().astype(np.float64), O.predict_query(x, Wq).astype(np.float64)
+    mag = np.abs(x.astype(np.float64)) @ np.abs(Wq.astype(np.float64)).T
+    step = np.maximum(np.spacing(np.abs(ref).astype(np.float16)).astype(np.float64), 2.0 ** -24)
+    assert (np.abs(got - ref) <= step + Dm * 2.0 ** -24 * mag).all()
+
+
+@pytest.mark.parametrize("B,Hkv,L,k", [(1, 1, 5, 1), (1, 3, 40, 33), (2, 4, 700, 97), (1, 2, 3000, 1600)])
+def test_gather_rows_host_rounds(B, Hkv, L, k):
+    """Row counts below, at and beyond one round of the gather's workgroups, with unused entries."""
+    rng = np.random.default_rng(k)
+    K = torch.from_numpy(rng.standard_normal((B, Hkv, L, 128)).astype(np.float16)).pin_memory()
+    V = torch.from_numpy(rng.standard_normal((B, Hkv, L, 128)).astype(np.float16)).pin_memory()
+    idx = rng.integers(0, L, size=(B, Hkv, k)).astype(np.int32)
+    idx[rng.random(idx.shape) < 0.1] = -1
+    rows = torch.full((B, Hkv, k, 2, 128), float("nan"), dtype=torch.float16, device="cuda")
+    ds.ds_gather_rows_host(K, V, to_dev(idx), rows, ds.shape(B, Hkv, Hkv, 128, L, L, 8, k))
+    torch.cuda.synchronize()
+    take = np.maximum(idx, 0)[..., None].astype(np.int64)
+    want = np.stack([np.take_along_axis(t.numpy(), take, axis=2) for t in (K, V)], axis=3)
+    want[idx < 0] = 0
+    assert np.array_equal(rows.cpu().numpy().view(np.uint16), want.view(np.uint16))
