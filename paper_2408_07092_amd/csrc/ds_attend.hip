@@ -602,99 +602,77 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     uint32_t n_cand = 0;
     uint32_t early_base = 0;  // (thread 0, several workgroups per unit, lists made by the single scan)
     // A workgroup that owns a CU (RPS > 4) has nobody else to hide its list work behind, so
-    // instructions count: it looks at each key once and orders the lists thread by thread with one
-    // scan (any fixed order of the row list will do; only the index list has to be in token order).
+    // instructions count: it keeps the candidates' masks until the exact threshold is in (any fixed
+    // order of the row list will do; only the index list has to be in token order).
     constexpr bool kAllKeys = RPS > 4;
-    // (kAllKeys) bit 4 p + e of a mask <-> the thread's key e of pass p, at this place in the chunk:
+    // Each thread owns n_pass groups of four consecutive keys (group p of thread t: keys
+    // 4 (p WGT + t) ..: a wavefront's loads then cover the LDS banks evenly).  One look at each key:
+    // which of the thread's keys are definite and which are candidates goes into bit masks, and the
+    // writes walk the set bits, few as they are.  Bit 4 p + e of a mask <-> key e of group p, at
+    // this place in the chunk:
     auto key_slot = [&](int j) { return ((j >> 2) * WGT + tid) * 4 + (j & 3); };
-    uint32_t mcan[2] = {0u, 0u};  // the thread's candidates
-    constexpr int kAllPasses = 16384 / (WGT * 4);  // ch <= 16384
-    if constexpr (kAllKeys) {
-        __syncthreads();  // the keys were stored by other threads
-        // One look at each key: which of the thread's keys are definite / candidates goes into two
-        // 64-bit masks (few keys are either), and the list writes -- now and when the exact
-        // threshold is in -- walk the set bits only.
-        uint32_t mdef[2] = {0u, 0u};
+    uint32_t mdef[2] = {0u, 0u}, mcan[2] = {0u, 0u};
+    if constexpr (SMODE == 0 || kAllKeys) __syncthreads();  // the keys were stored by other threads
+    {
+        // Two groups are read at a time, whatever lies past the chunk's end among them, and the
+        // masks cut to the chunk afterwards: no bounds in the loop, 32-bit masks at fixed places.
+        // (Against a loop over the groups with bounds and 64-bit masks: units of 4K tokens 12.2 -> 11.7 us,
+        //  128 units of 32K tokens in groups of 8 46.5 -> 45.7, of 4 with 4-bit labels 40.7 -> 39.8.)
+        const uint32_t hi_key = lo_key | ((1u << kKeyShift) - 1u);
 #pragma unroll
-        for (int p = 0; p < kAllPasses; ++p) {
-            const int lt = (p * WGT + tid) * 4;
-            uint4 kq = make_uint4(0u, 0u, 0u, 0u);
-            if (p < n_pass && t0 + lt < t1) kq = *reinterpret_cast<const uint4 *>(keys_sh + lt);
-            const uint32_t k4[4] = {kq.x, kq.y, kq.z, kq.w};
+        for (int w = 0; w < 2; ++w) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int j = p * 4 + e;
-                const bool live = p < n_pass && t0 + lt + e < t1;
-                const uint32_t bin = k4[e] >> kKeyShift;
-                if (live && bin > bstar) mdef[j >> 5] |= 1u << (j & 31);
-                if (live && bin == bstar) mcan[j >> 5] |= 1u << (j & 31);
+            for (int p2 = 0; p2 < 8; p2 += 2) {
+                if (w * 8 + p2 >= n_pass) break;
+                uint4 kq[2];
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    kq[i] = *reinterpret_cast<const uint4 *>(keys_sh + min(((w * 8 + p2 + i) * WGT + tid) * 4, a.ch - 4));
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint32_t k4[4] = {kq[i].x, kq[i].y, kq[i].z, kq[i].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t bit = 1u << ((p2 + i) * 4 + e);
+                        mdef[w] |= k4[e] > hi_key ? bit : 0u;
+                        mcan[w] |= k4[e] >= lo_key ? bit : 0u;
+                    }
+                }
             }
         }
+        // (the groups before the last pass are whole, the last has what is left of the chunk)
+        const int last = 4 * (n_pass - 1);
+        const int left = min(max(t1 - t0 - (last * WGT + tid * 4), 0), 4);
+        const unsigned long long live = ((1ull << last) << left) - 1ull;
+        mdef[0] &= (uint32_t)live;
+        mdef[1] &= (uint32_t)(live >> 32);
+        mcan[0] &= (uint32_t)live & ~mdef[0];
+        mcan[1] &= (uint32_t)(live >> 32) & ~mdef[1];
+    }
+    {
         const uint32_t packed = (uint32_t)(__builtin_popcount(mdef[0]) + __builtin_popcount(mdef[1])) |
                                 (uint32_t)(__builtin_popcount(mcan[0]) + __builtin_popcount(mcan[1])) << 16;
         uint32_t total;
         const uint32_t ex = block_exclusive_scan<NW>(packed, s_w, &total);
+        DS_TR(13);
+        // the chunk's place in the unit's candidate list is fetched while the lists are written
+        if (!kAllKeys && gridDim.x != 1 && tid == 0 && (total >> 16))
+            early_base = (uint32_t)__hip_atomic_fetch_add(cand_arrive, (unsigned long long)(total >> 16), __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT);
+        n_def = (int)(total & 0xffffu);
+        n_cand = total >> 16;
+        // the definite rows from the front of the list, the candidates behind them, or (kAllKeys)
+        // from its back; both in the thread's key order
         int dpos = (int)(ex & 0xffffu);
-        int cp = a.ch - 1 - (int)(ex >> 16);
+        int cp = kAllKeys ? a.ch - 1 - (int)(ex >> 16) : n_def + (int)(ex >> 16);
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
             for (uint32_t m = mdef[w]; m; m &= m - 1u) sel[dpos++] = (uint16_t)key_slot(w * 32 + __builtin_ctz(m));
-            for (uint32_t m = mcan[w]; m; m &= m - 1u) sel[cp--] = (uint16_t)key_slot(w * 32 + __builtin_ctz(m));
-        }
-        n_def = (int)(total & 0xffffu);
-        n_cand = total >> 16;
-    }
-    if constexpr (!kAllKeys) {
-        if constexpr (SMODE == 0) __syncthreads();  // the keys were stored by other threads
-        // Each thread owns n_pass groups of four consecutive keys (group p of thread t: keys
-        // 4 (p WGT + t) ..: a wavefront's loads then cover the LDS banks evenly).  Both lists are
-        // written in thread order, which is the same on every run (only the index list has to be
-        // in token order, and that is written further down).
-        auto block_keys = [&](int p, uint32_t (&k4)[4]) {
-            const int lt = (p * WGT + tid) * 4;
-            k4[0] = k4[1] = k4[2] = k4[3] = 0u;
-            if (t0 + lt < t1) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(keys_sh + lt);
-                k4[0] = v.x; k4[1] = v.y; k4[2] = v.z; k4[3] = v.w;
-            }
-            return lt;
-        };
-        // One look at each key: which of the thread's keys (64 at most) are definite and which are
-        // candidates goes into two masks, and the writes walk the set bits, few as they are
-        // (against a counting pass and a writing pass over the keys: C3 -0.2, C4a -0.9 us/layer).
-        unsigned long long mdef = 0, mcd = 0;
-        for (int p = 0; p < n_pass; ++p) {
-            uint32_t k4[4];
-            const int lt = block_keys(p, k4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool in = t0 + lt + e < t1 && k4[e] >= lo_key;
-                const bool cand = k4[e] - lo_key < (1u << kKeyShift);
-                if (in && !cand) mdef |= 1ull << (4 * p + e);
-                if (in && cand) mcd |= 1ull << (4 * p + e);
+            for (uint32_t m = mcan[w]; m; m &= m - 1u) {
+                sel[cp] = (uint16_t)key_slot(w * 32 + __builtin_ctz(m));
+                cp += kAllKeys ? -1 : 1;
             }
         }
-        const uint32_t packed = (uint32_t)__builtin_popcountll(mdef) | ((uint32_t)__builtin_popcountll(mcd) << 16);
-        uint32_t total;
-        const uint32_t ex = block_exclusive_scan<NW>(packed, s_w, &total);
-        DS_TR(13);
-        // the chunk's place in the unit's candidate list is fetched while the lists are written
-        if (gridDim.x != 1 && tid == 0 && (total >> 16))
-            early_base = (uint32_t)__hip_atomic_fetch_add(cand_arrive, (unsigned long long)(total >> 16), __ATOMIC_RELAXED,
-                                                          __HIP_MEMORY_SCOPE_AGENT);
-        // the candidates follow the definite rows in the row list; both in the thread's key order
-        uint32_t dpos = ex & 0xffffu;
-        uint32_t cp = (total & 0xffffu) + (ex >> 16);
-        for (unsigned long long m = mdef; m; m &= m - 1ull) {
-            const int j = __builtin_ctzll(m);
-            sel[dpos++] = (uint16_t)(((j >> 2) * WGT + tid) * 4 + (j & 3));
-        }
-        for (unsigned long long m = mcd; m; m &= m - 1ull) {
-            const int j = __builtin_ctzll(m);
-            sel[cp++] = (uint16_t)(((j >> 2) * WGT + tid) * 4 + (j & 3));
-        }
-        n_def = (int)(total & 0xffffu);
-        n_cand = total >> 16;
     }
     // where the chunk's i-th candidate waits in the row list: behind the definite rows, or (the
     // variant that looks at each key once) at the list's end, filled from the back
