@@ -710,10 +710,11 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     int tcut = 0x7fffffff;
     if (have_T) {
         // ---- the unit is complete: exact k-th key among the candidates (10 + 10 key bits), ties
-        // to the lowest token (4 + 10 + 10 index bits; tokens are below 2^24).  Up to 2048
-        // candidates stay in registers; beyond that every pass re-reads the list.
+        // to the lowest token (4 + 10 + 10 index bits; tokens are below 2^24).  The first 2048
+        // candidates (eight per thread) stay in registers; what lies beyond is read again by every
+        // pass, eight loads in flight.  (One load at a time, the 4400 candidates of a unit of 256K
+        // tokens took 16.5 us of the launch's 55, and every workgroup of the unit waited for them.)
         const uint32_t n = single ? n_cand : min(s_base, (uint32_t)a.L);  // the completed count came with the arrival
-        const bool in_regs = n <= 8u * WGT;
         // candidate i of the unit: out of the list in memory, or (single workgroup) the i-th
         // staged token of this chunk
         auto cand_at = [&](uint32_t i) {
@@ -724,17 +725,21 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
             return ld_dev(cu + i);
         };
         uint2 ce[8];
-        if (in_regs && n) {
+        auto read8 = [&](uint2 (&v)[8], uint32_t i0) {
 #pragma unroll
-            for (int x = 0; x < 8; ++x) ce[x] = cand_at(min((uint32_t)(tid + x * WGT), n - 1));
-        }
+            for (int x = 0; x < 8; ++x) v[x] = cand_at(min(i0 + (uint32_t)(x * WGT), n - 1));
+        };
+        if (n) read8(ce, tid);
         auto each = [&](auto f) {
-            if (in_regs) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+                if ((uint32_t)(tid + x * WGT) < n) f(ce[x]);
+            for (uint32_t i0 = tid + 8u * WGT; i0 < n; i0 += 8u * WGT) {
+                uint2 v[8];
+                read8(v, i0);
 #pragma unroll
                 for (int x = 0; x < 8; ++x)
-                    if ((uint32_t)(tid + x * WGT) < n) f(ce[x]);
-            } else {
-                for (uint32_t i = tid; i < n; i += WGT) f(cand_at(i));
+                    if (i0 + (uint32_t)(x * WGT) < n) f(v[x]);
             }
         };
         if (tid == 0) s_cnt2 = 0u;  // (pass 1 has barriers before its first use)
