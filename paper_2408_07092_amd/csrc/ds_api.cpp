@@ -537,10 +537,12 @@ static ds_status_t enqueue_select(const void *q, const void *label, const int32_
 
 static bool label_may_score(const ds_shape_t &s, ScoreSrcKind kind)
 {
-    // the attention launch can score as well when the labels are plain fp16 with 8 or 16 channels,
-    // or 4-bit codes of up to 16 channels in rows that 16-byte loads can take (knob 4 = 1 keeps
-    // the separate scoring launch)
-    return tune_get(4) != 1 && ((kind == SRC_LABEL && (s.r == 8 || s.r == 16)) ||
+    // the attention launch can score as well when the labels are plain fp16 with 4, 8, 12, 16 or 24
+    // channels (with a scoring launch against without: 12 channels, 12 units of 20K tokens in groups
+    // of 7 29.4 -> 25.3 us, 32 units of 64K tokens 44.3 -> 34.1; 24 channels, 128 units of 4K tokens
+    // 24.2 -> 18.3; 4 channels, 32 units of 2K tokens 15.4 -> 10.6), or 4-bit codes of up to 16
+    // channels in rows that 16-byte loads can take (knob 4 = 1 keeps the separate scoring launch)
+    return tune_get(4) != 1 && ((kind == SRC_LABEL && attend_scores_r(s.r)) ||
                                 (kind == SRC_Q4 && s.r <= 16 && (s.L_max & (s.r > 8 ? 1 : 3)) == 0));
 }
 
@@ -567,10 +569,21 @@ static ds_status_t sparse_decode_impl(const void *q, const void *label, const vo
 {
     if (!K || !V || !out) return DS_ERR_NULL;
     Plan p;
-    const bool may_score = shape && label_may_score(*shape, src.kind);
-    ds_status_t rc = select_common(q, label, channels, workspace, workspace_bytes, shape, &p,
-                                   may_score ? PLAN_DECODE_SCORING : PLAN_DECODE);
-    if (rc != DS_OK) return rc;
+    bool may_score = shape && label_may_score(*shape, src.kind);
+    ds_status_t rc;
+    if (may_score && src.kind == SRC_LABEL && shape->r != 8 && shape->r != 16) {
+        // (the workspace that a call needs is that of the plan with a scoring launch; the other
+        //  plan is taken when it fits too)
+        rc = select_common(q, label, channels, workspace, workspace_bytes, shape, &p, PLAN_DECODE);
+        if (rc != DS_OK) return rc;
+        Plan ps;
+        may_score = make_plan(*shape, &ps, PLAN_DECODE_SCORING) && ps.total <= workspace_bytes;
+        if (may_score) p = ps;
+    } else {
+        rc = select_common(q, label, channels, workspace, workspace_bytes, shape, &p,
+                           may_score ? PLAN_DECODE_SCORING : PLAN_DECODE);
+        if (rc != DS_OK) return rc;
+    }
     if (!aligned(K, 256) || !aligned(V, 256) || !aligned(out, 16) || (idx_out && !aligned(idx_out, 16)))
         return DS_ERR_ALIGN;
     hipStream_t st = (hipStream_t)stream;

@@ -16,6 +16,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <type_traits>
 
 #include "ds_attend_core.h"
 
@@ -284,11 +285,10 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     if constexpr (SMODE != 0) {
         // ---- 0. Algorithm 1 steps 1-2 right here: stream the chunk's label rows, keys go to LDS
         // only; with one workgroup per unit the threshold bin comes out of its own histogram.
-        // Same arithmetic and order as k_score.  SMODE = r for fp16 labels (8 or 16); SMODE = -8 /
+        // Same arithmetic and order as k_score.  SMODE = r for fp16 labels (4, 8, 12, 16 or 24); SMODE = -8 /
         // -16 for the 4-bit label cache of up to 8 / 16 channels (one / two words per token).
         constexpr bool kQ4 = SMODE < 0;
         constexpr int RR = kQ4 ? -SMODE : SMODE;
-        constexpr int NV = RR / 8;
         __shared__ uint32_t hist_own[kAliasHist ? 1 : kHistBins];
         auto hist_at = [&](int i) -> uint32_t & {
             if constexpr (kAliasHist) return reinterpret_cast<uint32_t *>(&wpart[0][0][0])[i];
@@ -320,7 +320,7 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
 #pragma unroll
             for (int j = 0; j < RR; ++j) wr[j] = qs_sh[j];
             // 16-byte loads of four (two) tokens, four loads per thread in flight
-            constexpr int WW = NV, TPL = 4 / WW;
+            constexpr int WW = RR / 8, TPL = 4 / WW;
             const uint32_t *codes = reinterpret_cast<const uint32_t *>(a.label) + (size_t)u * a.L_max * WW;
             auto nib = [](uint32_t word, int i) { return (float)(((int32_t)(word << (28 - 4 * i))) >> 28); };
             const int t_lastq = (t1 - 1) & ~(TPL - 1);
@@ -352,8 +352,14 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
         }
         if constexpr (!kQ4) {
         const _Float16 *lab = a.label + (size_t)u * a.L_max * SMODE;
-        constexpr int SD = ST ? kScoreDepth : 2 * kScoreDepth;  // (a mostly idle device: fewer round trips)
-        half8 v[SD][NV];
+        // A token's label row is NV pieces: of eight channels, or of four when eight do not divide it.
+        // (24 channels: half as many rows in flight, their registers are as many)
+        constexpr int PE = RR % 8 ? 4 : 8;
+        constexpr int NV = RR / PE;
+        using Piece = typename std::conditional<PE == 8, half8, half4>::type;
+        constexpr bool kPairs = RR == 16;
+        constexpr int SD = RR > 16 ? kScoreDepth / 2 : ST ? kScoreDepth : 2 * kScoreDepth;  // (a mostly idle device: fewer round trips)
+        Piece v[SD][NV];
         // (rows past the end of the chunk re-read its last row; their scores are dropped)
         // Rows of two 16-byte pieces (16 channels): a wavefront's two loads take 64 consecutive
         // pieces each -- whole cache lines, so they can carry the streaming mark --, which leaves
@@ -363,27 +369,27 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
         //  lines: measured 2 us per layer slower on the batch-8 workload.)
         const int lane_ = tid & 63;
         auto token_of = [&](int tb, int i) {
-            if constexpr (NV == 2) return tb - lane_ + i * WGT + (lane_ >> 1) + ((lane_ & 1) ? 32 : 0);
+            if constexpr (kPairs) return tb - lane_ + i * WGT + (lane_ >> 1) + ((lane_ & 1) ? 32 : 0);
             else return tb + i * WGT;
         };
         auto issue = [&](int tb) {
 #pragma unroll
             for (int i = 0; i < SD; ++i) {
-                if constexpr (NV == 2) {
+                if constexpr (kPairs) {
                     const int p0 = 2 * (tb - lane_ + i * WGT) + lane_, p_last = 2 * t1 - 1;
                     const half8 *pieces = reinterpret_cast<const half8 *>(lab);
                     v[i][0] = label_load<1, ST>(pieces + min(p0, p_last));
                     v[i][1] = label_load<1, ST>(pieces + min(p0 + 64, p_last));
                 } else {
-                    const half8 *row = reinterpret_cast<const half8 *>(lab + (size_t)min(tb + i * WGT, t1 - 1) * SMODE);
+                    const Piece *row = reinterpret_cast<const Piece *>(lab + (size_t)min(tb + i * WGT, t1 - 1) * SMODE);
 #pragma unroll
                     for (int j = 0; j < NV; ++j) v[i][j] = label_load<NV, ST>(row + j);
                 }
             }
         };
-        // (NV == 2) the lane's two pieces -> its token's two halves
-        auto own_row = [&](half8 (&r)[NV]) {
-            if constexpr (NV == 2) {
+        // (kPairs) the lane's two pieces -> its token's two halves
+        auto own_row = [&](Piece (&r)[NV]) {
+            if constexpr (kPairs) {
                 const bool odd = lane_ & 1;
                 const half8 got = swap_pairs(odd ? r[0] : r[1]);
                 if (odd) r[0] = got;
@@ -415,8 +421,8 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
         float qs[SMODE];
 #pragma unroll
         for (int j = 0; j < SMODE; ++j) qs[j] = qs_sh[j];
-        // (NV == 2: a lane's token is not the one of its place, so a wavefront stays together)
-        auto more = [&](int tb) { return (NV == 2 ? tb - lane_ : tb) < t1; };
+        // (kPairs: a lane's token is not the one of its place, so a wavefront stays together)
+        auto more = [&](int tb) { return (kPairs ? tb - lane_ : tb) < t1; };
         for (int tb = t0 + tid; more(tb);) {
 #pragma unroll
             for (int i = 0; i < SD; ++i) {
@@ -425,7 +431,7 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
 #pragma unroll
                 for (int j = 0; j < NV; ++j)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) acc = __builtin_fmaf(qs[j * 8 + e], (float)v[i][j][e], acc);
+                    for (int e = 0; e < PE; ++e) acc = __builtin_fmaf(qs[j * PE + e], (float)v[i][j][e], acc);
                 const int t = token_of(tb, i);
                 if (t < t1) {
                     const uint32_t key = score_key(acc);
@@ -1127,14 +1133,17 @@ struct RaKernel {
     int threads;
 };
 
-// smode: 0 = keys and threshold bin come from the scoring launch; 8 / 16 = fp16 labels of that
+// smode: 0 = keys and threshold bin come from the scoring launch; 4 .. 24 = fp16 labels of that
 // many channels scored here; -8 / -16 = 4-bit labels of up to that many channels scored here.
 template <int GT, int RPS, bool ST = true>
 static RaFn ra_fn(int smode)
 {
     switch (smode) {
     case 0: return RPS > 4 ? nullptr : static_cast<RaFn>(k_refine_attend<GT, 0, 4, ST>);
+    case 4: return k_refine_attend<GT, 4, RPS, ST>;
     case 8: return k_refine_attend<GT, 8, RPS, ST>;
+    case 12: return k_refine_attend<GT, 12, RPS, ST>;
+    case 24: return k_refine_attend<GT, 24, RPS, ST>;
     case 16: return k_refine_attend<GT, 16, RPS, ST>;
     case -8: return k_refine_attend<GT, -8, RPS, ST>;
     default: return k_refine_attend<GT, -16, RPS, ST>;
@@ -1173,7 +1182,7 @@ static int ra_smode(const ds_shape_t &s, bool scores_itself, bool q4)
 {
     if (!scores_itself) return 0;
     if (q4) return (s.r > 16 || (s.L_max & (s.r > 8 ? 1 : 3))) ? 0 : (s.r > 8 ? -16 : -8);
-    return (s.r == 8 || s.r == 16) ? s.r : 0;
+    return attend_scores_r(s.r) ? s.r : 0;
 }
 
 // What the runtime says of a kernel, asked once per (kernel, dynamic LDS): more than 64 KiB of
@@ -1237,8 +1246,8 @@ bool refine_attend_fits(const Plan &p, const ds_shape_t &s, bool scores_itself, 
     return ra_fits(ra_kernel(p, s, smode), p, smode);
 }
 
-// score_label / score_channels: non-null to run the scoring in the same launch (fp16 labels of 8
-// or 16 channels; with score_amax the 4-bit label cache of up to 16 channels, whose token rows
+// score_label / score_channels: non-null to run the scoring in the same launch (fp16 labels of
+// as many channels as attend_scores_r allows; with score_amax the 4-bit label cache of up to 16 channels, whose token rows
 // must be 16-byte loadable: L_max % 4 == 0 for one word per token, L_max % 2 == 0 for two);
 // otherwise the keys and the threshold bin of a preceding k_score launch are read from the
 // workspace.  kNotResident, with nothing enqueued, when the device cannot hold the workgroups

@@ -10,6 +10,7 @@
 namespace ds {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half4 __attribute__((ext_vector_type(4)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
 constexpr float kNegInf = -__builtin_inff();
@@ -23,8 +24,8 @@ constexpr float kNegInf = -__builtin_inff();
 // in the cache only if the first load was an ordinary one (measured on 16-channel labels:
 // streaming mark +3 us per layer).  (k_refine_attend loads such rows as whole lines, two tokens'
 // halves per lane, and lets neighbouring lanes swap: see swap_pairs.)
-template <int NV, bool ST = true>
-__device__ __forceinline__ half8 label_load(const half8 *p)
+template <int NV, bool ST = true, class Piece>
+__device__ __forceinline__ Piece label_load(const Piece *p)
 {
     if constexpr (NV == 1 && ST) return __builtin_nontemporal_load(p);
     else return *p;

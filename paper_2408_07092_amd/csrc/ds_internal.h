@@ -118,6 +118,9 @@ hipError_t launch_compact(void *ws, int32_t *idx_out, const Plan &p, const ds_sh
 hipError_t launch_attend_sparse(const void *q, const void *K, const void *V, void *ws, float *out,
                                 int32_t *idx_out, const Plan &p, const ds_shape_t &s,
                                 hipStream_t st, int kv_stride = kD);
+// fp16 label caches that the attention launch can score itself: of 4, 8, 12, 16 or 24 channels (its
+// label rows are loaded by a fixed layout per number of channels).
+constexpr bool attend_scores_r(int r) { return r == 4 || r == 8 || r == 12 || r == 16 || r == 24; }
 bool refine_attend_ok(const Plan &p, bool scores_itself);
 // Returned by launch_refine_attend (nothing enqueued) when the launch would wait for workgroups
 // that the device cannot hold at the same time as the waiting ones.
