@@ -123,8 +123,8 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose)
     // is 4K tokens; 8K when there are enough units (256) to fill the device; 16K for a workgroup
     // that scores its unit itself, single heads or pairs, with 192 units or more (one 96 KiB
     // workgroup per CU).  Units of 4K to 8K tokens that are too few for that take the long units'
-    // path when the attention launch can score (batch 4 x 8K tokens, 32 heads: 30.5 -> 25.1 us);
-    // what is left refines the threshold in the scoring launch's tail.
+    // path when the attention launch can score, with one workgroup or several (see below); what is
+    // left refines the threshold in the scoring launch's tail.
     const bool one_wg_units =
         purpose != PLAN_SELECT &&
         (s.L <= 4096 || (p->units >= caps.cus && s.L <= 8192) ||
@@ -205,9 +205,25 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose)
         if (p->G >= 4)
             while ((int64_t)p->units * ((s.L + ch - 1) / ch) > 3 * caps.cus && ch < 6144 && ch < s.L) ch += 256;
     }
+    // One workgroup also takes a unit of up to 6K tokens, and with half as many units as compute units
+    // one of up to 8K, when it can score it: what passes between several costs more than one compute
+    // unit's rate (about 33 GB/s).  Several against one, us per layer: single heads, 8 channels,
+    // 32 units of 5000 tokens 17.7 -> 15.0, 128 of 6016 22.7 -> 18.7, 128 of 8192 25.1 -> 21.6; 16
+    // channels 19.5 -> 18.7, 24.1 -> 21.5, 27.5 -> 25.7; groups of 4 and 8, 8 to 64 units of 6016
+    // 20.1 .. 22.2 -> 19.4 .. 21.0, 128 of 8192 25.4 -> 24.8.  On the other side of the line: 64 single
+    // heads of 8192 tokens 20.8 -> 20.5 and with 16 channels 22.2 -> 24.0, 32 to 64 groups of 4
+    // 21.3 -> 23.8, 128 single heads of 10240 with 16 channels 30.0 -> 30.1.  Pairs gain less: 64 units
+    // of 6016 20.8 -> 21.6, 128 23.6 -> 22.0, 128 of 8192 26.3 -> 26.9.
+    // (The workspace keeps the room of the plan with several.)
+    const int n_ws = (s.L + ch - 1) / ch;
+    if (n_ws > 1 && p->refine_attend && purpose == PLAN_DECODE_SCORING && tune_get(1) == 0 &&
+        s.L <= (p->G != 2 && p->units * 2 >= caps.cus ? 8192 : 6144) && (p->G != 2 || p->units * 2 >= caps.cus)) {
+        ch = (s.L + 255) & ~255;
+        p->unit_groups = 1;
+    }
     p->ch = ch;
     p->n_ch = (s.L + ch - 1) / ch;
-    if (p->n_ch > kMaxChunks) return false;
+    if (n_ws > kMaxChunks) return false;
     p->key_stride = (s.L + 3) & ~3;
 
     size_t off = 0;
@@ -216,9 +232,9 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose)
     p->off_coarse = off; off = align_up(off + (size_t)p->units * 256 * 4, 256);
     p->off_keys = off;  off = align_up(off + (size_t)p->units * p->key_stride * 4, 256);
     p->off_cand = off;  off = align_up(off + (size_t)p->units * s.L * 8, 256);
-    p->off_ndef = off;  off = align_up(off + (size_t)p->units * p->n_ch * 4, 256);
-    p->off_offs = off;  off = align_up(off + (size_t)p->units * p->n_ch * 4, 256);
-    p->off_part = off;  off = align_up(off + (size_t)p->units * p->G * p->n_ch * kPartStride * 4, 256);
+    p->off_ndef = off;  off = align_up(off + (size_t)p->units * n_ws * 4, 256);
+    p->off_offs = off;  off = align_up(off + (size_t)p->units * n_ws * 4, 256);
+    p->off_part = off;  off = align_up(off + (size_t)p->units * p->G * n_ws * kPartStride * 4, 256);
     p->total = off;
     return true;
 }

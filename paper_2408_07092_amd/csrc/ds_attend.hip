@@ -1164,10 +1164,15 @@ static size_t ra_shmem(const Plan &p) { return (size_t)p.ch * 4 + (size_t)p.ch *
 static RaKernel ra_kernel(const Plan &p, const ds_shape_t &s, int smode)
 {
     const int gt = pick_gt(p.G);
-    if (gt <= 2 && !streams_past_caches(p, s) && !(smode && gt == 1 && ra_shmem(p) > (64u << 10) && p.n_ch == 1))
+    // one workgroup per unit that has a CU to itself: 1024 threads, eight rows per slot in flight.
+    // More than 64 KiB of LDS let no second one in; with less, units of more than 6K tokens that
+    // leave a quarter of the CUs without one (128 units of 8K tokens 23.1 -> 21.6 us against 256
+    // threads; 192 units 24.0 -> 24.1, 256 units 26.4 -> 27.0, 32 units of 6K 15.8 -> 17.6).
+    const bool own_cu = smode && gt == 1 && p.n_ch == 1 &&
+                        (ra_shmem(p) > (64u << 10) || (p.ch > 6144 && p.units * 4 < p.cus * 3));
+    if (gt <= 2 && !streams_past_caches(p, s) && !own_cu)
         return {gt == 2 ? ra_fn<2, kRowsPerSlot, false>(smode) : ra_fn<1, kRowsPerSlot, false>(smode), 256};
-    // one workgroup per unit that has a CU to itself (LDS): 1024 threads, eight rows per slot in flight
-    if (smode && gt == 1 && ra_shmem(p) > (64u << 10) && p.n_ch == 1) return {ra_fn<1, 8>(smode), 1024};
+    if (own_cu) return {ra_fn<1, 8>(smode), 1024};
     switch (gt) {
     case 16: return {ra_fn<16, kRowsPerSlot>(smode), 256};
     case 8: return {ra_fn<8, kRowsPerSlot>(smode), 256};
