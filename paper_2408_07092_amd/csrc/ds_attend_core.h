@@ -455,7 +455,10 @@ __device__ __forceinline__ void merge_partials(const float *part_unit, int G, in
                                                float (*red)[kD], float (*red_ml)[2], Wait wait_chunk)
 {
     const int tid = threadIdx.x;
-    const int gph = (G >= 8) ? 1 : (G >= 4) ? 2 : (G >= 2) ? 4 : 8;  // groups per head
+    // groups per head; every group keeps eight partials in flight.  A round of heads and a batch of
+    // partials are a dependent round trip each, about 1 us of the launch's end.
+    const int gph = (G > 4) ? 1 : (G > 2) ? 2 : (G == 2) ? 4 : 8;
+    constexpr int kBatch = 8;
     const int hpr = 8 / gph;                                          // heads per round
     const int cl = tid >> 5, cg = tid & 31;
     const int hr = cl / gph, sub = cl % gph;
@@ -466,11 +469,11 @@ __device__ __forceinline__ void merge_partials(const float *part_unit, int G, in
         const bool active = g < G;
         const float *ph = part_unit + (size_t)(active ? g : 0) * n_ch * kPartStride;
         // every group runs the same number of batches so that wait_chunk stays wave-uniform
-        for (int c0 = sub; c0 - sub < n_ch; c0 += gph * 4) {
-            float2 ml[4];
-            float4 v[4];
+        for (int c0 = sub; c0 - sub < n_ch; c0 += gph * kBatch) {
+            float2 ml[kBatch];
+            float4 v[kBatch];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < kBatch; ++i) {
                 const int cc = c0 + i * gph;
                 const bool have = active && cc < n_ch;
                 wait_chunk(cc, have);
@@ -486,7 +489,7 @@ __device__ __forceinline__ void merge_partials(const float *part_unit, int G, in
                 }
             }
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < kBatch; ++i) {
                 if (ml[i].x != kNegInf) {
                     const float mn = fmaxf(m, ml[i].x);
                     const float so = (m == kNegInf) ? 0.0f : __builtin_amdgcn_exp2f(m - mn);
