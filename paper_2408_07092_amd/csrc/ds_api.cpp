@@ -207,17 +207,20 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose)
     }
     // One workgroup also takes a unit of up to 6K tokens, and with half as many units as compute units
     // one of up to 8K, when it can score it: what passes between several costs more than one compute
-    // unit's rate (about 33 GB/s).  Several against one, us per layer: single heads, 8 channels,
-    // 32 units of 5000 tokens 17.7 -> 15.0, 128 of 6016 22.7 -> 18.7, 128 of 8192 25.1 -> 21.6; 16
-    // channels 19.5 -> 18.7, 24.1 -> 21.5, 27.5 -> 25.7; groups of 4 and 8, 8 to 64 units of 6016
-    // 20.1 .. 22.2 -> 19.4 .. 21.0, 128 of 8192 25.4 -> 24.8.  On the other side of the line: 64 single
-    // heads of 8192 tokens 20.8 -> 20.5 and with 16 channels 22.2 -> 24.0, 32 to 64 groups of 4
-    // 21.3 -> 23.8, 128 single heads of 10240 with 16 channels 30.0 -> 30.1.  Pairs gain less: 64 units
-    // of 6016 20.8 -> 21.6, 128 23.6 -> 22.0, 128 of 8192 26.3 -> 26.9.
+    // unit's rate (about 33 GB/s) over a sixteenth of so many rows.  Several against one, us per
+    // layer: single heads, 8 channels, 32 units of 5000 tokens 17.7 -> 15.0, 128 of 6016 22.7 -> 18.7,
+    // 128 of 8192 25.1 -> 21.6; 16 channels 19.5 -> 18.7, 24.1 -> 21.5, 27.5 -> 25.7; groups of 4 and 8,
+    // 8 to 64 units of 6016 20.1 .. 22.2 -> 19.4 .. 21.0, 128 of 8192 25.4 -> 24.8.  On the other side
+    // of the line: 64 single heads of 8192 tokens 20.8 -> 20.5 and with 16 channels 22.2 -> 24.0, 32
+    // to 64 groups of 4 21.3 -> 23.8, 128 single heads of 10240 with 16 channels 30.0 -> 30.1; 680 rows,
+    // 80 single heads of 5445 22.0 -> 24.7.  Pairs gain less: 64 units of 6016 20.8 -> 21.6, 128
+    // 23.6 -> 22.0, 128 of 8192 26.3 -> 26.9.
     // (The workspace keeps the room of the plan with several.)
     const int n_ws = (s.L + ch - 1) / ch;
+    const bool half_full = p->units * 2 >= caps.cus;
+    const int one_wg_tokens = p->G == 2 ? (half_full ? 6144 : 0) : (half_full ? 8192 : 6144);
     if (n_ws > 1 && p->refine_attend && purpose == PLAN_DECODE_SCORING && tune_get(1) == 0 &&
-        s.L <= (p->G != 2 && p->units * 2 >= caps.cus ? 8192 : 6144) && (p->G != 2 || p->units * 2 >= caps.cus)) {
+        s.L <= one_wg_tokens && p->k_eff <= one_wg_tokens / 16) {
         ch = (s.L + 255) & ~255;
         p->unit_groups = 1;
     }
