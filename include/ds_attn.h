@@ -349,7 +349,7 @@ ds_status_t ds_profile_read(int id, double *total_ms, int64_t *launches);
  *   knob 4: where the exact top-k threshold is settled on the three-launch path: 0 = automatic
  *           (in the scoring launch for units of up to 8K tokens), 1 = always in a separate
  *           candidate launch, 2 = always in the scoring launch.  On launch shape 4 with a label
- *           cache of 8 or 16 fp16 channels, or a 4-bit one of up to 16 channels whose token
+ *           cache of 4, 8, 12, 16 or 24 fp16 channels, or a 4-bit one of up to 16 channels whose token
  *           rows 16-byte loads can take (L_max a multiple of 4, of 2 above 8 channels), the
  *           attention launch can do the scoring as well (one launch in all): 0 = when a unit
  *           has one workgroup, or the whole grid is resident at once (single heads and pairs:
