@@ -28,6 +28,7 @@ struct PickLanes {
 // token's V row).  Bound by the read of the K rows' lines: 512 MiB of K in 94 us, where a bare read of
 // them takes 80 and every other way to pick the values (whole rows through LDS, wider stores, other
 // workgroup sizes) 93 to 107; without the streaming mark 104.
+template <bool ST>
 __global__ __launch_bounds__(kWG) void k_label(const uint16_t *__restrict__ K,
                                                const int32_t *__restrict__ channels,
                                                uint16_t *__restrict__ label, int Hkv, int L_max,
@@ -40,11 +41,15 @@ __global__ __launch_bounds__(kWG) void k_label(const uint16_t *__restrict__ K,
     const int lo = blockIdx.x * per_wg, hi = min(n, lo + per_wg);
     const uint16_t *Ku = K + ((size_t)u * L_max + t0) * kv_stride + c;
     uint16_t *lu = label + ((size_t)u * L_max + t0) * r + p.j;
-    for (int i = lo + p.i0; i < hi; i += kPick * p.P) {
+    for (int ib = lo; ib < hi; ib += kPick * p.P) {
+        const int i = ib + p.i0;
         uint16_t x[kPick];
 #pragma unroll
         for (int e = 0; e < kPick; ++e)
-            x[e] = __builtin_nontemporal_load(Ku + (size_t)min(i + e * p.P, hi - 1) * kv_stride);
+            if (ib + e * p.P < hi) {
+                const uint16_t *src = Ku + (size_t)min(i + e * p.P, hi - 1) * kv_stride;
+                x[e] = ST ? __builtin_nontemporal_load(src) : *src;
+            }
 #pragma unroll
         for (int e = 0; e < kPick; ++e)
             if (i + e * p.P < hi) lu[(size_t)(i + e * p.P) * r] = x[e];
@@ -357,12 +362,22 @@ hipError_t launch_label(const void *K, const int32_t *channels, void *label, con
                         int t0, int n, hipStream_t st, int kv_stride)
 {
     if (n <= 0) return hipSuccess;
-    // 256 tokens to a workgroup (64 KiB of K; one round of loads per thread with 8 channels)
+    // 256 tokens to a workgroup (64 KiB of K; one round of loads per thread with 8 channels), fewer
+    // until there are 16 workgroups for every compute unit: 256 units of 300 tokens with 24 channels
+    // 13.2 -> 8.1 us, of 2500 42.6 -> 37.6.
     const int round = kPick * (kWG / s.r);
-    const int per_wg = round * std::max(1, 256 / round);
-    DS_LAUNCH(KID_LABEL, k_label, dim3((n + per_wg - 1) / per_wg, s.B * s.Hkv), dim3(kWG), 0, st,
-                       static_cast<const uint16_t *>(K), channels, static_cast<uint16_t *>(label),
-                       s.Hkv, s.L_max, s.r, t0, n, kv_stride, per_wg);
+    int per_wg = round * std::max(1, 256 / round);
+    const int64_t units = (int64_t)s.B * s.Hkv, want = 16ll * device_caps().cus;
+    while (per_wg > kWG / s.r && units * ((n + per_wg - 1) / per_wg) < want) per_wg = (per_wg + 1) / 2;
+    const dim3 grid((n + per_wg - 1) / per_wg, s.B * s.Hkv);
+    const auto *Kh = static_cast<const uint16_t *>(K);
+    auto *lh = static_cast<uint16_t *>(label);
+    // Rows that the memory-side cache (256 MiB) can hold may be there from the prefill and are not
+    // marked as streaming: 256 units of 2500 tokens (164 MB) 28.7 us with the mark.
+    if (units * n * kv_stride * 2 > (256ll << 20))
+        DS_LAUNCH(KID_LABEL, k_label<true>, grid, dim3(kWG), 0, st, Kh, channels, lh, s.Hkv, s.L_max, s.r, t0, n, kv_stride, per_wg);
+    else
+        DS_LAUNCH(KID_LABEL, k_label<false>, grid, dim3(kWG), 0, st, Kh, channels, lh, s.Hkv, s.L_max, s.r, t0, n, kv_stride, per_wg);
     return hipGetLastError();
 }
 
