@@ -363,11 +363,11 @@ hipError_t launch_label(const void *K, const int32_t *channels, void *label, con
 {
     if (n <= 0) return hipSuccess;
     // 256 tokens to a workgroup (64 KiB of K; one round of loads per thread with 8 channels), fewer
-    // until there are 16 workgroups for every compute unit: 256 units of 300 tokens with 24 channels
-    // 13.2 -> 8.1 us, of 2500 42.6 -> 37.6.
+    // until there are four workgroups for every compute unit (256 units of 300 tokens with 24 channels
+    // 6.7 us; until there are 16 7.6, and 32 units of 2500 7.6 against 6.8).
     const int round = kPick * (kWG / s.r);
     int per_wg = round * std::max(1, 256 / round);
-    const int64_t units = (int64_t)s.B * s.Hkv, want = 16ll * device_caps().cus;
+    const int64_t units = (int64_t)s.B * s.Hkv, want = 4ll * device_caps().cus;
     while (per_wg > kWG / s.r && units * ((n + per_wg - 1) / per_wg) < want) per_wg = (per_wg + 1) / 2;
     const dim3 grid((n + per_wg - 1) / per_wg, s.B * s.Hkv);
     const auto *Kh = static_cast<const uint16_t *>(K);
