@@ -152,7 +152,9 @@ __global__ __launch_bounds__(kWG, (GT == 1 ? 8 : 1)) void k_attend(AttendArgs a)
         if (!last) return;
     }
     if (tid == 0) a.ctl_rw[u].arrive_c = 0u;
-    merge_partials(a.part + (size_t)u * a.G * a.n_ch * kPartStride, a.G, a.n_ch,
+    // (single heads: eight partials in flight do not fit the 64 registers that eight wavefronts per
+    //  SIMD leave, 52 bytes a lane went to scratch; eight groups share a head's partials there anyway)
+    merge_partials<(GT == 1 ? 4 : 8)>(a.part + (size_t)u * a.G * a.n_ch * kPartStride, a.G, a.n_ch,
                    a.out + (size_t)u * a.G * kD, red, red_ml, [](int, bool) {});
     DS_TR(5);
 }
@@ -1056,7 +1058,7 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     if (!unit_ok) {
         poison_out();
     } else if constexpr (NW == 4) {  // (written for 256 threads; the wider variant never gets here)
-        merge_partials(a.part + (size_t)u * a.G * a.n_ch * kPartStride, a.G, a.n_ch,
+        merge_partials<8>(a.part + (size_t)u * a.G * a.n_ch * kPartStride, a.G, a.n_ch,
                        a.out + (size_t)u * a.G * kD, red, red_ml, [](int, bool) {});
     }
     DS_TR(7);

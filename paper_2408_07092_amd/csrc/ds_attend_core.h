@@ -450,15 +450,15 @@ __device__ __forceinline__ void wg_store_partial_mfma(const MfmaState &st, float
 // (G, n_ch).  wait_chunk(cc, active) is called by every lane of a group before
 // the group reads chunk cc (a no-op when all partials are already complete).
 // red: LDS [8][kD], red_ml: LDS [8][2].  All 256 threads must call it.
-template <class Wait>
+// kBatch partials of a group are in flight; the order in which they are folded does not depend on it.
+template <int kBatch, class Wait>
 __device__ __forceinline__ void merge_partials(const float *part_unit, int G, int n_ch, float *out_unit,
                                                float (*red)[kD], float (*red_ml)[2], Wait wait_chunk)
 {
     const int tid = threadIdx.x;
-    // groups per head; every group keeps eight partials in flight.  A round of heads and a batch of
-    // partials are a dependent round trip each, about 1 us of the launch's end.
+    // groups per head.  A round of heads and a batch of partials are a dependent round trip each,
+    // about 1 us of the launch's end.
     const int gph = (G > 4) ? 1 : (G > 2) ? 2 : (G == 2) ? 4 : 8;
-    constexpr int kBatch = 8;
     const int hpr = 8 / gph;                                          // heads per round
     const int cl = tid >> 5, cg = tid & 31;
     const int hr = cl / gph, sub = cl % gph;
