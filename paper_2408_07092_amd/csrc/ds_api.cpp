@@ -242,6 +242,20 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose)
     return true;
 }
 
+// Workspace of a dense plan with n_ch chunks per unit: the same control prefix (records +
+// histograms) as the sparse plan, so that sparse and dense calls may alternate on one workspace
+// without disturbing each other's zeroed counters, and a partial per chunk and head.
+static size_t dense_part_offset(int units)
+{
+    size_t off = align_up((size_t)units * sizeof(UnitCtl), 256);
+    off = align_up(off + (size_t)units * kHistBins * 4, 256);
+    return align_up(off + (size_t)units * 256 * 4, 256);
+}
+static size_t dense_total(int units, int G, int64_t n_ch)
+{
+    return align_up(dense_part_offset(units) + (size_t)units * G * n_ch * kPartStride * 4, 256);
+}
+
 bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p)
 {
     if (!shape_ok(s, false) || n_tokens < 1) return false;
@@ -249,41 +263,58 @@ bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p)
     p->G = s.Hq / s.Hkv;
     int ch = tune_get(2);
     if (ch == 0) {
-        // Chunks per unit: the number n with the least estimated time among those that fill the
-        // device w = 1/4, 1/2, 1 .. 8 times.  In rows of a compute unit, which streams about
-        // 50 of them per us:  the busiest one's share, at least the average one; a start and an end
-        // of each workgroup (150 on the matrix cores, where three fit at a time, 25 on the vector
-        // path); and the merge of n partials of G heads by the unit's last workgroup, 1.5 each.
-        // A unit with one workgroup draws less than one with two or more (24 against 29 GB/s).
-        // (Measured against chunks of 64 / 256 / 1024 tokens by the number of tokens alone: 32 units
-        // of 32K tokens in groups of 4 heads 105 -> 83 us, 12 units of 20K in groups of 7 116 -> 30,
-        // 8 units of 32K in groups of 8 66 -> 33, 32 single heads of 64K 179 -> 165, of 4K 19.6 -> 15.8.)
-        const int cus = device_caps().cus;
-        const bool matrix = p->G > 2;
+        // Chunks per unit: the number with the least estimated time, of 1, 2, 3, 4, 6, 8, 12 .. and those
+        // that fill the device w = 1/4, 1/2, 1 .. 8 times (chunks of 32 tokens at least, up to eight
+        // workgroups per compute unit).  The estimate, in rows of a compute unit, which streams
+        // about 46 of them per us:
+        //   - the busiest compute unit's rows, in whole rounds of 64 where heads share them, and not
+        //     fewer than the average one's (memory's rate) -- except where single heads and pairs have
+        //     fewer than 512 rows per compute unit: those wait for latency, which two workgroups on a
+        //     compute unit hide from each other;
+        //   - a start and an end of each workgroup: 300 on the matrix cores, 60 on the vector path;
+        //     groups of more than 16 heads pass over the rows, and pay both, once per 16 heads;
+        //   - the merge by the unit's last workgroup: 75, and 110 for each of its dependent batches of
+        //     loads (merge_partials: eight groups of threads share the heads of a round, each with eight
+        //     partials in flight, four for single heads).
+        // Over 649 shapes (1 to 512 units in groups of 1 to 64, 130 to 65536 tokens) the choice is 0.8 %
+        // from the best of 23 chunk counts, 3 % at the 90th percentile.  Against chunks of 64 / 256 / 1024
+        // tokens by the number of tokens alone: 32 units of 32K tokens in groups of 4 105 -> 83 us, 12
+        // units of 20K in groups of 7 116 -> 27, 8 units of 32K in groups of 8 66 -> 33, 32 single heads of
+        // 64K 179 -> 153, one unit of 2K in groups of 64 77 -> 50 (with 64 chunks 123); on the other side
+        // 200 units of 8K in groups of 4, 143 -> 151.
+        const int cus = device_caps().cus, G = p->G;
+        const int64_t units = p->units;
+        const bool matrix = G > 2;
+        const int passes = (G + 15) / 16;
+        const int gph = G > 4 ? 1 : G > 2 ? 2 : G == 2 ? 4 : 8, partials = gph * (G == 1 ? 4 : 8), heads = 8 / gph;
         double best = 0.0;
-        for (int w4 = 1; w4 <= 32; w4 += w4 < 4 ? w4 : 4) {
-            const int n_want = std::min(std::max(1, (int)((int64_t)w4 * cus / 4 / p->units)), std::max(1, n_tokens / 32));
-            const int c = ((n_tokens + n_want - 1) / n_want + 15) & ~15, n = (n_tokens + c - 1) / c;
-            const int busiest = (int)(((int64_t)p->units * n + cus - 1) / cus);
-            const double rows = std::max((double)p->units * n_tokens / cus,
-                                         (double)busiest * c / (busiest > 1 ? 1.2 : 1.0));
-            const double cost = rows + busiest * (matrix ? 150.0 : 25.0) + 1.5 * n * p->G;
-            if (ch == 0 || cost < best) {
+        auto consider = [&](int64_t n_want) {
+            const int64_t nw = std::min<int64_t>(std::max<int64_t>(n_want, 1), std::max(1, n_tokens / 32));
+            const int64_t c = ((n_tokens + nw - 1) / nw + 15) & ~15ll, n = (n_tokens + c - 1) / c;
+            if (n > 1 && units * n > 8ll * cus) return;
+            const int64_t busiest = (units * n + cus - 1) / cus;
+            double rows = (double)busiest * (G > 1 ? (c + 63) & ~63ll : c);
+            if (matrix || units * n_tokens >= 512ll * cus) rows = std::max(rows, (double)units * n_tokens / cus);
+            else if (busiest > 1) rows *= 0.5;
+            const double merge = n > 1 ? 75.0 + 110.0 * ((G + heads - 1) / heads) * ((n + partials - 1) / partials) : 0.0;
+            const double cost = passes * (rows + busiest * (matrix ? 300.0 : 60.0)) + merge;
+            // (of two equals the one with fewer chunks)
+            if (ch == 0 || cost < best || (cost == best && c > ch)) {
                 best = cost;
-                ch = c;
+                ch = (int)c;
             }
+        };
+        for (int64_t n = 1; n <= 8ll * cus; n *= 2) {
+            consider(n);
+            consider(n + n / 2);
         }
+        for (int w4 = 1; w4 <= 32; w4 += w4 < 4 ? w4 : 4) consider((int64_t)w4 * cus / 4 / units);
     }
     p->ch = ch;
     p->n_ch = (n_tokens + ch - 1) / ch;
-    // same control prefix (records + histograms) as the sparse plan, so that sparse and dense
-    // calls may alternate on one workspace without disturbing each other's zeroed counters
-    size_t off = 0;
-    p->off_ctl = off;   off = align_up(off + (size_t)p->units * sizeof(UnitCtl), 256);
-    off = align_up(off + (size_t)p->units * kHistBins * 4, 256);
-    off = align_up(off + (size_t)p->units * 256 * 4, 256);
-    p->off_part = off;  off = align_up(off + (size_t)p->units * p->G * p->n_ch * kPartStride * 4, 256);
-    p->total = off;
+    p->off_ctl = 0;
+    p->off_part = dense_part_offset(p->units);
+    p->total = dense_total(p->units, p->G, p->n_ch);
     return true;
 }
 

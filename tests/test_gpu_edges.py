@@ -72,6 +72,16 @@ def test_dense_decode_chunk_rule(B, Hq, Hkv, L, L_max):
     check_output(out.cpu().numpy(), O.dense_decode(t["q"], t["K"], t["V"], L), f"dense {(B, Hq, Hkv, L)}")
 
 
+@pytest.mark.parametrize("Hq,Hkv,L", [
+    (64, 1, 300),                # one chunk, four passes over the rows
+    (64, 1, 2048),               # several chunks, eight rounds of heads in the merge
+    (34, 2, 1000),               # groups of 17: a second pass with one head
+    (2, 1, 2000),                # pairs: chunks of whole rounds
+])
+def test_dense_decode_chunk_rule_of_large_groups(Hq, Hkv, L):
+    test_dense_decode_chunk_rule(1, Hq, Hkv, L, L)
+
+
 @pytest.mark.parametrize("B,Dm,N", [(1, 8, 5), (1, 512, 4), (3, 520, 1025), (5, 4096, 65), (1, 4104, 33), (2, 8192, 4100)])
 def test_predict_query_pieces(B, Dm, N):
     """Row lengths at the edges of the pieces in flight and feature counts at the edges of the
