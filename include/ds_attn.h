@@ -43,7 +43,8 @@
  *     idx, workspace: 16 bytes).  Workspace too small -> DS_ERR_WORKSPACE.
  *     A failed launch -> DS_ERR_HIP.  k > L is not an error: k_eff = min(k, L).
  *   - Inputs must be finite; behaviour on NaN/Inf is unspecified.
- *   - Results are bit-identical from run to run for the same inputs and shape.
+ *   - Results are bit-identical from run to run for the same inputs, shape and
+ *     workspace size.
  */
 #ifndef DS_ATTN_H
 #define DS_ATTN_H
@@ -162,7 +163,10 @@ ds_status_t ds_append_label_q4(const void *K, const int32_t *channels, void *lab
                                int32_t n_new, void *stream);
 
 /* Bytes of workspace any decode/select/attend call with this shape needs
- * (a multiple of 256).  Pure host function; 0 if the shape is invalid. */
+ * (a multiple of 256).  Pure host function; 0 if the shape is invalid.
+ * Enough for ds_dense_decode with fewer tokens of the same heads as well: a
+ * dense call whose workspace is smaller than its fastest plan splits its units
+ * into fewer chunks (the last bits of a sum can then differ). */
 size_t ds_workspace_bytes(const ds_shape_t *shape);
 /* Enqueues the clearing of a freshly allocated workspace (all workspace_bytes,
  * a multiple of 16).  Required once before the first call that uses it: the

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 #include <mutex>
 #include <vector>
@@ -256,12 +257,21 @@ static size_t dense_total(int units, int G, int64_t n_ch)
     return align_up(dense_part_offset(units) + (size_t)units * G * n_ch * kPartStride * 4, 256);
 }
 
-bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p)
+size_t dense_room(const ds_shape_t &s, int n_tokens)
+{
+    const int units = s.B * s.Hkv;
+    const int64_t tokens = (int64_t)units * n_tokens;
+    const int ch = tune_get(2) ? tune_get(2) : tokens >= (1 << 20) ? 1024 : tokens >= (1 << 18) ? 256 : 64;
+    return dense_total(units, s.Hq / s.Hkv, (n_tokens + ch - 1) / ch);
+}
+
+bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p, size_t workspace_bytes)
 {
     if (!shape_ok(s, false) || n_tokens < 1) return false;
     p->units = s.B * s.Hkv;
     p->G = s.Hq / s.Hkv;
     int ch = tune_get(2);
+    const size_t room = workspace_bytes >= dense_room(s, n_tokens) ? workspace_bytes : SIZE_MAX;
     if (ch == 0) {
         // Chunks per unit: the number with the least estimated time, of 1, 2, 3, 4, 6, 8, 12 .. and those
         // that fill the device w = 1/4, 1/2, 1 .. 8 times (chunks of 32 tokens at least, up to eight
@@ -282,6 +292,8 @@ bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p)
         // units of 20K in groups of 7 116 -> 27, 8 units of 32K in groups of 8 66 -> 33, 32 single heads of
         // 64K 179 -> 153, one unit of 2K in groups of 64 77 -> 50 (with 64 chunks 123); on the other side
         // 200 units of 8K in groups of 4, 143 -> 151.
+        // A workspace that has dense_room() but not the chosen plan's takes the best of those that fit it:
+        // one sized for more tokens of the same heads serves every shorter call.
         const int cus = device_caps().cus, G = p->G;
         const int64_t units = p->units;
         const bool matrix = G > 2;
@@ -291,7 +303,7 @@ bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p)
         auto consider = [&](int64_t n_want) {
             const int64_t nw = std::min<int64_t>(std::max<int64_t>(n_want, 1), std::max(1, n_tokens / 32));
             const int64_t c = ((n_tokens + nw - 1) / nw + 15) & ~15ll, n = (n_tokens + c - 1) / c;
-            if (n > 1 && units * n > 8ll * cus) return;
+            if ((n > 1 && units * n > 8ll * cus) || dense_total(p->units, G, n) > room) return;
             const int64_t busiest = (units * n + cus - 1) / cus;
             double rows = (double)busiest * (G > 1 ? (c + 63) & ~63ll : c);
             if (matrix || units * n_tokens >= 512ll * cus) rows = std::max(rows, (double)units * n_tokens / cus);
@@ -519,10 +531,10 @@ size_t ds_workspace_bytes(const ds_shape_t *shape)
     for (PlanFor purpose : {PLAN_SELECT, PLAN_DECODE, PLAN_DECODE_SCORING}) {
         if (make_plan(*shape, &p, purpose)) {
             need = std::max(need, p.total);
-            if (make_dense_plan(*shape, p.k_eff, &rp)) need = std::max(need, rp.total);
+            if (make_dense_plan(*shape, p.k_eff, &rp)) need = std::max({need, rp.total, dense_room(*shape, p.k_eff)});
         }
     }
-    if (make_dense_plan(*shape, shape->L, &dp)) need = std::max(need, dp.total);
+    if (make_dense_plan(*shape, shape->L, &dp)) need = std::max({need, dp.total, dense_room(*shape, shape->L)});
     return need;
 }
 
@@ -827,7 +839,7 @@ ds_status_t ds_dense_decode(const void *q, const void *K, const void *V, float *
     if (!q || !K || !V || !out || !workspace || !shape) return DS_ERR_NULL;
     if (!shape_ok(*shape, false)) return DS_ERR_SHAPE;
     DensePlan p;
-    if (!make_dense_plan(*shape, shape->L, &p)) return DS_ERR_UNSUPPORTED;
+    if (!make_dense_plan(*shape, shape->L, &p, workspace_bytes)) return DS_ERR_UNSUPPORTED;
     if (!aligned(K, 256) || !aligned(V, 256) || !aligned(q, 16) || !aligned(out, 16) ||
         !aligned(workspace, 16))
         return DS_ERR_ALIGN;
@@ -866,7 +878,7 @@ ds_status_t ds_attend_rows(const void *q, const void *KV_rows, float *out, void 
     if (!shape_ok(*shape, true)) return DS_ERR_SHAPE;
     const int n_rows = std::min(shape->k, shape->L);
     DensePlan p;
-    if (!make_dense_plan(*shape, n_rows, &p)) return DS_ERR_UNSUPPORTED;
+    if (!make_dense_plan(*shape, n_rows, &p, workspace_bytes)) return DS_ERR_UNSUPPORTED;
     if (!aligned(KV_rows, 256) || !aligned(q, 16) || !aligned(out, 16) || !aligned(workspace, 16))
         return DS_ERR_ALIGN;
     if (workspace_bytes < p.total) return DS_ERR_WORKSPACE;

@@ -100,7 +100,10 @@ void device_caps_pretend(const DeviceCaps *caps);  // test hook: overrides devic
 // decode call, or a decode call whose attention launch may do the scoring as well.
 enum PlanFor { PLAN_SELECT = 0, PLAN_DECODE = 1, PLAN_DECODE_SCORING = 2 };
 bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose = PLAN_SELECT);
-bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p);
+bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p, size_t workspace_bytes = SIZE_MAX);
+// Workspace with which a dense or gathered-rows call is never refused: that of chunks of 64, 256 or
+// 1024 tokens by the number of tokens.  (A plan may want less, or more; then it makes do.)
+size_t dense_room(const ds_shape_t &s, int n_tokens);
 
 // Per-kernel timing: while it is on, prof_events hands out a start and a stop event for one
 // launch of kernel `id` (false when it is off or no event could be made) and remembers the pair.

@@ -82,6 +82,22 @@ def test_dense_decode_chunk_rule_of_large_groups(Hq, Hkv, L):
     test_dense_decode_chunk_rule(1, Hq, Hkv, L, L)
 
 
+@pytest.mark.parametrize("Hq,Hkv,L,L_ws", [(1, 1, 256, 300), (1, 1, 1024, 1300), (4, 1, 800, 1300), (56, 8, 800, 800)])
+def test_dense_decode_in_the_workspace_of_more_tokens(Hq, Hkv, L, L_ws):
+    """A workspace sized for more tokens (or one with room for chunks of 64 tokens and no more) is not
+    refused where the chunk rule would like a larger one: fewer chunks, the same result."""
+    w = Workload("t", 1, Hq, Hkv, 128, L, 8, 1, 1)
+    t = make_layer_numpy(w)
+    shp = ds.shape(1, Hq, Hkv, 128, L, L, 8, 0)
+    n = ds.ds_workspace_bytes(ds.shape(1, Hq, Hkv, 128, L_ws, L_ws, 8, 0))
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    ds.ds_workspace_init(ws)
+    out = torch.full((1, Hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+    ds.ds_dense_decode(to_dev(t["q"]), to_dev(t["K"]), to_dev(t["V"]), out, ws, shp)
+    torch.cuda.synchronize()
+    check_output(out.cpu().numpy(), O.dense_decode(t["q"], t["K"], t["V"], L), f"dense {(Hq, Hkv, L, L_ws)}")
+
+
 @pytest.mark.parametrize("B,Dm,N", [(1, 8, 5), (1, 512, 4), (3, 520, 1025), (5, 4096, 65), (1, 4104, 33), (2, 8192, 4100)])
 def test_predict_query_pieces(B, Dm, N):
     """Row lengths at the edges of the pieces in flight and feature counts at the edges of the

@@ -12,14 +12,14 @@ class DensePlan(ctypes.Structure):
                [(n, ctypes.c_size_t) for n in ("off_ctl", "off_part", "total")]
 
 
-def dense_plan(units, G, n_tokens):
+def dense_plan(units, G, n_tokens, workspace_bytes=2 ** 64 - 1):
     """make_dense_plan of the library (an internal C++ function: by its mangled name)."""
-    fn = getattr(ds.lib(), "_ZN2ds15make_dense_planERK10ds_shape_tiPNS_9DensePlanE")
+    fn = getattr(ds.lib(), "_ZN2ds15make_dense_planERK10ds_shape_tiPNS_9DensePlanEm")
     fn.restype = ctypes.c_bool
-    fn.argtypes = [ctypes.POINTER(ds.binding.DsShape), ctypes.c_int, ctypes.POINTER(DensePlan)]
+    fn.argtypes = [ctypes.POINTER(ds.binding.DsShape), ctypes.c_int, ctypes.POINTER(DensePlan), ctypes.c_size_t]
     plan = DensePlan()
     shp = ds.shape(1, units * G, units, 128, n_tokens, n_tokens, 8, 1)
-    assert fn(ctypes.byref(shp), n_tokens, ctypes.byref(plan))
+    assert fn(ctypes.byref(shp), n_tokens, ctypes.byref(plan), workspace_bytes)
     return plan
 
 
@@ -52,3 +52,18 @@ def mi355x():
 def test_dense_plan_takes_a_chunk_count_near_the_fastest(units, G, tokens, lo, hi):
     p = dense_plan(units, G, tokens)
     assert lo <= p.n_ch <= hi and (p.n_ch - 1) * p.ch < tokens <= p.n_ch * p.ch and p.ch % 16 == 0
+
+
+@pytest.mark.parametrize("units", [1, 3, 12, 32, 200, 512])
+@pytest.mark.parametrize("G", [1, 2, 7, 16, 64])
+@pytest.mark.parametrize("k", [0, 1])
+def test_workspace_for_more_tokens_serves_fewer(units, G, k):
+    """A workspace of ds_workspace_bytes() for some number of tokens is enough for dense decode of
+    every smaller number (a cache that grows by a token per step is one allocation)."""
+    lengths = [1, 33, 100, 256, 300, 512, 600, 800, 1024, 1300, 2048, 4096, 5000, 8191, 8192, 16384, 40000, 65536]
+    for i, longer in enumerate(lengths):
+        have = ds.ds_workspace_bytes(ds.shape(1, units * G, units, 128, longer, longer, 8, k * max(1, longer // 16)))
+        for tokens in lengths[:i + 1]:
+            p = dense_plan(units, G, tokens, have)
+            assert p.total <= have, (tokens, longer, p.n_ch)
+            assert p.off_part + units * G * p.n_ch * 132 * 4 <= p.total
