@@ -9,49 +9,60 @@ namespace ds {
 // The label values of K rows are picked by a fixed thread layout: thread tid takes channel j =
 // tid mod r of the rows i0 = tid / r, i0 + P, i0 + 2 P, .. with P = 256 / r rows per pass (the last
 // 256 - P r threads idle), so that its channel stays in a register and no element costs a division.
-// A wavefront's load covers every line of 64 / r rows once; eight passes are in flight.
-constexpr int kPick = 8;
+// A wavefront's load covers every line of 64 / r rows once.
+struct PickLayout {
+    int r, P;
+    uint32_t inv;  // tid / r == tid * inv >> 16 for every thread of a workgroup and r <= 128
+};
+static PickLayout pick_layout(int r) { return {r, kWG / r, (65535u + (uint32_t)r) / (uint32_t)r}; }
 struct PickLanes {
     int P, j, i0;
     bool on;
-    __device__ __forceinline__ explicit PickLanes(int r)
+    __device__ __forceinline__ explicit PickLanes(const PickLayout &l)
     {
-        P = kWG / r;
-        j = (int)threadIdx.x % r;
-        i0 = (int)threadIdx.x / r;
+        P = l.P;
+        i0 = (int)(threadIdx.x * l.inv >> 16);
+        j = (int)threadIdx.x - i0 * l.r;
         on = i0 < P;
     }
 };
 
 // label[u, t, j] = K[u, t, channels[h, j]] for t in [t0, t0 + n): a bit copy, `per_wg` tokens to a
 // workgroup (kv_stride halves from row to row: d, or 2d when each K row is followed by the
-// token's V row).  Bound by the read of the K rows' lines: 512 MiB of K in 94 us, where a bare read of
-// them takes 80 and every other way to pick the values (whole rows through LDS, wider stores, other
-// workgroup sizes) 93 to 107; without the streaming mark 104.
-template <bool ST>
+// token's V row); h = blockIdx.y, batch blockIdx.z.  Bound by the read of the K rows' lines: 512 MiB of K,
+// 8 channels, in 94 us, where a bare read of them takes 80.  PICK passes of a thread are in flight (see
+// launch_label for where one pass, without the streaming mark, is better than eight with it).
+template <int PICK, bool ST>
 __global__ __launch_bounds__(kWG) void k_label(const uint16_t *__restrict__ K,
                                                const int32_t *__restrict__ channels,
-                                               uint16_t *__restrict__ label, int Hkv, int L_max,
-                                               int r, int t0, int n, int kv_stride, int per_wg)
+                                               uint16_t *__restrict__ label, int L_max,
+                                               PickLayout pl, int t0, int n, int kv_stride, int per_wg)
 {
-    const PickLanes p(r);
+    const PickLanes p(pl);
     if (!p.on) return;
-    const int u = blockIdx.y, h = u % Hkv;
+    const int h = blockIdx.y, u = blockIdx.z * gridDim.y + h, r = pl.r;
     const int c = channels[h * r + p.j];
     const int lo = blockIdx.x * per_wg, hi = min(n, lo + per_wg);
     const uint16_t *Ku = K + ((size_t)u * L_max + t0) * kv_stride + c;
     uint16_t *lu = label + ((size_t)u * L_max + t0) * r + p.j;
-    for (int ib = lo; ib < hi; ib += kPick * p.P) {
+    if constexpr (PICK == 1) {
+        for (int i = lo + p.i0; i < hi; i += p.P) {
+            const uint16_t *src = Ku + (size_t)i * kv_stride;
+            lu[(size_t)i * r] = ST ? __builtin_nontemporal_load(src) : *src;
+        }
+        return;
+    }
+    for (int ib = lo; ib < hi; ib += PICK * p.P) {
         const int i = ib + p.i0;
-        uint16_t x[kPick];
+        uint16_t x[PICK];
 #pragma unroll
-        for (int e = 0; e < kPick; ++e)
+        for (int e = 0; e < PICK; ++e)
             if (ib + e * p.P < hi) {
                 const uint16_t *src = Ku + (size_t)min(i + e * p.P, hi - 1) * kv_stride;
                 x[e] = ST ? __builtin_nontemporal_load(src) : *src;
             }
 #pragma unroll
-        for (int e = 0; e < kPick; ++e)
+        for (int e = 0; e < PICK; ++e)
             if (i + e * p.P < hi) lu[(size_t)(i + e * p.P) * r] = x[e];
     }
 }
@@ -111,6 +122,8 @@ __global__ __launch_bounds__(kWG) void k_q4_zero(uint32_t *amax, size_t n, uint3
     for (size_t i = i0; i < (size_t)units; i += step) codes[i * unit_words] = 0u;
 }
 
+constexpr int kPick = 8;  // passes of a thread in flight
+
 // Builds the 4-bit label cache with one read of the K rows, which bounds it (64 units of 16K tokens,
 // 16 channels: 268 MB in 54 us; a pass for the maxima and a pass for the codes, each reading the
 // rows with a division per element: 60 + 226 us).  A workgroup picks the label values of
@@ -133,7 +146,7 @@ __global__ __launch_bounds__(kWG) void k_q4_build(const uint16_t *__restrict__ K
     __shared__ uint32_t s_ok, s_last;
     const int tid = threadIdx.x, u = blockIdx.y, h = u % Hkv;
     const int W = (r + 7) / 8, stride = 8 * W;
-    const PickLanes p(r);
+    const PickLanes p(PickLayout{r, kWG / r, (65535u + (uint32_t)r) / (uint32_t)r});
     const int c = p.on ? channels[h * r + p.j] : 0;
     if (tid < kD) mx_sh[tid] = 0u;
     const uint16_t *Ku = K + (size_t)u * L_max * kD + c;
@@ -362,22 +375,34 @@ hipError_t launch_label(const void *K, const int32_t *channels, void *label, con
                         int t0, int n, hipStream_t st, int kv_stride)
 {
     if (n <= 0) return hipSuccess;
-    // 256 tokens to a workgroup (64 KiB of K; one round of loads per thread with 8 channels), fewer
-    // until there are four workgroups for every compute unit (256 units of 300 tokens with 24 channels
-    // 6.7 us; until there are 16 7.6, and 32 units of 2500 7.6 against 6.8).
-    const int round = kPick * (kWG / s.r);
+    const PickLayout pl = pick_layout(s.r);
+    // How many rows a workgroup takes, and how, goes by the size of the K rows.  Measured cold (several
+    // K in turn), just after a kernel has written K (with that write), and with K built again and again, 1
+    // to 512 units of 1 to 131072 tokens, 1 to 128 channels; us, cold where nothing else is said:
+    // - One pass at a time and many workgroups, whose wavefronts hide the latency: until there are 4
+    //   per compute unit below 48 MiB, 16 below 100, 64 above.  (Eight passes in flight and 4 workgroups:
+    //   8 units of 8192 tokens, 64 channels 8.2 against 5.9; 32 of 32K, 24 channels 71 against 57, of which 66 with
+    //   one pass but 4 workgroups; one unit of 128K, 24 channels 8.5 with 4 workgroups, 11.6 with 64.)
+    // - From 200 MiB on and below 64 channels, eight passes in flight with the streaming mark (256 units
+    //   of 8192, 24 channels 116 against 138; 32 of 32K, 8 channels 46 against 48, written just before 137
+    //   against 156).  Below that the mark loses where the memory-side cache (256 MiB) holds K: 256 units of
+    //   2500 tokens, 16 channels, built again 35 against 26; at 256 MiB still 45 against 42.
+    const int64_t units = (int64_t)s.B * s.Hkv, bytes = units * n * kv_stride * 2, mib = 1 << 20;
+    const bool stream = bytes >= 200 * mib && s.r < 64;
+    const int64_t want = (bytes < 48 * mib ? 4ll : bytes < 100 * mib ? 16ll : 64ll) * device_caps().cus;
+    const int round = (stream ? 8 : 1) * pl.P;
     int per_wg = round * std::max(1, 256 / round);
-    const int64_t units = (int64_t)s.B * s.Hkv, want = 4ll * device_caps().cus;
-    while (per_wg > kWG / s.r && units * ((n + per_wg - 1) / per_wg) < want) per_wg = (per_wg + 1) / 2;
-    const dim3 grid((n + per_wg - 1) / per_wg, s.B * s.Hkv);
+    while (per_wg > pl.P && units * ((n + per_wg - 1) / per_wg) < want) per_wg = (per_wg + 1) / 2;
+    // (equal shares: 300 tokens in pieces of 256 would be one long and one short)
+    const int n_wg = (n + per_wg - 1) / per_wg;
+    per_wg = (n + n_wg - 1) / n_wg;
+    const dim3 grid((n + per_wg - 1) / per_wg, s.Hkv, s.B);
     const auto *Kh = static_cast<const uint16_t *>(K);
     auto *lh = static_cast<uint16_t *>(label);
-    // Rows that the memory-side cache (256 MiB) can hold may be there from the prefill and are not
-    // marked as streaming: 256 units of 2500 tokens (164 MB) 28.7 us with the mark.
-    if (units * n * kv_stride * 2 > (256ll << 20))
-        DS_LAUNCH(KID_LABEL, k_label<true>, grid, dim3(kWG), 0, st, Kh, channels, lh, s.Hkv, s.L_max, s.r, t0, n, kv_stride, per_wg);
+    if (stream)
+        DS_LAUNCH(KID_LABEL, (k_label<8, true>), grid, dim3(kWG), 0, st, Kh, channels, lh, s.L_max, pl, t0, n, kv_stride, per_wg);
     else
-        DS_LAUNCH(KID_LABEL, k_label<false>, grid, dim3(kWG), 0, st, Kh, channels, lh, s.Hkv, s.L_max, s.r, t0, n, kv_stride, per_wg);
+        DS_LAUNCH(KID_LABEL, (k_label<1, false>), grid, dim3(kWG), 0, st, Kh, channels, lh, s.L_max, pl, t0, n, kv_stride, per_wg);
     return hipGetLastError();
 }
 

@@ -50,6 +50,32 @@ def test_q4_build_tiles(B, Hkv, L, L_max, r, spin):
     assert (codes[:, :, L:] == -1).all()
 
 
+@pytest.mark.parametrize("B,Hkv,L,L_max,r,kv", [
+    (1, 1, 1, 1, 1, False),          # one token, one channel
+    (1, 1, 2, 5, 128, False),        # one pass of two rows
+    (2, 3, 300, 301, 24, False),     # equal shares, idle threads in a pass
+    (1, 2, 33, 33, 100, True),       # interleaved rows, a remainder in the last pass
+    (3, 40, 1700, 1700, 8, False),   # 50 MiB: more workgroups per compute unit ...
+    (4, 32, 3300, 3301, 16, False),  # ... 103 MiB: and more
+    (8, 16, 6400, 6400, 24, False),  # the first size with the streaming mark and eight passes in flight (200 MiB)
+    (4, 16, 6401, 6401, 7, True),    # ... of interleaved rows, idle threads and a remainder
+    (8, 16, 6400, 6400, 64, False),  # 64 channels: one pass at a time at every size
+])
+def test_label_build_sizes(B, Hkv, L, L_max, r, kv):
+    """Bit copies on both sides of the rules that choose the rows of a workgroup and the streaming mark."""
+    g = torch.Generator(device="cuda").manual_seed(L + r)
+    rows = 2 if kv else 1
+    K = torch.randint(-32768, 32768, (B, Hkv, L_max, rows, 128), dtype=torch.int16, device="cuda", generator=g)
+    ch = to_dev(rand_channels(Hkv, r, seed=L + r))
+    label = torch.full((B, Hkv, L_max, r), 0x7e01, dtype=torch.int16, device="cuda")
+    shp = ds.shape(B, Hkv, Hkv, 128, L, L_max, r, 1)
+    (ds.ds_build_label_kv if kv else ds.ds_build_label)(K, ch, label, shp)
+    torch.cuda.synchronize()
+    want = torch.gather(K[:, :, :L, 0], 3, ch.long()[None, :, None, :].expand(B, Hkv, L, r))
+    assert torch.equal(label[:, :, :L], want)
+    assert (label[:, :, L:] == 0x7e01).all()
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,L,L_max", [
     (1, 1, 1, 1, 1),
     (1, 1, 1, 33, 40),           # one row more than the smallest chunk of a device full of chunks
