@@ -334,7 +334,7 @@ bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p, size_t wor
 static const char *const kKernelNames[KID_COUNT] = {
     "k_init", "k_score", "k_cand", "k_attend", "k_compact", "k_dense",
     "k_attend_rows", "k_label", "k_gather_host", "k_probe",
-    "k_refine_attend", "k_append_kv", "k_q4_build", "k_q4_write", "k_predict_query"};
+    "k_refine_attend", "k_append_kv", "k_q4_build", "k_q4_write", "k_predict_query", "k_q4_amax", "k_q4_code"};
 
 struct ProfRec { int id; hipEvent_t a, b; };
 static std::mutex g_prof_mu;

@@ -56,6 +56,8 @@ enum KernelId {
     KID_Q4_BUILD,
     KID_Q4_WRITE,
     KID_PREDICT,
+    KID_Q4_AMAX,
+    KID_Q4_CODE,
     KID_COUNT
 };
 
@@ -78,6 +80,18 @@ struct DensePlan {
     int ch, n_ch;
     size_t off_ctl, off_part, total;  // same control prefix as Plan
 };
+
+// Plan of ds_build_label_q4.  One launch with a workgroup per unit; two, of which the second
+// (k_q4_build) reads the K rows once and its workgroups wait for the others of their unit; or three
+// (k_q4_amax, k_q4_code) that read them twice and wait for nobody.
+struct Q4Plan {
+    int launches;
+    int tile, n_wg;      // tokens per workgroup / workgroups per unit of the launch that writes the codes
+    int per_wg, n_max;   // the same of k_q4_amax
+};
+constexpr size_t kQ4TileLds = 60 << 10;   // LDS of the largest tile: no more than a launch gets without asking
+constexpr size_t kQ4StaticLds = 1280;     // k_q4_build's other LDS, rounded up
+void make_q4_plan(const ds_shape_t &s, Q4Plan *p);
 
 // Where the approximate scores come from: the fp16 label cache, the K rows themselves (no label
 // cache), or the 4-bit label cache (packed codes + per-channel amax).

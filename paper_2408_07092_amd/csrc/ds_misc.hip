@@ -1,6 +1,7 @@
 // Label-cache maintenance (Sec. 4.2), the host-row gather of the offload
 // arrangement (Sec. 5.1) and the read-bandwidth probe.
 #include <algorithm>
+#include <cmath>
 
 #include "ds_device.h"
 
@@ -113,7 +114,63 @@ __device__ __forceinline__ uint32_t q4_code(float x, float inv)
 }
 __device__ __forceinline__ float q4_inverse(float amax) { return amax > 0.0f ? 7.0f / amax : 0.0f; }
 
-// Before k_q4_build: amax and every unit's counter word (its first word of codes) to zero.
+__device__ __forceinline__ float q4_f16(uint16_t v) { return (float)__builtin_bit_cast(_Float16, v); }
+
+// Largest magnitude of the thread's channel over its share of the rows [lo, hi), values to `keep`; eight
+// passes of a thread in flight.
+template <class Keep>
+__device__ __forceinline__ uint32_t q4_pick(const uint16_t *Kc, const PickLanes &p, int lo, int hi, Keep keep)
+{
+    constexpr int kPick = 8;
+    uint32_t mx = 0u;
+    if (p.on)
+        for (int i = lo + p.i0; i < hi; i += kPick * p.P) {
+            uint16_t x[kPick];
+#pragma unroll
+            for (int e = 0; e < kPick; ++e)
+                x[e] = __builtin_nontemporal_load(Kc + (size_t)min(i + e * p.P, hi - 1) * kD);
+#pragma unroll
+            for (int e = 0; e < kPick; ++e) {
+                mx = max(mx, (uint32_t)(x[e] & 0x7fffu));
+                if (i + e * p.P < hi) keep(i + e * p.P, x[e]);
+            }
+        }
+    return __float_as_uint(q4_f16((uint16_t)mx));
+}
+
+// Folds every thread's maximum into its channel's of mx_sh (after a barrier).  Powers of two: lanes a
+// multiple of r apart hold the same channel, and a wavefront's are folded in registers first (one
+// channel: 256 adds to one LDS word otherwise).
+__device__ __forceinline__ void q4_fold_max(uint32_t mine, const PickLanes &p, int r, uint32_t *mx_sh)
+{
+    bool add = p.on;
+    if (r <= 32 && (r & (r - 1)) == 0) {
+        for (int d = 32; d >= r; d >>= 1) mine = max(mine, (uint32_t)__shfl_xor((int)mine, d));
+        add = (threadIdx.x & 63) < (uint32_t)r;
+    }
+    if (add) atomicMax(&mx_sh[p.j], mine);
+}
+
+// Codes of the n tokens whose picked values are in tile_sh ([n][8 W]), words to cu[n][W]; a thread keeps
+// its word of a token.  skip_first: token 0's first word is left alone.
+__device__ __forceinline__ void q4_code_tile(const uint16_t *tile_sh, const float *inv_sh, int r, const PickLayout &words,
+                                             int n, bool skip_first, uint32_t *cu)
+{
+    const PickLanes q(words);
+    const int W = words.r;
+    if (!q.on) return;
+    for (int i = q.i0; i < n; i += q.P) {
+        const half8 v = *reinterpret_cast<const half8 *>(tile_sh + (i * W + q.j) * 8);
+        uint32_t word = 0u;
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (q.j * 8 + k < r) word |= q4_code((float)v[k], inv_sh[q.j * 8 + k]) << (4 * k);
+        if (i + q.j || !skip_first) cu[(size_t)i * W + q.j] = word;
+    }
+}
+
+// Before k_q4_build and k_q4_amax: amax, and for k_q4_build every unit's counter word (its first word of
+// codes), to zero.
 __global__ __launch_bounds__(kWG) void k_q4_zero(uint32_t *amax, size_t n, uint32_t *codes, size_t unit_words,
                                                  int units)
 {
@@ -122,59 +179,49 @@ __global__ __launch_bounds__(kWG) void k_q4_zero(uint32_t *amax, size_t n, uint3
     for (size_t i = i0; i < (size_t)units; i += step) codes[i * unit_words] = 0u;
 }
 
-constexpr int kPick = 8;  // passes of a thread in flight
-
 // Builds the 4-bit label cache with one read of the K rows, which bounds it (64 units of 16K tokens,
-// 16 channels: 268 MB in 54 us; a pass for the maxima and a pass for the codes, each reading the
-// rows with a division per element: 60 + 226 us).  A workgroup picks the label values of
-// its tile of tokens into LDS, adds its channel maxima to the unit's (amax), arrives at the unit's
+// 16 channels: 268 MB in 53 us, with two reads of it 87).  A workgroup picks the label values of its tile of
+// tokens into LDS, adds its channel maxima to the unit's (amax), arrives at the unit's
 // counter and waits for the unit's other workgroups; with the unit's maxima complete it codes the
 // tile out of LDS.  The counter (arrivals in the low half, departures in the high half) is the
-// unit's first word of codes: token 0 is coded by the last workgroup to depart, when nobody looks
-// at the counter any more.
-// The wait: a unit's workgroups are neighbours in the grid and start in grid order, so those that a
-// workgroup waits for are running or next in line.  It is bounded all the same, and a workgroup
+// unit's first word of codes: it is coded by the last workgroup to depart, when nobody looks
+// at the counter any more.  A unit with one workgroup needs none of this: no k_q4_zero, no atomics.
+// The wait: make_q4_plan lets workgroups wait only where the device holds a unit's several times over; a
+// unit's workgroups are neighbours in the grid and start in grid order, so those that a workgroup
+// waits for are running or next in line.  It is bounded all the same, and a workgroup
 // whose wait runs out reads the unit's K rows itself for the maxima: slower, the same result.
-__global__ __launch_bounds__(kWG) void k_q4_build(const uint16_t *__restrict__ K,
-                                                  const int32_t *__restrict__ channels, uint32_t *amax_bits,
-                                                  uint32_t *codes, int Hkv, int L_max, int r, int L, int tile,
-                                                  uint32_t spin_limit)
+// (Eight workgroups to a compute unit by registers, so that LDS alone decides how many it holds.)
+__global__ __launch_bounds__(kWG, 8) void k_q4_build(const uint16_t *__restrict__ K,
+                                                     const int32_t *__restrict__ channels, uint32_t *amax_bits,
+                                                     uint32_t *codes, int L_max, PickLayout pl, PickLayout words,
+                                                     int L, int tile, uint32_t spin_limit)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t tile_sh[];  // [tile][8 W] picked values
     __shared__ uint32_t mx_sh[kD];
     __shared__ float inv_sh[kD];
     __shared__ uint32_t s_ok, s_last;
-    const int tid = threadIdx.x, u = blockIdx.y, h = u % Hkv;
-    const int W = (r + 7) / 8, stride = 8 * W;
-    const PickLanes p(PickLayout{r, kWG / r, (65535u + (uint32_t)r) / (uint32_t)r});
+    const int tid = threadIdx.x, h = blockIdx.y, u = blockIdx.z * gridDim.y + h, r = pl.r;
+    const int W = words.r, stride = 8 * W;
+    const PickLanes p(pl);
     const int c = p.on ? channels[h * r + p.j] : 0;
     if (tid < kD) mx_sh[tid] = 0u;
     const uint16_t *Ku = K + (size_t)u * L_max * kD + c;
-    auto f16 = [](uint16_t v) { return (float)__builtin_bit_cast(_Float16, v); };
-    // largest magnitude of the thread's channel over its share of the rows [lo, hi), values to `keep`
-    auto pick = [&](int lo, int hi, auto keep) {
-        uint32_t mx = 0u;
-        if (p.on)
-            for (int i = lo + p.i0; i < hi; i += kPick * p.P) {
-                uint16_t x[kPick];
-#pragma unroll
-                for (int e = 0; e < kPick; ++e)
-                    x[e] = __builtin_nontemporal_load(Ku + (size_t)min(i + e * p.P, hi - 1) * kD);
-#pragma unroll
-                for (int e = 0; e < kPick; ++e) {
-                    mx = max(mx, (uint32_t)(x[e] & 0x7fffu));
-                    if (i + e * p.P < hi) keep(i + e * p.P, x[e]);
-                }
-            }
-        return __float_as_uint(f16((uint16_t)mx));
-    };
     const int t0 = blockIdx.x * tile, t1 = min(L, t0 + tile);
-    const uint32_t mine = pick(t0, t1, [&](int t, uint16_t x) { tile_sh[(t - t0) * stride + p.j] = x; });
+    const uint32_t mine = q4_pick(Ku, p, t0, t1, [&](int t, uint16_t x) { tile_sh[(t - t0) * stride + p.j] = x; });
     __syncthreads();
-    if (p.on) atomicMax(&mx_sh[p.j], mine);
+    q4_fold_max(mine, p, r, mx_sh);
     __syncthreads();
     uint32_t *am = amax_bits + (size_t)u * r;
     uint32_t *cu = codes + (size_t)u * L_max * W;
+    if (gridDim.x == 1) {
+        if (tid < r) {
+            am[tid] = mx_sh[tid];
+            inv_sh[tid] = q4_inverse(__uint_as_float(mx_sh[tid]));
+        }
+        __syncthreads();
+        q4_code_tile(tile_sh, inv_sh, r, words, t1, false, cu);
+        return;
+    }
     if (tid < r && mx_sh[tid]) atomicMax(&am[tid], mx_sh[tid]);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -191,29 +238,56 @@ __global__ __launch_bounds__(kWG) void k_q4_build(const uint16_t *__restrict__ K
     }
     __syncthreads();
     if (!s_ok) {
-        const uint32_t all = pick(0, L, [](int, uint16_t) {});
-        if (p.on) atomicMax(&mx_sh[p.j], all);
+        const uint32_t all = q4_pick(Ku, p, 0, L, [](int, uint16_t) {});
+        q4_fold_max(all, p, r, mx_sh);
         __syncthreads();
         if (tid < r) inv_sh[tid] = q4_inverse(__uint_as_float(mx_sh[tid]));
     } else if (tid < r) {
         inv_sh[tid] = q4_inverse(__uint_as_float(ld_dev(am + tid)));
     }
     __syncthreads();
-    for (int e = tid; e < (t1 - t0) * W; e += kWG) {
-        const int i = e / W, w = e - i * W;
-        const half8 v = *reinterpret_cast<const half8 *>(tile_sh + i * stride + w * 8);
+    q4_code_tile(tile_sh, inv_sh, r, words, t1 - t0, t0 == 0, cu + (size_t)t0 * W);
+    if (s_last && tid == 0) {
         uint32_t word = 0u;
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (w * 8 + k < r) word |= q4_code((float)v[k], inv_sh[w * 8 + k]) << (4 * k);
-        if (t0 + i) cu[(size_t)(t0 + i) * W + w] = word;
+        for (int k = 0; k < 8 && k < r; ++k)
+            word |= q4_code(q4_f16(Ku[channels[h * r + k] - c]), inv_sh[k]) << (4 * k);
+        cu[0] = word;
     }
-    if (s_last && tid < W) {
-        uint32_t word = 0u;
-        for (int k = 0; k < 8 && tid * 8 + k < r; ++k)
-            word |= q4_code(f16(Ku[channels[h * r + tid * 8 + k] - c]), inv_sh[tid * 8 + k]) << (4 * k);
-        cu[tid] = word;
-    }
+}
+
+// The same with two reads of the K rows and nobody waiting: the channel maxima ...
+__global__ __launch_bounds__(kWG) void k_q4_amax(const uint16_t *__restrict__ K, const int32_t *__restrict__ channels,
+                                                 uint32_t *amax_bits, int L_max, PickLayout pl, int L, int per_wg)
+{
+    __shared__ uint32_t mx_sh[kD];
+    const int tid = threadIdx.x, h = blockIdx.y, u = blockIdx.z * gridDim.y + h, r = pl.r;
+    const PickLanes p(pl);
+    const int c = p.on ? channels[h * r + p.j] : 0;
+    if (tid < kD) mx_sh[tid] = 0u;
+    const int lo = blockIdx.x * per_wg;
+    const uint32_t mine = q4_pick(K + (size_t)u * L_max * kD + c, p, lo, min(L, lo + per_wg), [](int, uint16_t) {});
+    __syncthreads();
+    q4_fold_max(mine, p, r, mx_sh);
+    __syncthreads();
+    if (tid < r && mx_sh[tid]) atomicMax(&amax_bits[(size_t)u * r + tid], mx_sh[tid]);
+}
+
+// ... and the codes.
+__global__ __launch_bounds__(kWG) void k_q4_code(const uint16_t *__restrict__ K, const int32_t *__restrict__ channels,
+                                                 const float *__restrict__ amax, uint32_t *__restrict__ codes, int L_max,
+                                                 PickLayout pl, PickLayout words, int L, int tile)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t tile_sh[];  // [tile][8 W] picked values
+    __shared__ float inv_sh[kD];
+    const int tid = threadIdx.x, h = blockIdx.y, u = blockIdx.z * gridDim.y + h, r = pl.r;
+    const int W = words.r, stride = 8 * W;
+    const PickLanes p(pl);
+    const int c = p.on ? channels[h * r + p.j] : 0;
+    if (tid < r) inv_sh[tid] = q4_inverse(amax[(size_t)u * r + tid]);
+    const int t0 = blockIdx.x * tile, t1 = min(L, t0 + tile);
+    q4_pick(K + (size_t)u * L_max * kD + c, p, t0, t1, [&](int t, uint16_t x) { tile_sh[(t - t0) * stride + p.j] = x; });
+    __syncthreads();
+    q4_code_tile(tile_sh, inv_sh, r, words, t1 - t0, false, codes + ((size_t)u * L_max + t0) * W);
 }
 
 // One thread per (token, word): up to eight codes packed into the word.
@@ -406,28 +480,78 @@ hipError_t launch_label(const void *K, const int32_t *channels, void *label, con
     return hipGetLastError();
 }
 
+void make_q4_plan(const ds_shape_t &s, Q4Plan *p)
+{
+    const DeviceCaps caps = device_caps();
+    const int64_t units = (int64_t)s.B * s.Hkv, tokens = units * s.L;
+    const int W = (s.r + 7) / 8, P = std::min(kWG / s.r, 32);  // rows of a pass (few channels: as far as it matters)
+    const size_t token_lds = 16 * (size_t)W;
+    const int most = (int)(kQ4TileLds / token_lds);            // tokens of the largest tile
+    // One workgroup per unit: up to four rounds of eight passes, where one read of the rows by one
+    // workgroup is over before several have met (us, 32 units: 300 tokens of 8 channels 8.9 -> 5.5, of 16 9.0 -> 6.4;
+    // 1024 tokens of 8 channels 9.4 against 9.3; 500 of 24, six rounds, 1.27 times as long); all that fit the LDS when the
+    // units fill the device (256 units of 2500 tokens, 8 channels 34.0 -> 31.9).
+    if (s.L <= most && (s.L <= 32 * P || units >= caps.cus)) {
+        *p = {1, s.L, 1, 0, 0};
+        return;
+    }
+    // A workgroup's tile: its rounds of loads cost about 1.2 us each, its atomics on the unit's words 0.15 us
+    // one after the other, and the sum is least at the root of tokens times rows of a pass -- half of that
+    // on an idle device, more where other units' workgroups hide the rounds.  (0.5 / 1 / 2 / 4 times
+    // as many tokens: 1.01 / 1.05 / 1.2 / 1.5 times the best below 50K tokens in all; 512 units of 500 to
+    // 2500 tokens, 16 channels and more 1.7 / 1.15 / 1.0 / 1.1.)
+    const double root = std::sqrt((double)s.L * P);
+    const double share = tokens < 49152 ? 0.5 : units * 2 >= caps.cus ? 1.5 : 1.0;
+    const int tile = std::min(most, std::max(4 * P, (int)(share * root)));
+    const int n = (s.L + tile - 1) / tile;
+    // One read and a wait for the unit's other workgroups, or two reads without.  The read that is saved
+    // has to be worth the second counter and the atomics that queue on a unit's words (two reads
+    // against one: 8 units of 8192 tokens 8 channels 11.9 against 11.6, 16 channels 11.9 against 12.8; 32 of
+    // 8192 with 16 channels 26 against 20; with 128 channels, 64 workgroups of 128 atomics each, 46 against
+    // 60; one unit of 32K, 8 channels 13 against 15).  And a device has to hold a unit's workgroups four times over, in each
+    // of its dies: with that, calls on several streams at once, each with one unit partly started, all get on.
+    const int held = (int)std::min<size_t>(8, (size_t)caps.lds_per_cu / (tile * token_lds + kQ4StaticLds));
+    const int dies = std::max(1, caps.xccs);
+    const bool fits = 4 * ((n + dies - 1) / dies) <= held * std::max(1, caps.cus / dies);
+    if (units >= 4 && tokens >= (W == 1 ? 8192 : 49152) && n <= 128 && n * W <= 400 && fits) {
+        const int even = (s.L + n - 1) / n;
+        *p = {2, even, (s.L + even - 1) / even, 0, 0};
+        return;
+    }
+    // Two reads.  The maxima by shares of half the root (no counter and no wait: atomics cost less; an
+    // eighth / a quarter / half / once / twice: one unit of 32K tokens, 8 channels 12.0 / 10.7 / 11.1 / 13.4 / 17.6 us); the codes by a round of
+    // eight passes, or four with 64 channels and more (512 units of 2500, 128 channels 1.16 times as long by one).
+    const int per = std::min(s.L, std::max(4 * P, (int)(root / 2)));
+    const int n_max = (s.L + per - 1) / per;
+    int code = std::min(most, s.r >= 64 && tokens >= 60000 ? 32 * P : 8 * P);
+    while ((s.L + code - 1) / code > (1 << 23) && code * 2 <= most) code *= 2;  // (grid limit: 2^32 threads)
+    code = std::min(code, s.L);
+    *p = {3, code, (s.L + code - 1) / code, per, n_max};
+}
+
 hipError_t launch_q4_build(const void *K, const int32_t *channels, float *amax, void *codes,
                            const ds_shape_t &s, hipStream_t st)
 {
-    const int units = s.B * s.Hkv, W = (s.r + 7) / 8;
-    const size_t n_amax = (size_t)units * s.r;
-    hipLaunchKernelGGL(k_q4_zero, dim3((unsigned)std::min<size_t>((n_amax + kWG - 1) / kWG, 1024)), dim3(kWG), 0, st,
-                       reinterpret_cast<uint32_t *>(amax), n_amax, static_cast<uint32_t *>(codes),
-                       (size_t)s.L_max * W, units);
-    // Tiles of 16 KiB (1024 tokens of up to 8 channels): eight workgroups per compute unit, as many
-    // as its wavefronts allow.  Calls of few tokens take smaller tiles, down to 64 tokens, until
-    // there are four workgroups for every compute unit or 32 for a unit: the atomics of a unit's
-    // workgroups queue at its maxima and its counter, about 0.17 us each (64 units of 16K tokens,
-    // 16 channels: 32 workgroups per unit 54 us, 64: 72, 128: 145).  A unit has at most 65535 (its
-    // counter).
-    int tile = std::max(64, 1024 / W);
-    const int64_t want = 4ll * device_caps().cus;
-    while (tile > 64 && (int64_t)units * ((s.L + tile - 1) / tile) < want && (s.L + tile - 1) / tile <= 16) tile /= 2;
-    while ((s.L + tile - 1) / tile > 65535) tile *= 2;
-    DS_LAUNCH(KID_Q4_BUILD, k_q4_build, dim3((s.L + tile - 1) / tile, units), dim3(kWG), (size_t)tile * 16 * W, st,
-              static_cast<const uint16_t *>(K), channels, reinterpret_cast<uint32_t *>(amax),
-              static_cast<uint32_t *>(codes), s.Hkv, s.L_max, s.r, s.L, tile,
-              tune_get(5) ? (uint32_t)tune_get(5) : 1u << 14);
+    const int W = (s.r + 7) / 8;
+    const size_t n_amax = (size_t)s.B * s.Hkv * s.r;
+    const PickLayout pl = pick_layout(s.r), words = pick_layout(W);
+    const auto *Kh = static_cast<const uint16_t *>(K);
+    auto *am = reinterpret_cast<uint32_t *>(amax), *cw = static_cast<uint32_t *>(codes);
+    Q4Plan p;
+    make_q4_plan(s, &p);
+    const size_t lds = (size_t)p.tile * 16 * W;
+    if (p.launches > 1)
+        hipLaunchKernelGGL(k_q4_zero, dim3((unsigned)std::min<size_t>((n_amax + kWG - 1) / kWG, 1024)), dim3(kWG), 0, st,
+                           am, n_amax, cw, (size_t)s.L_max * W, p.launches == 2 ? s.B * s.Hkv : 0);
+    if (p.launches < 3) {
+        DS_LAUNCH(KID_Q4_BUILD, k_q4_build, dim3(p.n_wg, s.Hkv, s.B), dim3(kWG), lds, st, Kh, channels, am, cw,
+                  s.L_max, pl, words, s.L, p.tile, tune_get(5) ? (uint32_t)tune_get(5) : 1u << 14);
+    } else {
+        DS_LAUNCH(KID_Q4_AMAX, k_q4_amax, dim3(p.n_max, s.Hkv, s.B), dim3(kWG), 0, st, Kh, channels, am, s.L_max, pl,
+                  s.L, p.per_wg);
+        DS_LAUNCH(KID_Q4_CODE, k_q4_code, dim3(p.n_wg, s.Hkv, s.B), dim3(kWG), lds, st, Kh, channels,
+                  static_cast<const float *>(amax), cw, s.L_max, pl, words, s.L, p.tile);
+    }
     return hipGetLastError();
 }
 

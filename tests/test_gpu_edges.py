@@ -9,6 +9,7 @@ import torch
 import paper_2408_07092_amd as ds
 from oracle import ds_oracle as O
 from tests.parity_util import Case, check_output, full_parity, to_dev
+from tests.test_plans_host import q4_plan
 from workloads import Workload, make_layer_numpy
 
 pytestmark = pytest.mark.gpu
@@ -19,35 +20,93 @@ def rand_channels(Hkv, r, seed):
     return np.stack([np.sort(rng.permutation(128)[:r]) for _ in range(Hkv)]).astype(np.int32)
 
 
-@pytest.mark.parametrize("B,Hkv,L,L_max,r,spin", [
-    (1, 1, 1, 1, 1, 0),            # one token
-    (2, 3, 64, 64, 8, 0),          # one whole tile
-    (1, 2, 65, 70, 3, 0),          # one token into the second tile
-    (1, 2, 1025, 1028, 16, 0),     # ... of a unit with many tiles
-    (1, 1, 40001, 40001, 8, 0),    # more tiles than a small unit gets otherwise
-    (1, 2, 700, 700, 128, 0),      # every channel, two rows per pass
-    (1, 2, 3000, 3000, 100, 0),    # idle threads in a pass
-    (2, 2, 5000, 5000, 12, 1),     # waits that run out: a workgroup finds the maxima by itself
+def launches_of(fn):
+    """{kernel: launches} of the library's kernels that `fn` enqueues."""
+    ds.ds_profile_reset()
+    ds.ds_profile_enable(True)
+    try:
+        fn()
+        torch.cuda.synchronize()
+        return {name: n for name, (_, n) in ds.ds_profile_read().items()}
+    finally:
+        ds.ds_profile_enable(False)
+        ds.ds_profile_reset()
+
+
+ALONE, WAITS, TWO_READS = ["k_q4_build"], ["k_q4_build", "waits"], ["k_q4_amax", "k_q4_code"]
+
+
+@pytest.mark.parametrize("B,Hkv,L,L_max,r,spin,plan", [
+    (1, 1, 1, 1, 1, 0, ALONE),               # one token
+    (2, 3, 64, 64, 8, 0, ALONE),
+    (1, 2, 65, 70, 3, 0, ALONE),
+    (1, 3, 64, 64, 128, 0, ALONE),           # the longest unit that one workgroup takes: every channel ...
+    (1, 3, 65, 66, 128, 0, TWO_READS),       # ... and one token more
+    (1, 2, 1024, 1024, 8, 0, ALONE),         # ... of 8 channels ...
+    (1, 2, 1025, 1028, 8, 0, TWO_READS),
+    (1, 2, 1025, 1028, 16, 0, TWO_READS),
+    (8, 32, 1290, 1290, 20, 0, WAITS),       # units that fill the device, one tile too long for one workgroup
+    (8, 32, 1280, 1281, 20, 0, ALONE),       # ... and just not (60 KiB of LDS)
+    (1, 1, 40001, 40001, 8, 0, TWO_READS),   # few units wait for nobody
+    (1, 2, 700, 700, 128, 0, TWO_READS),
+    (1, 2, 3000, 3000, 100, 0, TWO_READS),   # idle threads in a pass
+    (4, 1, 2047, 2047, 8, 0, TWO_READS),     # the least work for a wait ...
+    (4, 1, 2048, 2050, 8, 0, WAITS),
+    (4, 3, 4100, 4100, 12, 0, WAITS),        # ... of two words a token, idle threads
+    (2, 12, 2049, 2049, 100, 0, TWO_READS),  # 64 channels and more: four rounds to a tile
+    (5, 10, 1250, 1251, 128, 0, WAITS),      # 16 words a token, workgroups of 50 tokens
+    (1, 32, 6250, 6250, 64, 0, WAITS),
+    (4, 1, 270000, 270000, 8, 0, WAITS),     # a hundred workgroups per unit
+    (4, 1, 530000, 530000, 8, 0, TWO_READS), # more than 128 would have to wait
+    (2, 4, 9000, 9000, 12, 1, WAITS),        # waits that run out: a workgroup finds the maxima by itself
+    (1, 8, 2500, 2500, 8, 1, WAITS),
 ])
-def test_q4_build_tiles(B, Hkv, L, L_max, r, spin):
-    """Codes and maxima bit-equal to the oracle's at the edges of the tiles, and when a workgroup
-    stops waiting for the others of its unit."""
+def test_q4_build_tiles(B, Hkv, L, L_max, r, spin, plan):
+    """Codes and maxima bit-equal to the oracle's on both sides of the rules that choose between one
+    workgroup per unit, workgroups that wait and two reads, and when a workgroup stops waiting for the
+    others of its unit."""
     w = Workload("t", B, Hkv, Hkv, 128, L, r, 1, 1)
     t = make_layer_numpy(w, L_max=L_max)
     ch = rand_channels(Hkv, r, seed=L + r)
     W = (r + 7) // 8
     codes = torch.full((B, Hkv, L_max, W), -1, dtype=torch.int32, device="cuda")
     amax = torch.full((B, Hkv, r), -1.0, dtype=torch.float32, device="cuda")
+    shp = ds.shape(B, Hkv, Hkv, 128, L, L_max, r, 1)
+    K, chd = to_dev(t["K"]), to_dev(ch)
     ds.ds_tune_set(5, spin)
     try:
-        ds.ds_build_label_q4(to_dev(t["K"]), to_dev(ch), codes, amax, ds.shape(B, Hkv, Hkv, 128, L, L_max, r, 1))
-        torch.cuda.synchronize()
+        ran = launches_of(lambda: ds.ds_build_label_q4(K, chd, codes, amax, shp))
     finally:
         ds.ds_tune_set(5, 0)
+    assert sorted(ran) == [k for k in plan if k.startswith("k_")]
+    assert (q4_plan(B * Hkv, L, r).n_wg > 1) == (plan is not ALONE)
     want_codes, want_amax = O.build_label_q4(t["K"], ch, L)
     assert np.array_equal(amax.cpu().numpy(), want_amax)
     assert np.array_equal(codes.cpu().numpy()[:, :, :L].view(np.uint32), want_codes[:, :, :L])
     assert (codes[:, :, L:] == -1).all()
+
+
+def test_q4_build_on_a_device_that_holds_few_workgroups():
+    """Told of a device of 8 compute units, the build has no workgroup wait for more than the device
+    holds four times over; the codes are the same."""
+    B, Hkv, L, r = 2, 4, 20000, 16
+    w = Workload("t", B, Hkv, Hkv, 128, L, r, 1, 1)
+    t = make_layer_numpy(w)
+    ch = rand_channels(Hkv, r, seed=1)
+    K, chd = to_dev(t["K"]), to_dev(ch)
+    codes = torch.empty((B, Hkv, L, 2), dtype=torch.int32, device="cuda")
+    amax = torch.empty((B, Hkv, r), dtype=torch.float32, device="cuda")
+    build = lambda: ds.ds_build_label_q4(K, chd, codes, amax, ds.shape(B, Hkv, Hkv, 128, L, L, r, 1))
+    assert list(launches_of(build)) == ["k_q4_build"]
+    ds.ds_pretend_device(8, 8, 160 << 10)
+    try:
+        codes.fill_(-1)
+        assert sorted(launches_of(build)) == TWO_READS
+    finally:
+        ds.ds_pretend_device(0, 0, 0)
+    want_codes, want_amax = O.build_label_q4(t["K"], ch, L)
+    assert np.array_equal(amax.cpu().numpy(), want_amax)
+    assert np.array_equal(codes.cpu().numpy().view(np.uint32), want_codes)
 
 
 @pytest.mark.parametrize("B,Hkv,L,L_max,r,kv", [

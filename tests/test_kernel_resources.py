@@ -61,3 +61,10 @@ def test_no_kernel_uses_scratch_memory(kernels):
     spilled = {n: (k[".private_segment_fixed_size"], k[".vgpr_spill_count"]) for n, k in kernels.items()
                if k[".private_segment_fixed_size"] or k[".vgpr_spill_count"]}
     assert not spilled
+
+
+def test_q4_build_is_limited_by_its_tile_alone(kernels):
+    """What make_q4_plan counts on: eight workgroups to a compute unit by registers, and no more static
+    LDS than it allows for."""
+    k = kernels["k_q4_build"]
+    assert k[".vgpr_count"] + k.get(".agpr_count", 0) <= 64 and k[".group_segment_fixed_size"] <= 1280

@@ -1,5 +1,5 @@
-"""Host only: the plans of dense and gathered-rows attention, made for an MI355X (the device that
-plans are made for where none is visible)."""
+"""Host only: the plans of dense and gathered-rows attention and of the 4-bit label build, made for an
+MI355X (the device that plans are made for where none is visible)."""
 import ctypes
 
 import pytest
@@ -67,3 +67,41 @@ def test_workspace_for_more_tokens_serves_fewer(units, G, k):
             p = dense_plan(units, G, tokens, have)
             assert p.total <= have, (tokens, longer, p.n_ch)
             assert p.off_part + units * G * p.n_ch * 132 * 4 <= p.total
+
+
+class Q4Plan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("launches", "tile", "n_wg", "per_wg", "n_max")]
+
+
+def q4_plan(units, L, r):
+    fn = getattr(ds.lib(), "_ZN2ds12make_q4_planERK10ds_shape_tPNS_6Q4PlanE")
+    fn.restype, fn.argtypes = None, [ctypes.POINTER(ds.binding.DsShape), ctypes.POINTER(Q4Plan)]
+    plan = Q4Plan()
+    fn(ctypes.byref(ds.shape(1, units, units, 128, L, L, r, 1)), ctypes.byref(plan))
+    return plan
+
+
+@pytest.mark.parametrize("cus", [256, 64, 8])
+@pytest.mark.parametrize("r", [1, 5, 8, 16, 24, 40, 64, 100, 128])
+def test_q4_build_waits_only_for_workgroups_that_the_device_holds(cus, r):
+    """Workgroups of the 4-bit label build wait for each other only where each die holds four units'
+    shares at once; a tile fits the LDS that a launch gets without asking for more, up to the longest
+    cache that the card's memory holds (1.1e9 rows of K); and the tiles cover the tokens."""
+    ds.ds_pretend_device(cus, 8, 160 << 10)
+    words = (r + 7) // 8
+    seen = set()
+    for units in (1, 3, 4, 32, 256, 5000):
+        for L in (1, 7, 64, 65, 300, 1024, 1025, 5000, 16384, 65536, 131073, 262144, 1 << 20, 8400000, 1 << 24, 1100000000):
+            p = q4_plan(units, L, r)
+            seen.add(p.launches)
+            lds = p.tile * 16 * words
+            assert lds <= 60 << 10 and (p.n_wg - 1) * p.tile < L <= p.n_wg * p.tile
+            assert p.n_wg * 256 < 1 << 32
+            if p.launches == 1:
+                assert p.n_wg == 1
+            elif p.launches == 2:
+                held = min(8, (160 << 10) // (lds + 1280)) * (cus // 8)
+                assert 1 < p.n_wg <= 128 and 4 * -(-p.n_wg // 8) <= held
+            else:
+                assert p.launches == 3 and (p.n_max - 1) * p.per_wg < L <= p.n_max * p.per_wg
+    assert seen == ({1, 2, 3} if cus > 8 or r >= 64 else seen | {1, 3})
