@@ -324,11 +324,12 @@ __global__ __launch_bounds__(kWG) void k_q4_write(const _Float16 *__restrict__ K
 // split m in 16-byte pieces, products are exact (fp16 x fp16) and accumulated in binary32, the
 // lanes are summed in a fixed butterfly, the result is rounded once to fp16.  Up to four batch
 // rows share a pass over Wq (x sits in LDS); larger batches take several passes.
-// Eight pieces of a row are in flight per lane and the first are asked for before x is staged (a
-// piece of two rows in turn at a time: 14.4 us for 4096 x 4096, now 9.1; 8192 x 8192 42.7, now 24.8).
+// Up to PIECES pieces of a row are in flight per lane and the first are asked for before x is staged (a
+// piece of two rows in turn at a time: 4096 x 4096 11.6 us, now 8.4; 8192 x 8192 42, now 24).  PIECES goes by
+// the row length (launch_predict_query); the order of the sums does not depend on it.
 constexpr int kPredBatch = 4;
-constexpr int kPredPieces = 8;
 
+template <int PIECES, bool ST>
 __global__ __launch_bounds__(kWG) void k_predict_query(const _Float16 *__restrict__ x,
                                                        const _Float16 *__restrict__ Wq,
                                                        _Float16 *__restrict__ q_out, int B, int Dm,
@@ -337,14 +338,16 @@ __global__ __launch_bounds__(kWG) void k_predict_query(const _Float16 *__restric
     extern __shared__ __attribute__((aligned(16))) _Float16 x_sh[];  // [min(B, kPredBatch)][Dm]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_lo = blockIdx.x * rows_per_wg, n_hi = min(N, n_lo + rows_per_wg);
-    half8 wv[kPredPieces];
+    half8 wv[PIECES];
     // (pieces past the end of the row re-read its last one; they are not used)
     auto issue = [&](int n, int m0) {
         const _Float16 *wrow = Wq + (size_t)min(n, N - 1) * Dm;
 #pragma unroll
-        for (int i = 0; i < kPredPieces; ++i)
-            if (m0 - lane * 8 + i * 512 < Dm)
-                wv[i] = __builtin_nontemporal_load(reinterpret_cast<const half8 *>(wrow + min(m0 + i * 512, Dm - 8)));
+        for (int i = 0; i < PIECES; ++i)
+            if (m0 - lane * 8 + i * 512 < Dm) {
+                const half8 *src = reinterpret_cast<const half8 *>(wrow + min(m0 + i * 512, Dm - 8));
+                wv[i] = ST ? __builtin_nontemporal_load(src) : *src;
+            }
     };
     for (int b0 = 0; b0 < B; b0 += kPredBatch) {
         const int nb = min(kPredBatch, B - b0);
@@ -355,10 +358,10 @@ __global__ __launch_bounds__(kWG) void k_predict_query(const _Float16 *__restric
         __syncthreads();
         for (int n = n_lo + wave; n < n_hi; n += 4) {
             float acc[kPredBatch] = {0.0f, 0.0f, 0.0f, 0.0f};
-            for (int m0 = lane * 8; m0 - lane * 8 < Dm; m0 += 512 * kPredPieces) {
-                if (m0 >= 512 * kPredPieces || n != n_lo + wave) issue(n, m0);
+            for (int m0 = lane * 8; m0 - lane * 8 < Dm; m0 += 512 * PIECES) {
+                if (m0 >= 512 * PIECES || n != n_lo + wave) issue(n, m0);
 #pragma unroll
-                for (int i = 0; i < kPredPieces; ++i) {
+                for (int i = 0; i < PIECES; ++i) {
                     const int m = m0 + i * 512;
                     if (m >= Dm) continue;
 #pragma unroll
@@ -577,9 +580,21 @@ hipError_t launch_predict_query(const void *x, const void *Wq, void *q_out, int 
     rows_per_wg = (rows_per_wg + 3) & ~3;
     const int blocks = (N + rows_per_wg - 1) / rows_per_wg;
     const size_t shmem = (size_t)std::min(B, kPredBatch) * Dm * sizeof(_Float16);
-    DS_LAUNCH(KID_PREDICT, k_predict_query, dim3((unsigned)blocks), dim3(kWG), shmem, st,
-              static_cast<const _Float16 *>(x), static_cast<const _Float16 *>(Wq),
-              static_cast<_Float16 *>(q_out), B, Dm, N, rows_per_wg);
+    // Pieces in flight: all of a row of up to 2048 elements, where more code for a row than it has only
+    // costs (512 x 512 2.85 us with one, 3.2 with eight), four up to 4096 (4096 x 4096 8.4, with eight 8.5; batch 8
+    // 16.9 and 18.4), eight beyond (8192 x 8192 24.2 and 25.0).
+    // The streaming mark where Wq is no small part of what the memory-side cache holds and is not read
+    // over and over, once per four rows of a batch (8192 x 8192 24.2 us with it, 26.2 without, batch 8 68.7 and 70.9, batch
+    // 64 493 and 485; 4096 x 4096 8.8 and 8.4, in the cache 6.0 and 5.2, batch 64 112 and 100).
+    const bool mark = B <= 4 * kPredBatch && (size_t)N * Dm * 2 >= (64u << 20);
+    auto go = [&](auto kernel) {
+        DS_LAUNCH(KID_PREDICT, kernel, dim3((unsigned)blocks), dim3(kWG), shmem, st, static_cast<const _Float16 *>(x),
+                  static_cast<const _Float16 *>(Wq), static_cast<_Float16 *>(q_out), B, Dm, N, rows_per_wg);
+    };
+    if (Dm > 4096) mark ? go(k_predict_query<8, true>) : go(k_predict_query<8, false>);
+    else if (Dm > 1024) mark ? go(k_predict_query<4, true>) : go(k_predict_query<4, false>);
+    else if (Dm > 512) mark ? go(k_predict_query<2, true>) : go(k_predict_query<2, false>);
+    else mark ? go(k_predict_query<1, true>) : go(k_predict_query<1, false>);
     return hipGetLastError();
 }
 

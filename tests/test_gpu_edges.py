@@ -183,7 +183,11 @@ def test_dense_decode_in_the_workspace_of_more_tokens(Hq, Hkv, L, L_ws):
     check_output(out.cpu().numpy(), O.dense_decode(t["q"], t["K"], t["V"], L), f"dense {(Hq, Hkv, L, L_ws)}")
 
 
-@pytest.mark.parametrize("B,Dm,N", [(1, 8, 5), (1, 512, 4), (3, 520, 1025), (5, 4096, 65), (1, 4104, 33), (2, 8192, 4100)])
+@pytest.mark.parametrize("B,Dm,N", [(1, 8, 5), (1, 512, 4), (3, 520, 1025), (5, 4096, 65), (1, 4104, 33), (2, 8192, 4100),
+                                    # one past each number of pieces in flight, read once with and without
+                                    # the streaming mark (64 MiB of Wq) and once per four rows of a batch
+                                    (4, 1032, 9), (9, 2056, 40), (4, 512, 65537), (17, 512, 65537), (1, 4096, 8192),
+                                    (6, 4096, 8193), (4, 8192, 4096), (7, 8184, 4100)])
 def test_predict_query_pieces(B, Dm, N):
     """Row lengths at the edges of the pieces in flight and feature counts at the edges of the
     workgroups: one fp16 step plus the binary32 error of Dm products from the float64 oracle."""
