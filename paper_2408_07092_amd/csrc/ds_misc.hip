@@ -397,6 +397,29 @@ __global__ __launch_bounds__(kWG) void k_predict_query(const _Float16 *__restric
 // and 302, with 12 21 and 315 (alone: 20).
 constexpr int kGatherRows = 4;   // rows of a 16-lane slot in flight
 constexpr int kGatherWgs = 24;   // 24 x 16 slots x 4 rows of 512 bytes: 768 KiB
+constexpr int kGatherFew = 512;  // up to this many rows: k_gather_few
+// So few rows that their loads are all in flight anyway: a slot per row, nothing to divide or to loop
+// over (8 units of 64 rows 7.4 us, with the loop 8.1; one of 16 2.7 and 2.9; from 1024 rows on the loop is
+// faster, 12.1 against 13.2).
+__global__ __launch_bounds__(kWG) void k_gather_few(const uint4 *__restrict__ Kh, const uint4 *__restrict__ Vh,
+                                                    const int32_t *__restrict__ idx, uint4 *__restrict__ rows,
+                                                    int L_max, int k)
+{
+    const int u = blockIdx.y;
+    const int i = blockIdx.x * 16 + (threadIdx.x >> 4), p = threadIdx.x & 15;
+    if (i >= k) return;
+    const int tok = idx[(size_t)u * k + i];
+    uint4 kv = make_uint4(0, 0, 0, 0), vv = kv;
+    if (tok >= 0) {
+        const size_t src = ((size_t)u * L_max + tok) * 16 + p;
+        kv = Kh[src];
+        vv = Vh[src];
+    }
+    const size_t dst = ((size_t)u * k + i) * 32 + p;
+    rows[dst] = kv;
+    rows[dst + 16] = vv;
+}
+
 __global__ __launch_bounds__(kWG) void k_gather_host(const uint4 *__restrict__ Kh,
                                                      const uint4 *__restrict__ Vh,
                                                      const int32_t *__restrict__ idx,
@@ -616,6 +639,12 @@ hipError_t launch_gather_host(const void *Kh, const void *Vh, const int32_t *idx
                               const ds_shape_t &s, hipStream_t st)
 {
     const int total = s.B * s.Hkv * s.k;
+    if (total <= kGatherFew) {
+        DS_LAUNCH(KID_GATHER_HOST, k_gather_few, dim3((s.k + 15) / 16, s.B * s.Hkv), dim3(kWG), 0, st,
+                  static_cast<const uint4 *>(Kh), static_cast<const uint4 *>(Vh), idx, static_cast<uint4 *>(rows),
+                  s.L_max, s.k);
+        return hipGetLastError();
+    }
     DS_LAUNCH(KID_GATHER_HOST, k_gather_host, dim3(std::min(kGatherWgs, (total + 15) / 16)), dim3(kWG), 0, st,
                        static_cast<const uint4 *>(Kh), static_cast<const uint4 *>(Vh), idx,
                        static_cast<uint4 *>(rows), s.L_max, s.k, total);

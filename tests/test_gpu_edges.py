@@ -203,7 +203,8 @@ def test_predict_query_pieces(B, Dm, N):
     assert (np.abs(got - ref) <= step + Dm * 2.0 ** -24 * mag).all()
 
 
-@pytest.mark.parametrize("B,Hkv,L,k", [(1, 1, 5, 1), (1, 3, 40, 33), (2, 4, 700, 97), (1, 2, 3000, 1600)])
+@pytest.mark.parametrize("B,Hkv,L,k", [(1, 1, 5, 1), (1, 3, 40, 33), (2, 4, 700, 97), (1, 2, 3000, 1600),
+                                        (1, 8, 64, 64), (1, 1, 600, 513), (3, 19, 9, 9), (1, 1, 900, 512)])
 def test_gather_rows_host_rounds(B, Hkv, L, k):
     """Row counts below, at and beyond one round of the gather's workgroups, with unused entries."""
     rng = np.random.default_rng(k)
