@@ -95,7 +95,7 @@ static int group_wgs_per_cu(int G, int ch, int n_ch, const DeviceCaps &caps)
     return (int)std::min<size_t>(3, (size_t)caps.lds_per_cu / lds);
 }
 
-bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose)
+bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
 {
     if (!shape_ok(s, true)) return false;
     const DeviceCaps caps = device_caps();
@@ -216,10 +216,19 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose)
     // to 64 groups of 4 21.3 -> 23.8, 128 single heads of 10240 with 16 channels 30.0 -> 30.1; 680 rows,
     // 80 single heads of 5445 22.0 -> 24.7.  Pairs gain less: 64 units of 6016 20.8 -> 21.6, 128
     // 23.6 -> 22.0, 128 of 8192 26.3 -> 26.9.
+    // Where heads share a unit, wide label rows (more than 12 fp16 channels, two words of 4-bit codes) move the
+    // line: one / several for groups of 4 with 16 channels 0.97 at 5000 tokens, 1.01 at 5632, 1.02 to 1.04 at 6144 (8 to 32
+    // units), 4-bit 0.94, 0.99, 1.00; 128 units with 24 channels 0.90 at 6144, 0.95 at 7000, 1.02 at 8192, 4-bit 0.92, 1.02,
+    // 1.05; pairs 4-bit 0.98 at 5632, 1.02 at 6144.  Single heads of up to 24 channels stay below 1 (64 units of 6144, 4-bit of
+    // 16 channels: 1.02).
     // (The workspace keeps the room of the plan with several.)
     const int n_ws = (s.L + ch - 1) / ch;
     const bool half_full = p->units * 2 >= caps.cus;
-    const int one_wg_tokens = p->G == 2 ? (half_full ? 6144 : 0) : (half_full ? 8192 : 6144);
+    const bool wide = s.r > (q4 ? 8 : 12);
+    const int one_wg_tokens = p->G == 1   ? (half_full ? 8192 : 6144)
+                              : p->G == 2 ? (half_full ? (wide ? 5632 : 6144) : 0)
+                              : half_full ? (wide ? 6656 : 8192)
+                                          : (wide ? 5376 : 6144);
     if (n_ws > 1 && p->refine_attend && purpose == PLAN_DECODE_SCORING && tune_get(1) == 0 &&
         s.L <= one_wg_tokens && p->k_eff <= one_wg_tokens / 16) {
         ch = (s.L + 255) & ~255;
@@ -574,11 +583,11 @@ ds_status_t ds_workspace_errors(const void *workspace, size_t workspace_bytes, c
 
 static ds_status_t select_common(const void *q, const void *label, const int32_t *channels,
                                  void *workspace, size_t workspace_bytes, const ds_shape_t *shape,
-                                 Plan *p, PlanFor purpose = PLAN_SELECT)
+                                 Plan *p, PlanFor purpose = PLAN_SELECT, bool q4 = false)
 {
     if (!q || !label || !channels || !workspace || !shape) return DS_ERR_NULL;
     if (!shape_ok(*shape, true)) return DS_ERR_SHAPE;
-    if (!make_plan(*shape, p, purpose)) return DS_ERR_UNSUPPORTED;
+    if (!make_plan(*shape, p, purpose, q4)) return DS_ERR_UNSUPPORTED;
     if (!aligned(q, 16) || !aligned(label, 16) || !aligned(workspace, 16)) return DS_ERR_ALIGN;
     if (workspace_bytes < p->total) return DS_ERR_WORKSPACE;
     return DS_OK;
@@ -643,7 +652,7 @@ static ds_status_t sparse_decode_impl(const void *q, const void *label, const vo
         if (may_score) p = ps;
     } else {
         rc = select_common(q, label, channels, workspace, workspace_bytes, shape, &p,
-                           may_score ? PLAN_DECODE_SCORING : PLAN_DECODE);
+                           may_score ? PLAN_DECODE_SCORING : PLAN_DECODE, src.kind == SRC_Q4);
         if (rc != DS_OK) return rc;
     }
     if (!aligned(K, 256) || !aligned(V, 256) || !aligned(out, 16) || (idx_out && !aligned(idx_out, 16)))
@@ -705,7 +714,7 @@ ds_status_t ds_plan_describe(const ds_shape_t *shape, int32_t label_kind, int32_
     const ScoreSrcKind kind = static_cast<ScoreSrcKind>(label_kind);
     const bool may_score = label_may_score(*shape, kind);
     Plan p;
-    if (!make_plan(*shape, &p, may_score ? PLAN_DECODE_SCORING : PLAN_DECODE)) return DS_ERR_UNSUPPORTED;
+    if (!make_plan(*shape, &p, may_score ? PLAN_DECODE_SCORING : PLAN_DECODE, kind == SRC_Q4)) return DS_ERR_UNSUPPORTED;
     const bool si = plan_scores_itself(p, may_score);
     const bool ra = p.refine_attend && refine_attend_ok(p, si);
     const int planned = !ra ? 3 : si ? p.unit_groups : 2;

@@ -111,9 +111,10 @@ DeviceCaps device_caps();                  // of the current device (cached per 
 void device_caps_pretend(const DeviceCaps *caps);  // test hook: overrides device_caps() for this thread (nullptr: off)
 
 // What the plan is for: the split select call (and anything that runs the candidate launch), a
-// decode call, or a decode call whose attention launch may do the scoring as well.
+// decode call, or a decode call whose attention launch may do the scoring as well.  q4: that launch
+// would score 4-bit labels.
 enum PlanFor { PLAN_SELECT = 0, PLAN_DECODE = 1, PLAN_DECODE_SCORING = 2 };
-bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose = PLAN_SELECT);
+bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose = PLAN_SELECT, bool q4 = false);
 bool make_dense_plan(const ds_shape_t &s, int n_tokens, DensePlan *p, size_t workspace_bytes = SIZE_MAX);
 // Workspace with which a dense or gathered-rows call is never refused: that of chunks of 64, 256 or
 // 1024 tokens by the number of tokens.  (A plan may want less, or more; then it makes do.)

@@ -105,3 +105,25 @@ def test_q4_build_waits_only_for_workgroups_that_the_device_holds(cus, r):
             else:
                 assert p.launches == 3 and (p.n_max - 1) * p.per_wg < L <= p.n_max * p.per_wg
     assert seen == ({1, 2, 3} if cus > 8 or r >= 64 else seen | {1, 3})
+
+
+@pytest.mark.parametrize("units,G,tokens,r,kind,one", [
+    (32, 1, 6144, 8, 0, True), (32, 1, 6145, 8, 0, False), (32, 1, 6144, 16, 0, True), (32, 1, 6144, 24, 0, True),
+    (128, 1, 8192, 24, 0, True), (128, 1, 8193, 8, 0, False), (127, 1, 8192, 8, 0, False), (64, 1, 6144, 16, 2, True),
+    (32, 4, 6144, 8, 0, True), (32, 4, 6145, 8, 0, False), (32, 4, 6144, 12, 0, True), (32, 4, 6144, 8, 2, True),
+    (32, 4, 5376, 16, 0, True), (32, 4, 5377, 16, 0, False), (8, 8, 6000, 16, 2, False), (8, 8, 6000, 12, 2, False),
+    (128, 4, 8192, 8, 0, True), (128, 4, 6656, 24, 0, True), (128, 4, 6657, 24, 0, False), (128, 4, 8192, 12, 0, True),
+    (128, 8, 6657, 16, 2, False), (128, 2, 6144, 8, 0, True), (128, 2, 6145, 8, 0, False), (128, 2, 5632, 16, 2, True),
+    (128, 2, 5633, 16, 2, False), (64, 2, 5000, 8, 0, False),
+])
+def test_one_workgroup_per_unit_up_to_a_line(units, G, tokens, r, kind, one):
+    """Both sides of the rule for units of 4K to 8K tokens, and of its limit of a sixteenth in rows."""
+    wgs = lambda k: ds.ds_plan_describe(ds.shape(1, units * G, units, 128, tokens, (tokens + 3) // 4 * 4, r, k),
+                                        kind)["workgroups_per_unit"]
+    assert (wgs(tokens // 16) == 1) == one
+    if one:
+        half = 2 * units >= 256
+        wide = r > (8 if kind == 2 else 12)
+        line = (8192 if half else 6144) if G == 1 else (5632 if wide else 6144) if G == 2 else \
+               (6656 if wide else 8192) if half else (5376 if wide else 6144)
+        assert wgs(line // 16) == 1 and wgs(line // 16 + 1) > 1
