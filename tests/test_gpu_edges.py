@@ -221,48 +221,73 @@ def test_gather_rows_host_rounds(B, Hkv, L, k):
     assert np.array_equal(rows.cpu().numpy().view(np.uint16), want.view(np.uint16))
 
 
-@pytest.mark.parametrize("Hq,Hkv,L,L_max,r,k,cus", [
-    (1, 1, 1, 1, 4, 1, 0),              # one token
-    (3, 3, 1500, 1501, 4, 93, 0),       # rows of 8 bytes, units on odd multiples of 8 bytes
-    (2, 2, 9001, 9003, 4, 562, 0),      # several workgroups per unit, a ragged last chunk
-    (2, 1, 700, 701, 12, 50, 0),        # pairs, rows of three 8-byte pieces
-    (7, 1, 9100, 9101, 12, 570, 0),     # groups of 7, several workgroups per unit
-    (120, 120, 2100, 2100, 12, 131, 0), # a call that streams past the caches
-    (1, 1, 12000, 12000, 12, 750, 0),   # single head, several workgroups
-    (4, 4, 3000, 3001, 24, 187, 0),     # rows of three 16-byte pieces
-    (16, 1, 8500, 8500, 24, 531, 0),    # groups of 16
-    (6, 6, 11000, 11000, 24, 300, 8),   # units enough for one workgroup of 1024 threads each
-    (6, 6, 10950, 10951, 4, 300, 8),    # ... with 8-byte rows
-    (6, 6, 16384, 16384, 12, 1024, 8),  # ... of the longest unit
-    (1, 1, 6144, 6144, 8, 384, 0),      # the longest unit that one workgroup takes of few units ...
-    (4, 1, 6145, 6145, 16, 384, 0),     # ... and one token more, in groups of 4
-    (4, 4, 8191, 8191, 8, 511, 8),      # units for half the device: one workgroup of 1024 threads each ...
-    (4, 4, 8193, 8193, 8, 511, 8),      # ... and several per unit
-    (6, 3, 6100, 6100, 8, 400, 8),      # pairs: several per unit ...
-    (8, 4, 6100, 6100, 8, 400, 8),      # ... or one when there are units for half the device
+ONE, SEVERAL = True, False
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,L_max,r,k,cus,one,streams", [
+    (1, 1, 1, 1, 4, 1, 0, ONE, False),              # one token
+    (3, 3, 1500, 1501, 4, 93, 0, ONE, False),       # rows of 8 bytes, units on odd multiples of 8 bytes
+    (2, 2, 9001, 9003, 4, 562, 0, SEVERAL, False),  # several workgroups per unit, a ragged last chunk
+    (2, 1, 700, 701, 12, 50, 0, ONE, False),        # pairs, rows of three 8-byte pieces
+    (7, 1, 9100, 9101, 12, 570, 0, SEVERAL, False), # groups of 7, several workgroups per unit
+    (120, 120, 2100, 2100, 12, 131, 0, ONE, False), # many units that the caches hold
+    (1, 1, 12000, 12000, 12, 750, 0, SEVERAL, False),  # single head, several workgroups
+    (4, 4, 3000, 3001, 24, 187, 0, ONE, False),     # rows of three 16-byte pieces
+    (16, 1, 8500, 8500, 24, 531, 0, SEVERAL, False),  # groups of 16
+    (6, 6, 11000, 11000, 24, 300, 8, ONE, False),   # units enough for one workgroup of 1024 threads each
+    (6, 6, 10950, 10951, 4, 300, 8, ONE, False),    # ... with 8-byte rows
+    (6, 6, 16384, 16384, 12, 1024, 8, ONE, False),  # ... of the longest unit
+    # calls that stream past the caches: single heads and pairs with one workgroup per unit and several
+    (24, 24, 2500, 2500, 4, 1400, 0, ONE, True),
+    (24, 24, 2500, 2501, 12, 1400, 0, ONE, True),
+    (24, 24, 2500, 2500, 24, 1400, 0, ONE, True),
+    (48, 24, 2500, 2501, 4, 1400, 0, ONE, True),
+    (48, 24, 2500, 2500, 12, 1400, 0, ONE, True),
+    (48, 24, 2500, 2500, 24, 1400, 0, ONE, True),
+    (12, 12, 12000, 12001, 4, 2600, 0, SEVERAL, True),
+    (12, 12, 12000, 12000, 12, 2600, 0, SEVERAL, True),
+    (12, 12, 12000, 12000, 24, 2600, 0, SEVERAL, True),
+    (24, 12, 12000, 12000, 4, 2600, 0, SEVERAL, True),
+    (24, 12, 12000, 12001, 12, 2600, 0, SEVERAL, True),
+    (24, 12, 12000, 12000, 24, 2600, 0, SEVERAL, True),
+    # both sides of the rule for units of 4K to 8K tokens
+    (1, 1, 6144, 6144, 8, 384, 0, ONE, False),      # the longest unit that one workgroup takes of few units ...
+    (1, 1, 6144, 6144, 8, 385, 0, SEVERAL, False),  # ... and a row more ...
+    (4, 1, 6145, 6145, 8, 384, 0, SEVERAL, False),  # ... or a token more, in groups of 4
+    (4, 1, 5376, 5376, 16, 336, 0, ONE, False),     # the same of wide label rows
+    (4, 1, 5377, 5377, 16, 336, 0, SEVERAL, False),
+    (4, 4, 8191, 8191, 8, 511, 8, ONE, False),      # units for half the device: one workgroup of 1024 threads each ...
+    (4, 4, 8193, 8193, 8, 511, 8, SEVERAL, False),  # ... and several per unit
+    (6, 3, 6100, 6100, 8, 380, 8, SEVERAL, False),  # pairs: several per unit ...
+    (8, 4, 6100, 6100, 8, 380, 8, ONE, False),      # ... or one when there are units for half the device
+    (8, 4, 6144, 6144, 8, 385, 8, SEVERAL, False),
 ])
-def test_decode_label_rows_and_workgroups_per_unit(Hq, Hkv, L, L_max, r, k, cus):
+def test_decode_label_rows_and_workgroups_per_unit(Hq, Hkv, L, L_max, r, k, cus, one, streams):
     """Label rows of every number of channels that the attention launch scores itself, and both
     sides of the rules that give a unit one workgroup (planned for a small device where they
-    count units)."""
+    count units) and that mark loads as streaming (16 MiB of label and K/V rows)."""
     w = Workload("t", 1, Hq, Hkv, 128, L, r, k, 1)
     t = make_layer_numpy(w, L_max=L_max)
+    assert (Hkv * (L * r * 2 + k * 512) >= 16 << 20) == streams
     if cus:
         ds.ds_pretend_device(cus, 8, 160 << 10)
     try:
+        plan = ds.ds_plan_describe(ds.shape(1, Hq, Hkv, 128, L, L_max, r, k))
+        assert plan["scores_itself"] == 1 and (plan["workgroups_per_unit"] == 1) == one
         case = Case(t["q"], t["K"], t["V"], rand_channels(Hkv, r, seed=L + r), L, k)
         full_parity(case, what=f"Hq{Hq} Hkv{Hkv} L{L} r{r} k{k}")
     finally:
         ds.ds_pretend_device(0, 0, 0)
 
 
-@pytest.mark.parametrize("Hq,L,k,step", [
-    (1, 12000, 800, 0.0),      # every key the same: 12000 candidates, the tie cut among them all
-    (2, 20000, 9000, 1e-3),    # a few keys of many tokens each
-    (4, 9000, 500, 1e-3),      # matrix-core variant
-    (1, 5000, 3100, 1e-3),     # one workgroup per unit, more candidates than it ranks at once
+@pytest.mark.parametrize("Hq,L,k,step,one", [
+    (1, 12000, 800, 0.0, SEVERAL),      # every key the same: 12000 candidates, the tie cut among them all
+    (2, 20000, 9000, 1e-3, SEVERAL),    # a few keys of many tokens each
+    (4, 9000, 500, 1e-3, SEVERAL),      # matrix-core variant
+    (1, 4000, 2900, 1e-3, ONE),         # one workgroup per unit, more candidates than it ranks at once
+    (1, 5000, 3100, 1e-3, SEVERAL),
 ])
-def test_decode_many_candidates(Hq, L, k, step):
+def test_decode_many_candidates(Hq, L, k, step, one):
     """Thousands of keys in the threshold bin: the refinement reads those beyond the first 2048 again
     in every pass; the index list is the oracle's, ties to the lowest token."""
     w = Workload("t", 1, Hq, 1, 128, L, 8, k, 1)
@@ -271,5 +296,6 @@ def test_decode_many_candidates(Hq, L, k, step):
     t["q"][:] = np.float16(0.5)
     rng = np.random.default_rng(L)
     t["K"][0, 0][:, ch[0]] = (1.0 + step * rng.integers(0, 5, (L, 1))).astype(np.float16)
+    assert (ds.ds_plan_describe(ds.shape(1, Hq, 1, 128, L, L, 8, k))["workgroups_per_unit"] == 1) == one
     case = Case(t["q"], t["K"], t["V"], ch, L, k)
     full_parity(case, what=f"many candidates L{L} k{k}")
