@@ -353,7 +353,7 @@ ds_status_t ds_profile_read(int id, double *total_ms, int64_t *launches);
  *   knob 4: where the exact top-k threshold is settled on the three-launch path: 0 = automatic
  *           (in the scoring launch for units of up to 8K tokens), 1 = always in a separate
  *           candidate launch, 2 = always in the scoring launch.  On launch shape 4 with a label
- *           cache of 4, 8, 12, 16 or 24 fp16 channels, or a 4-bit one of up to 16 channels whose token
+ *           cache of a multiple of 4 fp16 channels up to 32, or a 4-bit one of up to 16 channels whose token
  *           rows 16-byte loads can take (L_max a multiple of 4, of 2 above 8 channels), the
  *           attention launch can do the scoring as well (one launch in all): 0 = when a unit
  *           has one workgroup, or the whole grid is resident at once (single heads and pairs:
@@ -381,7 +381,9 @@ int ds_tune_get(int knob);
  * runtime reports for the kernels has been taken into account (-1 when no device is visible);
  * out[2] = tokens per workgroup, out[3] = workgroups per unit, out[4] = workgroups of the
  * attention launches together, out[5] = compute units planned for, out[6] = 1 if the attention launch
- * scores as well, out[7] = query heads per KV head.
+ * scores as well, out[7] = query heads per KV head.  (For a workspace of ds_workspace_bytes(); one
+ * that holds no more than the plan with a scoring launch of its own is enough for fp16 labels of other
+ * than 8 or 16 channels, and gets that plan.)
  * ds_pretend_device makes the calling thread's plans (and residency checks) assume a device of
  * `cus` compute units on `xccs` dies with `lds_per_cu` bytes of LDS each, instead of the current
  * one; (0, 0, 0) ends it.  The workspace layout follows the plan: query ds_workspace_bytes() and

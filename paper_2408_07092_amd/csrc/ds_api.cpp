@@ -119,7 +119,7 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
     // Launch shape of ds_sparse_decode: units of more than 8K tokens refine the threshold behind
     // the attention (two launches).  Short units get one workgroup each, which refines and attends
     // the whole unit out of LDS and writes the result itself (and scores it too when the label
-    // cache is plain fp16 with 8 or 16 channels): everything between workgroups -- keys in memory,
+    // cache allows it): everything between workgroups -- keys in memory,
     // histograms, arrival counting, partials -- costs more than it spreads at that size.  "Short"
     // is 4K tokens; 8K when there are enough units (256) to fill the device; 16K for a workgroup
     // that scores its unit itself, single heads or pairs, with 192 units or more (one 96 KiB
@@ -608,8 +608,8 @@ static ds_status_t enqueue_select(const void *q, const void *label, const int32_
 
 static bool label_may_score(const ds_shape_t &s, ScoreSrcKind kind)
 {
-    // the attention launch can score as well when the labels are plain fp16 with 4, 8, 12, 16 or 24
-    // channels (with a scoring launch against without: 12 channels, 12 units of 20K tokens in groups
+    // the attention launch can score as well when the labels are plain fp16 of a multiple of 4 channels
+    // up to 32 (with a scoring launch against without: 12 channels, 12 units of 20K tokens in groups
     // of 7 29.4 -> 25.3 us, 32 units of 64K tokens 44.3 -> 34.1; 24 channels, 128 units of 4K tokens
     // 24.2 -> 18.3; 4 channels, 32 units of 2K tokens 15.4 -> 10.6), or 4-bit codes of up to 16
     // channels in rows that 16-byte loads can take (knob 4 = 1 keeps the separate scoring launch)

@@ -287,7 +287,7 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     if constexpr (SMODE != 0) {
         // ---- 0. Algorithm 1 steps 1-2 right here: stream the chunk's label rows, keys go to LDS
         // only; with one workgroup per unit the threshold bin comes out of its own histogram.
-        // Same arithmetic and order as k_score.  SMODE = r for fp16 labels (4, 8, 12, 16 or 24); SMODE = -8 /
+        // Same arithmetic and order as k_score.  SMODE = r for fp16 labels (a multiple of 4, up to 32); SMODE = -8 /
         // -16 for the 4-bit label cache of up to 8 / 16 channels (one / two words per token).
         constexpr bool kQ4 = SMODE < 0;
         constexpr int RR = kQ4 ? -SMODE : SMODE;
@@ -355,7 +355,7 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
         if constexpr (!kQ4) {
         const _Float16 *lab = a.label + (size_t)u * a.L_max * SMODE;
         // A token's label row is NV pieces: of eight channels, or of four when eight do not divide it.
-        // (24 channels: half as many rows in flight, their registers are as many)
+        // (more than 16 channels: half as many rows in flight)
         constexpr int PE = RR % 8 ? 4 : 8;
         constexpr int NV = RR / PE;
         using Piece = typename std::conditional<PE == 8, half8, half4>::type;
@@ -1135,7 +1135,7 @@ struct RaKernel {
     int threads;
 };
 
-// smode: 0 = keys and threshold bin come from the scoring launch; 4 .. 24 = fp16 labels of that
+// smode: 0 = keys and threshold bin come from the scoring launch; 4 .. 32 = fp16 labels of that
 // many channels scored here; -8 / -16 = 4-bit labels of up to that many channels scored here.
 template <int GT, int RPS, bool ST = true>
 static RaFn ra_fn(int smode)
@@ -1145,8 +1145,11 @@ static RaFn ra_fn(int smode)
     case 4: return k_refine_attend<GT, 4, RPS, ST>;
     case 8: return k_refine_attend<GT, 8, RPS, ST>;
     case 12: return k_refine_attend<GT, 12, RPS, ST>;
-    case 24: return k_refine_attend<GT, 24, RPS, ST>;
     case 16: return k_refine_attend<GT, 16, RPS, ST>;
+    case 20: return k_refine_attend<GT, 20, RPS, ST>;
+    case 24: return k_refine_attend<GT, 24, RPS, ST>;
+    case 28: return k_refine_attend<GT, 28, RPS, ST>;
+    case 32: return k_refine_attend<GT, 32, RPS, ST>;
     case -8: return k_refine_attend<GT, -8, RPS, ST>;
     default: return k_refine_attend<GT, -16, RPS, ST>;
     }

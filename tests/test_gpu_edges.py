@@ -9,7 +9,7 @@ import torch
 import paper_2408_07092_amd as ds
 from oracle import ds_oracle as O
 from tests.parity_util import Case, check_output, full_parity, to_dev
-from tests.test_plans_host import q4_plan
+from tests.test_plans_host import q4_plan, smallest_workspace
 from workloads import Workload, make_layer_numpy
 
 pytestmark = pytest.mark.gpu
@@ -250,6 +250,19 @@ ONE, SEVERAL = True, False
     (24, 12, 12000, 12000, 4, 2600, 0, SEVERAL, True),
     (24, 12, 12000, 12001, 12, 2600, 0, SEVERAL, True),
     (24, 12, 12000, 12000, 24, 2600, 0, SEVERAL, True),
+    # wider label rows: five and seven pieces of 8 bytes, four of 16
+    (3, 3, 1500, 1501, 20, 93, 0, ONE, False),
+    (2, 1, 9001, 9003, 20, 562, 0, SEVERAL, False),
+    (12, 12, 12000, 12001, 20, 2600, 0, SEVERAL, True),
+    (1, 1, 64, 65, 28, 9, 0, ONE, False),
+    (48, 24, 2500, 2501, 28, 1400, 0, ONE, True),
+    (6, 6, 10950, 10951, 28, 300, 8, ONE, False),
+    (7, 1, 9100, 9101, 28, 570, 0, SEVERAL, False),
+    (2, 2, 9001, 9003, 32, 562, 0, SEVERAL, False),
+    (24, 24, 2500, 2501, 32, 1400, 0, ONE, True),
+    (6, 6, 16384, 16384, 32, 1024, 8, ONE, False),
+    (16, 1, 8500, 8500, 32, 531, 0, SEVERAL, False),
+    (4, 1, 4000, 4001, 32, 250, 0, ONE, False),
     # both sides of the rule for units of 4K to 8K tokens
     (1, 1, 6144, 6144, 8, 384, 0, ONE, False),      # the longest unit that one workgroup takes of few units ...
     (1, 1, 6144, 6144, 8, 385, 0, SEVERAL, False),  # ... and a row more ...
@@ -278,6 +291,34 @@ def test_decode_label_rows_and_workgroups_per_unit(Hq, Hkv, L, L_max, r, k, cus,
         full_parity(case, what=f"Hq{Hq} Hkv{Hkv} L{L} r{r} k{k}")
     finally:
         ds.ds_pretend_device(0, 0, 0)
+
+
+@pytest.mark.parametrize("r", [12, 32])
+def test_decode_in_the_smallest_workspace(r):
+    """A workspace that holds the plan with a scoring launch and not the one without (planned for 16
+    compute units, where the two differ): that plan, the same rows."""
+    B, Hq, Hkv, L, k = 1, 12, 3, 33000, 4125
+    shp = ds.shape(B, Hq, Hkv, 128, L, L, r, k)
+    t = make_layer_numpy(Workload("t", B, Hq, Hkv, 128, L, r, k, 1))
+    ch = rand_channels(Hkv, r, seed=r)
+    q, K, V, chd = to_dev(t["q"]), to_dev(t["K"]), to_dev(t["V"]), to_dev(ch)
+    label = torch.empty((B, Hkv, L, r), dtype=torch.float16, device="cuda")
+    ds.ds_build_label(K, chd, label, shp)
+    got = []
+    ds.ds_pretend_device(16, 8, 160 << 10)
+    try:
+        for n in ((smallest_workspace(shp) + 15) // 16 * 16, ds.ds_workspace_bytes(shp)):
+            ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+            ds.ds_workspace_init(ws)
+            out = torch.full((B, Hq, 128), float("nan"), dtype=torch.float32, device="cuda")
+            idx = torch.full((B, Hkv, k), -1, dtype=torch.int32, device="cuda")
+            ran = launches_of(lambda: ds.ds_sparse_decode(q, label, K, V, chd, out, idx, ws, shp))
+            got.append(("k_score" in ran, idx.cpu().numpy(), out.cpu().numpy()))
+    finally:
+        ds.ds_pretend_device(0, 0, 0)
+    assert got[0][0] and not got[1][0]
+    assert np.array_equal(got[0][1], got[1][1])
+    check_output(got[0][2], got[1][2].astype(np.float64), "smallest workspace")
 
 
 @pytest.mark.parametrize("Hq,L,k,step,one", [

@@ -127,3 +127,40 @@ def test_one_workgroup_per_unit_up_to_a_line(units, G, tokens, r, kind, one):
         line = (8192 if half else 6144) if G == 1 else (5632 if wide else 6144) if G == 2 else \
                (6656 if wide else 8192) if half else (5376 if wide else 6144)
         assert wgs(line // 16) == 1 and wgs(line // 16 + 1) > 1
+
+
+def smallest_workspace(shp):
+    """Bytes from which ds_sparse_decode no longer refuses the workspace: host only, a misaligned K is
+    refused after it and before anything is enqueued."""
+    fake, bad = ctypes.c_void_p(0x10000), ctypes.c_void_p(0x10010)
+    status = lambda n: ds.lib().ds_sparse_decode(fake, fake, bad, fake, fake, fake, None, fake, n, ctypes.byref(shp), None)
+    lo, hi = 0, ds.ds_workspace_bytes(shp)
+    assert status(hi) == ds.DS_ERR_ALIGN and status(lo) == ds.DS_ERR_WORKSPACE
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        if status(mid) == ds.DS_ERR_WORKSPACE:
+            lo = mid
+        else:
+            hi = mid
+    return hi
+
+
+@pytest.mark.parametrize("r", [4, 12, 20, 24, 28, 32])
+@pytest.mark.parametrize("units,G,L", [(2, 1, 3000), (12, 7, 20011), (32, 1, 65536), (128, 2, 9000), (1, 1, 262144)])
+def test_scoring_in_the_attention_launch_needs_no_larger_workspace(units, G, L, r):
+    """Label widths that may be scored in the attention launch ask for no more than the plan with a
+    scoring launch does."""
+    shp = ds.shape(1, units * G, units, 128, L, L, r, L // 16)
+    need = smallest_workspace(shp)
+    ds.ds_tune_set(4, 1)
+    try:
+        assert smallest_workspace(shp) == need
+    finally:
+        ds.ds_tune_set(4, 0)
+
+
+def test_label_widths_that_the_attention_launch_scores():
+    """Every multiple of 4 up to 32, and no other."""
+    for r in range(1, 129):
+        si = ds.ds_plan_describe(ds.shape(1, 32, 32, 128, 4096, 4096, r, 256))["scores_itself"]
+        assert si == (r % 4 == 0 and r <= 32), r
