@@ -134,7 +134,7 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
                        (tune_get(3) == 4 ||
                         (tune_get(3) == 0 && (s.L > (1 << 13) || one_wg_units ||
                                             (purpose == PLAN_DECODE_SCORING && s.L > (1 << 12)))));
-    int ch = tune_get(1);
+    int ch = tune_get(1), ch_room = 0;
     p->group_scores_itself = false;
     p->unit_groups = 1;
     if (ch == 0 && p->refine_attend && !one_wg_units && p->G > 2 && purpose == PLAN_DECODE_SCORING) {
@@ -162,8 +162,8 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
     } else if (p->refine_attend && one_wg_units) {
         ch = (s.L + 255) & ~255;
     } else if (p->refine_attend) {
-        // every workgroup resident at once (six per CU on the vector path, three on the matrix
-        // cores) when chunks of up to 4096 / 6144 tokens allow it
+        // every workgroup resident at once (registers allow four per CU on the vector path, three on
+        // the matrix cores) when chunks of up to 4096 / 6144 tokens allow it
         if (p->G <= 2) {
             // A launch that scores as well needs its whole grid resident, and LDS decides how many
             // workgroups a CU holds (6 bytes a token for keys and row list, about 26 KiB of fixed
@@ -189,9 +189,15 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
                     }
                 }
             }
+            // Behind a scoring launch: a second round of workgroups for the few that do not fit costs far
+            // more than chunks of twice the size (scores from K rows, 17 single heads of 64K tokens, 1088
+            // workgroups 104.4 us, 544 93.3; 48 of 32K 113.0 and 103.6; pairs 107.0 and 95.1; 64
+            // fp16 channels 78.9 and 67.9; below that line 40 single heads of 16K tokens in 640 or 320, 59.7 and 59.0).
             if (ch == 0) {
                 ch = 1024;
                 while (ch < 4096 && (int64_t)p->units * ((s.L + ch - 1) / ch) > 6 * caps.cus) ch *= 2;
+                ch_room = ch;  // (the workspace keeps the room of six per CU)
+                while (ch < 4096 && (int64_t)p->units * ((s.L + ch - 1) / ch) > 4 * caps.cus) ch *= 2;
             }
         } else {
             ch = 2048;
@@ -222,7 +228,7 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
     // 1.05; pairs 4-bit 0.98 at 5632, 1.02 at 6144.  Single heads of up to 24 channels stay below 1 (64 units of 6144, 4-bit of
     // 16 channels: 1.02).
     // (The workspace keeps the room of the plan with several.)
-    const int n_ws = (s.L + ch - 1) / ch;
+    const int n_ws = (s.L + (ch_room ? ch_room : ch) - 1) / (ch_room ? ch_room : ch);
     const bool half_full = p->units * 2 >= caps.cus;
     const bool wide = s.r > (q4 ? 8 : 12);
     const int one_wg_tokens = p->G == 1   ? (half_full ? 8192 : 6144)
@@ -405,7 +411,7 @@ const char *ds_strerror(ds_status_t status)
     return "unknown status";
 }
 
-int ds_version(void) { return 109; }
+int ds_version(void) { return 110; }
 
 ds_status_t ds_calibrate_channels(const uint16_t *q_calib, const uint16_t *k_calib, int32_t N,
                                   int32_t Hq, int32_t Hkv, int32_t d, int32_t r,

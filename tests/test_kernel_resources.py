@@ -68,3 +68,15 @@ def test_q4_build_is_limited_by_its_tile_alone(kernels):
     LDS than it allows for."""
     k = kernels["k_q4_build"]
     assert k[".vgpr_count"] + k.get(".agpr_count", 0) <= 64 and k[".group_segment_fixed_size"] <= 1280
+
+
+def test_vector_attention_kernels_leave_room_for_four_workgroups(kernels):
+    """What the plans count on: four workgroups of 256 threads to a compute unit (128 registers) for the
+    streaming kernels of single heads and pairs, three (168) for those on the matrix cores."""
+    seen = 0
+    for n, k in kernels.items():
+        m = re.match(r"k_refine_attend<(\d+), (-?\d+), (\d+), (true|false)>", n)
+        if m and m.group(3) != "8" and m.group(4) == "true":
+            seen += 1
+            assert k[".vgpr_count"] + k.get(".agpr_count", 0) <= (128 if int(m.group(1)) <= 2 else 168), n
+    assert seen >= 5 * 11

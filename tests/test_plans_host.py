@@ -164,3 +164,16 @@ def test_label_widths_that_the_attention_launch_scores():
     for r in range(1, 129):
         si = ds.ds_plan_describe(ds.shape(1, 32, 32, 128, 4096, 4096, r, 256))["scores_itself"]
         assert si == (r % 4 == 0 and r <= 32), r
+
+
+@pytest.mark.parametrize("units,G,L,chunk", [
+    (16, 1, 65536, 1024), (17, 1, 65536, 2048), (20, 2, 65536, 2048), (48, 1, 32768, 2048), (8, 1, 131072, 1024),
+    (9, 1, 131072, 2048), (40, 1, 16384, 1024), (32, 1, 65536, 2048), (40, 1, 65536, 4096), (150, 2, 9000, 2048),
+])
+def test_chunks_behind_a_scoring_launch_fit_at_once(units, G, L, chunk):
+    """Single heads and pairs that a separate launch scores: four workgroups to a compute unit, as many
+    as the kernel's registers allow, and not a second round for a few more."""
+    for kind, r in ((1, 8), (0, 64), (0, 7), (2, 32)):
+        p = ds.ds_plan_describe(ds.shape(1, units * G, units, 128, L, L, r, L // 16), kind)
+        assert p["scores_itself"] == 0 and p["tokens_per_workgroup"] == chunk
+        assert p["workgroups"] <= 4 * 256 or chunk == 4096
