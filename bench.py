@@ -60,7 +60,7 @@ def parse():
     ap.add_argument("--interleaved", action="store_true",
                     help="K|V cache as one [L,2,d] array per head (512-byte gathers), ds_sparse_decode_kv")
     ap.add_argument("--predict", action="store_true",
-                    help="C5: select with queries predicted from the previous layer's embedding (W_q GEMV on the select stream)")
+                    help="C5: select with queries predicted from the previous layer's embedding (W_q GEMV ahead of the selection)")
     ap.add_argument("--label-bits", type=int, default=16, choices=(16, 4),
                     help="label cache precision: fp16 (the metric's configuration) or the 4-bit cache")
     ap.add_argument("--trace", action="store_true",
@@ -483,7 +483,7 @@ def bench_offload(args, w, ds, torch, dev):
         else:
             q_sel = q
         ev[1].record()
-        ds.ds_select(q_sel, label, ch, dec.idx[0], dec.ws_sel[0], shp)
+        ds.ds_select(q_sel, label, ch, dec.idx[0], dec.ws_sel, shp)
         ev[2].record()
         ds.ds_gather_rows_host(Kp, Vp, dec.idx[0], dec.rows[0], shp)
         ev[3].record()
@@ -497,13 +497,13 @@ def bench_offload(args, w, ds, torch, dev):
     # the alternative transport for the selected rows (Sec. 5.1 leaves it open): index list to the
     # host, rows packed there into a pinned staging buffer, one asynchronous copy to the device
     q, label, ch, Kp, Vp = layers[0]
-    ds.ds_select(q, label, ch, dec.idx[0], dec.ws_sel[0], shp)
+    ds.ds_select(q, label, ch, dec.idx[0], dec.ws_sel, shp)
     torch.cuda.synchronize()
     staging = torch.empty((w.B, w.Hkv, w.k, 2, w.d), dtype=torch.float16).pin_memory()
     pack_us = []
     for _ in range(3):
         t0 = time.perf_counter()
-        idx_h = dec.idx[0].cpu().to(torch.int64)                       # waits for the select stream's result
+        idx_h = dec.idx[0].cpu().to(torch.int64)                       # waits for the selection
         for b in range(w.B):
             for h in range(w.Hkv):
                 torch.index_select(Kp[b, h], 0, idx_h[b, h], out=staging[b, h, :, 0])

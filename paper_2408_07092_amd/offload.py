@@ -38,7 +38,7 @@ class OffloadDecoder:
         self.idx = [torch.empty((B, Hkv, k), dtype=torch.int32, device=self.dev) for _ in range(2)]
         self.rows = [torch.empty((B, Hkv, k, 2, d), dtype=torch.float16, device=self.dev) for _ in range(2)]
         # one workspace for the selections, one for the attention
-        self.ws_sel = [ds.ds_workspace_alloc(shp, self.dev)] * 2
+        self.ws_sel = ds.ds_workspace_alloc(shp, self.dev)
         self.ws_att = ds.ds_workspace_alloc(shp, self.dev)
         self.s_copy = torch.cuda.Stream(device=self.dev)
         self.ev_sel = [torch.cuda.Event() for _ in range(2)]
@@ -63,7 +63,7 @@ class OffloadDecoder:
                 x, Wq, q_pred = predict[l]
                 ds.ds_predict_query(x, Wq, q_pred, stream=main)
                 q = q_pred
-            ds.ds_select(q, label, ch, self.idx[s], self.ws_sel[s], self.shp, stream=main)
+            ds.ds_select(q, label, ch, self.idx[s], self.ws_sel, self.shp, stream=main)
             self.ev_sel[s].record(main)
             self.s_copy.wait_event(self.ev_sel[s])
             ds.ds_gather_rows_host(Kp, Vp, self.idx[s], self.rows[s], self.shp, stream=self.s_copy)

@@ -184,16 +184,17 @@ def test_planner_follows_the_device_it_is_told_of():
 
 
 def test_handed_over_arrays_are_never_read_with_plain_loads():
-    """Host only, a grep over the attention kernels: the workspace arrays that one workgroup
+    """Host only, a grep over the kernels: the workspace arrays that one workgroup
     writes and another reads inside a launch (unit histograms, candidate list, per-chunk counts
-    and offsets, partials) may be read only through ld_dev (device-scope loads).  A plain
+    and offsets, partials; of the 4-bit label build a unit's maxima and counter) may be read only
+    through ld_dev (device-scope loads).  A plain
     indexed read -- `x = cu[i]`, `... hu[i] + ...` -- could be served from a stale cache line.
     Allowed forms: the address taken for an atomic (`&hu[i]`), a clearing store (`hu[i] = 0`)."""
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     csrc = os.path.join(root, "paper_2408_07092_amd", "csrc")
-    names = r"(?:cu|hu|cuh|a\.cand|a\.ndef|a\.offs_rw|a\.part|a\.hist|a\.coarse|po|pg|part_unit|ph|pc)"
+    names = r"(?:cu|hu|cuh|a\.cand|a\.ndef|a\.offs_rw|a\.part|a\.hist|a\.coarse|po|pg|part_unit|ph|pc|am)"
     bad = []
-    for fn in ("ds_attend.hip", "ds_attend_core.h"):
+    for fn in ("ds_attend.hip", "ds_attend_core.h", "ds_misc.hip"):
         for ln, line in enumerate(open(os.path.join(csrc, fn)), 1):
             code = line.split("//")[0]
             for m in re.finditer(r"(?<![\w.&])" + names + r"\s*\[", code):

@@ -301,8 +301,8 @@ def test_select_gather_from_pinned_host_attend_rows():
 
 
 def test_offload_pipeline_double_buffer_matches_oracle_over_layers():
-    """Five layers through the two-slot pipeline (select / host-row fetch / attend on
-    three streams), twice, against the oracle per layer."""
+    """Five layers through the two-slot pipeline (selection and attention on one stream,
+    host-row fetch on another), twice, against the oracle per layer."""
     from paper_2408_07092_amd.offload import OffloadDecoder
     w = small_workload(2, 4, 2, 2500, 8, 150)          # GQA group 2, ragged L
     shp = ds.shape(w.B, w.Hq, w.Hkv, w.d, w.L, w.L, w.r, w.k)
