@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kWG) void k_q4_zero(uint32_t *amax, size_t n, uint3
 }
 
 // Builds the 4-bit label cache with one read of the K rows, which bounds it (64 units of 16K tokens,
-// 16 channels: 268 MB in 53 us, with two reads of it 87).  A workgroup picks the label values of its tile of
+// 16 channels: 268 MB in 53 us; 32 of 32K 59, with two reads of the rows 86).  A workgroup picks the label values of its tile of
 // tokens into LDS, adds its channel maxima to the unit's (amax), arrives at the unit's
 // counter and waits for the unit's other workgroups; with the unit's maxima complete it codes the
 // tile out of LDS.  The counter (arrivals in the low half, departures in the high half) is the
@@ -537,7 +537,7 @@ void make_q4_plan(const ds_shape_t &s, Q4Plan *p)
     // has to be worth the second counter and the atomics that queue on a unit's words (two reads
     // against one: 8 units of 8192 tokens 8 channels 11.9 against 11.6, 16 channels 11.9 against 12.8; 32 of
     // 8192 with 16 channels 26 against 20; with 128 channels, 64 workgroups of 128 atomics each, 46 against
-    // 60; one unit of 32K, 8 channels 13 against 15).  And a device has to hold a unit's workgroups four times over, in each
+    // 60; one unit of 32K, 8 channels 11 against 13).  And a device has to hold a unit's workgroups four times over, in each
     // of its dies: with that, calls on several streams at once, each with one unit partly started, all get on.
     const int held = (int)std::min<size_t>(8, (size_t)caps.lds_per_cu / (tile * token_lds + kQ4StaticLds));
     const int dies = std::max(1, caps.xccs);
