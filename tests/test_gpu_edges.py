@@ -109,6 +109,44 @@ def test_q4_build_on_a_device_that_holds_few_workgroups():
     assert np.array_equal(codes.cpu().numpy().view(np.uint32), want_codes)
 
 
+@pytest.mark.parametrize("B,Hkv,L,r,plan", [(2, 4, 300, 16, ALONE), (2, 4, 20000, 16, WAITS), (1, 2, 5000, 24, TWO_READS)])
+def test_q4_build_on_streams_and_in_a_graph(B, Hkv, L, r, plan):
+    """Three streams that build at the same time, and a captured build that is replayed with other K
+    rows: the oracle's codes and maxima each time."""
+    shp = ds.shape(B, Hkv, Hkv, 128, L, L, r, 1)
+    assert q4_plan(B * Hkv, L, r).launches == {"k_q4_amax": 3}.get(plan[0], len(plan))
+    ch = rand_channels(Hkv, r, seed=L)
+    chd = to_dev(ch)
+    sets = []
+    for i in range(3):
+        K = make_layer_numpy(Workload("t", B, Hkv, Hkv, 128, L, r, 1, 1), layer=i)["K"]
+        sets.append((K, to_dev(K), torch.empty((B, Hkv, L, (r + 7) // 8), dtype=torch.int32, device="cuda"),
+                     torch.empty((B, Hkv, r), dtype=torch.float32, device="cuda"), O.build_label_q4(K, ch, L)))
+
+    def check(codes, amax, want):
+        assert np.array_equal(amax.cpu().numpy(), want[1])
+        assert np.array_equal(codes.cpu().numpy().view(np.uint32), want[0])
+
+    streams = [torch.cuda.Stream() for _ in sets]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for st, (_, K, codes, amax, _) in zip(streams, sets):
+            ds.ds_build_label_q4(K, chd, codes, amax, shp, stream=st)
+    torch.cuda.synchronize()
+    for _, _, codes, amax, want in sets:
+        check(codes, amax, want)
+    Kg, codes, amax = sets[0][1].clone(), torch.empty_like(sets[0][2]), torch.empty_like(sets[0][3])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ds.ds_build_label_q4(Kg, chd, codes, amax, shp)
+    for _, K, _, _, want in sets + sets[:1]:
+        Kg.copy_(K)
+        codes.fill_(-1)
+        graph.replay()
+        torch.cuda.synchronize()
+        check(codes, amax, want)
+
+
 @pytest.mark.parametrize("B,Hkv,L,L_max,r,kv", [
     (1, 1, 1, 1, 1, False),          # one token, one channel
     (1, 1, 2, 5, 128, False),        # one pass of two rows
