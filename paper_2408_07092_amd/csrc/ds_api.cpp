@@ -95,6 +95,58 @@ static int group_wgs_per_cu(int G, int ch, int n_ch, const DeviceCaps &caps)
     return (int)std::min<size_t>(3, (size_t)caps.lds_per_cu / lds);
 }
 
+// Chunks of a decode launch that scores itself with several workgroups per unit, whose whole grid has to be
+// resident: two workgroups of 512 threads to a compute unit by registers and LDS; for groups of more than
+// eight heads, whose kernels take more registers, one, or three of 256 threads and half the tokens.  The number of chunks per unit with the least estimated time, and in how many
+// launches of a share of the units each:
+//   - the busiest compute unit's tokens, scored and their rows attended: about 53 GB/s (48 bytes a token with 8
+//     channels and a sixteenth of the rows: 0.9 us a thousand) by one workgroup, 61 by two, whose idle stretches fill each other's (128 single heads of 32K tokens 43.6 us with
+//     one, 42.8 with two; 96 of 30K, one 35.7, two 32.1; but 32 of 64K 26.9 and 28.3);
+//   - 0.25 us for each of a unit's workgroups, which meet at the same few lines of memory (one unit of 256K tokens
+//     39.7 us with 256 chunks, 28.0 with 128, 21.9 with 64; 32 units of 16K 21.7 with 2, 18.5 with 4, 17.7 with 8,
+//     20.8 with 16);
+//   - 10 us for every launch.
+// At most n_room chunks, for which the workspace has room.
+static bool choose_chunks(int units, int L, int G, double token_bytes, int cus, int n_room, int *ch, int *groups)
+{
+    const double us = std::max(0.5e-3, token_bytes * 0.01875e-3);
+    // (more than one is measured on a whole MI355X only: a part of one plans one)
+    const int per_cu = cus < 128 ? 1 : G > 8 ? 3 : 2;
+    double best = 0.0;
+    bool found = false;
+    for (int g = 1; g <= 3; ++g) {
+        const int u = (units + g - 1) / g, n_max = std::min(n_room, per_cu * cus / u);
+        const int n0 = std::max(2, (L + kDecodeTokens - 1) / kDecodeTokens);
+        for (int n = n0; n <= std::min(n_max, n0 + 64); ++n) {
+            const int c = (((L + n - 1) / n) + 63) & ~63, n_ch = (L + c - 1) / c;
+            const int on_cu = (int)(((int64_t)u * n_ch + cus - 1) / cus);
+            if (c > (G > 8 && on_cu > 1 ? kDecodeTokens / 2 : kDecodeTokens)) continue;
+            const double cost = g * (10.0 + c * us * (on_cu == 1 ? 1.0 : on_cu == 2 ? 1.73 : 2.5) + 0.25 * n_ch);
+            if (!found || cost < best) {
+                best = cost;
+                *ch = c;
+                *groups = g;
+                found = true;
+            }
+        }
+    }
+    return found;
+}
+
+// The variant of the kernel that scores itself.
+//   - 256 threads where single-workgroup units outnumber two to a compute unit: four fit at once (1024 single heads
+//     of 1000 tokens 16.8 us with 512 threads, 12.9 with 256; of 2048 22.5 and 19.8; 256 units of 1000 7.7 and 7.8);
+//   - without the streaming mark and with four rows per slot in flight instead of two where the device is mostly
+//     idle or the call moves a few MiB (one layer of 32 heads of 4K tokens 9.4 -> 9.2 us, 128 of 6000 14.5 -> 13.8;
+//     256 of 8192 22.4 -> 22.9).
+DecodeVariant decode_variant(const Plan &p, bool streams)
+{
+    const int64_t wgs = (int64_t)p.n_ch * ((p.units + p.unit_groups - 1) / p.unit_groups);
+    if (wgs > (p.G > 8 ? 1 : 2) * (int64_t)p.cus && p.ch <= kDecodeTokens / 2) return DECODE_NARROW;
+    if (!streams || (p.n_ch == 1 && (int64_t)p.units * 4 < 3 * (int64_t)p.cus)) return DECODE_LIGHT;
+    return DECODE_WIDE;
+}
+
 bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
 {
     if (!shape_ok(s, true)) return false;
@@ -135,7 +187,7 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
                         (tune_get(3) == 0 && (s.L > (1 << 13) || one_wg_units ||
                                             (purpose == PLAN_DECODE_SCORING && s.L > (1 << 12)))));
     int ch = tune_get(1), ch_room = 0;
-    p->group_scores_itself = false;
+    p->chunks_score = false;
     p->unit_groups = 1;
     if (ch == 0 && p->refine_attend && !one_wg_units && p->G > 2 && purpose == PLAN_DECODE_SCORING) {
         // Query groups: one launch that scores as well pays off when all of its workgroups are
@@ -151,7 +203,6 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
                 const int c = std::max(2048, (((s.L + n - 1) / n) + 63) & ~63);  // (no point in tiny chunks)
                 if (c <= 8192 && group_wgs_per_cu(p->G, c, (s.L + c - 1) / c, caps) >= w) {
                     ch = c;
-                    p->group_scores_itself = true;
                     p->unit_groups = g;
                 }
             }
@@ -235,10 +286,18 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
                               : p->G == 2 ? (half_full ? (wide ? 5632 : 6144) : 0)
                               : half_full ? (wide ? 6656 : 8192)
                                           : (wide ? 5376 : 6144);
+    // Units that fill the device by themselves take one as long as it can hold them, groups as single heads and
+    // pairs do above: 192 units of 9000 tokens in groups of 4 27.1 -> 23.2 us, 256 of 16000 38.1 -> 34.9, 512 of 9000 53.7 -> 36.4,
+    // 1024 of 12000 139.6 -> 87.2.
+    const bool many_groups = p->G > 2 && p->units * 4 >= caps.cus * 3 && s.L > 8192 && s.L <= kDecodeTokens;
     if (n_ws > 1 && p->refine_attend && purpose == PLAN_DECODE_SCORING && tune_get(1) == 0 &&
-        s.L <= one_wg_tokens && p->k_eff <= one_wg_tokens / 16) {
+        (many_groups || (s.L <= one_wg_tokens && p->k_eff <= one_wg_tokens / 16))) {
         ch = (s.L + 255) & ~255;
         p->unit_groups = 1;
+    } else if (n_ws > 1 && p->refine_attend && purpose == PLAN_DECODE_SCORING && tune_get(1) == 0) {
+        if (!choose_chunks(p->units, s.L, p->G, (q4 ? (s.r + 7) / 8 * 4.0 : 2.0 * s.r) + 512.0 * p->k_eff / s.L, caps.cus, n_ws, &ch, &p->unit_groups))
+            return make_plan(s, p, PLAN_DECODE, q4);  // (no launch that scores itself fits at once)
+        p->chunks_score = true;
     }
     p->ch = ch;
     p->n_ch = (s.L + ch - 1) / ch;
@@ -607,7 +666,7 @@ static ds_status_t enqueue_select(const void *q, const void *label, const int32_
     // exact threshold (knob 4 = 1 forces the separate candidate launch, 2 forces the tail).
     const int mode = tune_get(4);
     const bool tail_refine = mode == 2 || (mode == 0 && s.L <= (1 << 13));
-    DS_TRY(launch_score(q, label, channels, ws, p, s, tail_refine, want_offsets, st, src));
+    DS_TRY(launch_score(q, label, channels, ws, p, s, true, tail_refine, want_offsets, st, src));
     if (!tail_refine) DS_TRY(launch_cand(ws, p, s, want_offsets, st));
     return DS_OK;
 }
@@ -633,7 +692,7 @@ static bool plan_scores_itself(const Plan &p, bool may_score)
     return may_score && (p.n_ch == 1 || tune_get(4) == 2 ||
                          (tune_get(4) == 0 && p.G <= 2 &&
                           (int64_t)((p.units + p.unit_groups - 1) / p.unit_groups) * p.n_ch <= 4 * (int64_t)p.cus) ||
-                         (tune_get(4) == 0 && p.group_scores_itself));
+                         (tune_get(4) == 0 && p.chunks_score));
 }
 
 // ds_sparse_decode with the scores taken from the label cache, from the K rows themselves or from
@@ -678,17 +737,22 @@ static ds_status_t sparse_decode_impl(const void *q, const void *label, const vo
         // (the runtime's occupancy figure for the kernel decides whether the workgroups that wait
         //  for each other are all resident; if not, the separate scoring launch needs less room,
         //  and the three launches below need none)
-        if (scores_itself && !refine_attend_fits(p, *shape, true, q4)) scores_itself = false;
+        if (scores_itself && !refine_attend_fits(p, *shape, true, q4)) {
+            scores_itself = false;
+            Plan ps;  // (chunks for the scoring launch's sake; a knob's chunks stay)
+            if (p.chunks_score && make_plan(*shape, &ps, PLAN_DECODE, q4) && ps.total <= workspace_bytes) p = ps;
+        }
         if (scores_itself) {
-            DS_TRY(launch_refine_attend(q, K, V, workspace, out, idx_out, p, *shape, st, kv_stride, label, channels,
-                                        q4 ? src.amax : nullptr));
+            DS_TRY(launch_refine_attend(q, K, V, workspace, out, idx_out, p, *shape, st, kv_stride, channels, src.amax,
+                                        label));
             return DS_OK;
         }
         // otherwise scoring leaves keys and the threshold bin; one more launch settles the exact
         // threshold behind the attention over the rows that are selected either way
         if (refine_attend_ok(p, false) && refine_attend_fits(p, *shape, false, q4)) {
-            DS_TRY(launch_score(q, label, channels, workspace, p, *shape, false, false, st, src));
-            DS_TRY(launch_refine_attend(q, K, V, workspace, out, idx_out, p, *shape, st, kv_stride));
+            DS_TRY(launch_score(q, label, channels, workspace, p, *shape, p.n_ch > 1, false, false, st, src));
+            DS_TRY(launch_refine_attend(q, K, V, workspace, out, idx_out, p, *shape, st, kv_stride, channels, src.amax,
+                                        nullptr));
             return DS_OK;
         }
     }

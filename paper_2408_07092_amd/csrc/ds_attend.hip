@@ -18,11 +18,16 @@
 #include <tuple>
 #include <type_traits>
 
-#include "ds_attend_core.h"
-
-#define DS_PRIO(x) __builtin_amdgcn_s_setprio(x)
+#include "ds_device.h"
 
 namespace ds {
+DS_TRACE_BUFFER
+}
+
+#include "ds_decode_core.h"
+
+namespace ds {
+
 
 constexpr int kRowsPerSlot = 4;   // rows of a 16-lane slot in flight (2: -0.2 us on the 64K workload, 8: +0.5)
 // ... on the vector path of the 256-thread variants: five, i.e. rounds of 80 rows.  A chunk of the
@@ -30,34 +35,6 @@ constexpr int kRowsPerSlot = 4;   // rows of a 16-lane slot in flight (2: -0.2 u
 // third, almost empty round (31.1 -> 30.9 us/layer; batch 4 x 16K tokens 30.9 -> 30.5; six rows
 // per slot: 31.4).
 constexpr int kRowsPerSlotVector = 5;
-constexpr int kScoreDepth = 8;    // label loads of a thread in flight (4: +1.1 us; 12, 16: no gain)
-
-DS_TRACE_BUFFER
-
-struct AttendArgs {
-    const _Float16 *q, *K, *V;
-    const uint32_t *keys;
-    const UnitCtl *ctl;
-    const uint32_t *offs;
-    int32_t *idx_out;
-    float *part;
-    float *out;
-    UnitCtl *ctl_rw;
-    int Hq, Hkv, G, L, L_max, key_stride, ch, n_ch, k, k_eff, n_rows;
-    int kv_stride;       // halves from one token's K (V) row to the next: d, or 2d when K|V interleave
-    int unit0;           // k_refine_attend: first unit of this launch (a launch may take a share of the units)
-    // k_refine_attend only
-    uint2 *cand;         // [units][L] (key, token) of the keys in bin b*, unordered
-    uint32_t *ndef;      // [units][n_ch] keys above bin b* per chunk
-    uint32_t *offs_rw;   // [units][n_ch] offset of the chunk in the ascending index list
-    uint32_t spin_limit;
-    // k_refine_attend with the scoring done in the same launch (one workgroup per unit)
-    const _Float16 *label;     // [units][L_max][r]
-    const int32_t *channels;   // [Hkv][r]
-    uint32_t *hist, *coarse;   // unit histograms (4096 / 256 bins), zero between calls
-    const float *amax;         // 4-bit label cache: [units][r] largest magnitude per channel
-    int r;                     // label channels (4-bit label cache; fp16 labels have it in the kernel's type)
-};
 
 // MODE 0: rows = tokens of the chunk that pass the selection predicate
 // MODE 1: rows = all tokens of the chunk (dense)
@@ -160,12 +137,9 @@ __global__ __launch_bounds__(kWG, (GT == 1 ? 8 : 1)) void k_attend(AttendArgs a)
 }
 
 
-// ---------------------------------------------------------------- exact threshold + attention, one launch
+// ---------------------------------------------------------------- exact threshold + attention behind a scoring launch
 // Runs after k_score has left the unit's keys and the threshold bin b* (with the
-// rank krem of the k-th key inside it) -- or, with SMODE != 0, does that part itself
-// first (Algorithm 1 steps 1-2: label rows streamed, keys kept in LDS, chunk
-// histograms met in the unit's histograms in memory; see step 0 in the body), so
-// that the whole decode is this one launch.  Tokens whose key lies in a bin above b*
+// rank krem of the k-th key inside it).  Tokens whose key lies in a bin above b*
 // are selected whatever the exact threshold turns out to be, so a workgroup
 //   1. splits its chunk's keys into definite tokens, candidates (bin b*) and the rest,
 //      appends the candidates to the unit's list and arrives at the unit's counter;
@@ -176,43 +150,21 @@ __global__ __launch_bounds__(kWG, (GT == 1 ? 8 : 1)) void k_attend(AttendArgs a)
 // The workgroup whose arrival completes the unit radix-selects T from the
 // candidate list before its own step 2 and publishes (T, tie cut, ready) as one
 // 64-bit word, so the refinement hides behind the other workgroups' row traffic.
-// (A refiner workgroup of its own per unit was tried: it costs a place among the
-// resident workgroups and gains nothing measurable.)
 // Waiting: a workgroup waits only for the publishing workgroup, which is running
 // by then and never waits itself; every workgroup of the unit arrives before
 // any waits, and workgroups are dispatched in grid order, so all of a unit's
 // workgroups get to run as long as one XCD can hold its share (every eighth) of
-// the n_ch of them (checked on the host).  (With SMODE != 0 a workgroup also waits
-// for its unit's histogram to be complete, i.e. for workgroups that may not have
-// started: the host then sizes the chunks so that the whole grid is resident.)
-// Every wait is bounded as well: on expiry the unit's error word is raised and
-// the workgroup carries on with a value that keeps all accesses in range.
-//
-// The body, in order (the "----" comments mark the parts):
-//   0.  (SMODE != 0) score the chunk: label query, label rows -> keys in LDS + chunk histogram;
-//       threshold bin b*: from the workgroup's own histogram (one workgroup per unit), or the
-//       chunk histograms meet in memory and every workgroup finds b* there (vector variants) /
-//       the last to arrive finds and publishes it (matrix-core variants)
-//   1.  (SMODE == 0) keys and b* of the scoring launch are loaded instead
-//   --  classify the keys against b*: row list (definite rows from the front, candidates from the
-//       back), candidates to the unit's list in memory, arrival
-//   --  (the workgroup that completes the unit) exact threshold T and tie cut by radix select over
-//       the candidates; published
-//   2-4 definite rows in whole rounds; settle() = wait for (T, tie cut), add the selected
-//       candidates (and write the index list if asked); the remaining rows; partial
-//   --  (the unit's last workgroup) merge of the partials
-// Template: GT heads per pass (1, 2 on the vector ALUs; 4, 8, 16 on the matrix cores), SMODE see
-// 0./1., RPS rows per 16-lane slot in flight (4; 8 = the 1024-thread variant of one workgroup
-// per unit that has a CU to itself).
-template <int GT, int SMODE, int RPS = 4, bool ST = true>
-__global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : GT == 1 ? 4 : 3))) void k_refine_attend(AttendArgs a)
+// the n_ch of them (checked on the host).  Every wait is bounded as well: on expiry the unit's
+// error word is raised and the workgroup carries on with a value that keeps all accesses in range.
+// (Label caches that the attention launch can score itself take decode_unit instead, see
+// ds_decode_core.h.)
+// (It serves units of several chunks, of which a scoring launch has many: up to 200 workgroups of a unit
+//  meet less often here.  Where decode_unit takes the keys of the scoring launch with so many chunks, four
+//  units of 200K tokens scored with 40 channels take 61 -> 82 us.)
+template <int GT, bool ST>
+__global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behind_scoring(AttendArgs a)
 {
-    // Workgroup size: 256 threads; 1024 (four wavefronts per SIMD, 128 registers each: RPS = 8)
-    // for the variant that has a CU to itself (RPS > 4: one workgroup per unit, launched with
-    // gridDim.x == 1 only), where a single wavefront per SIMD would leave every instruction's
-    // latency exposed (C2: 256 threads 56.9, 512 threads 55.7, 1024 threads 55.1 us/layer).
-    constexpr int NW = RPS > 4 ? 16 : 4;
-    constexpr int WGT = 64 * NW;
+    constexpr int NW = 4, WGT = 64 * NW;
     extern __shared__ __attribute__((aligned(16))) uint32_t dyn_sh[];  // ch keys | ch 16-bit row list | n_ch counters
     uint32_t *keys_sh = dyn_sh;
     uint16_t *sel = reinterpret_cast<uint16_t *>(dyn_sh + a.ch);
@@ -224,12 +176,7 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     // 4 KiB serve the radix bins of the refinement, later the merge of the unit's partials; the
     // workgroup's own wavefront partials lie between the two in time and share the space when
     // they are at least that large
-    // On the matrix-core variants, where LDS limits the workgroups per CU, the chunk histogram of
-    // the launch that scores as well lives there too (it is dead before any of the above), with
-    // the array padded to its 16 KiB where four heads make it smaller.
-    constexpr bool kAliasHist = SMODE != 0 && GT >= 4;
-    constexpr int kWpartRows = (kAliasHist && 4 * GT * kPartStride < kHistBins) ? 8 : NW;
-    __shared__ __attribute__((aligned(16))) float wpart[kWpartRows][GT][kPartStride];
+    __shared__ __attribute__((aligned(16))) float wpart[NW][GT][kPartStride];
     __shared__ __attribute__((aligned(16))) float red_own[GT >= 2 ? 1 : 8][kD];
     float(*red)[kD] = GT >= 2 ? reinterpret_cast<float(*)[kD]>(&wpart[0][0][0]) : red_own;
     uint32_t *lh = reinterpret_cast<uint32_t *>(&red[0][0]);  // 1024 radix bins
@@ -261,339 +208,33 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
         float *ou = a.out + (size_t)u * a.G * kD;
         for (int i = tid; i < a.G * kD; i += WGT) ou[i] = __builtin_nanf("");
     };
-    // (the word is asked for here and looked at after the chunk has been scored, before the first
-    //  thing that another workgroup could see: the load is off the path)
-    const uint32_t sticky = a.ctl[u].err;
-    auto refuse_if_poisoned = [&]() {
-        if (sticky != 0u && c == 0) poison_out();
-        return sticky != 0u;
-    };
     if (tid == 0) s_failed = 0u;
-    if constexpr (SMODE == 0) {
-        if (refuse_if_poisoned()) return;
+    if (a.ctl[u].err != 0u) {
+        if (c == 0) poison_out();
+        return;
     }
 
-    // the group's query rows (up to eight at a time), loaded for the label query; single heads and
-    // pairs attend with them too, so that no load of q sits between the lists and the rows
-    __shared__ __attribute__((aligned(16))) _Float16 qrow_sh[SMODE != 0 ? 8 : 1][kD];
-    if constexpr (SMODE == 0 && GT <= 2) {
+    if constexpr (GT <= 2) {
         if (tid < GT * 16) {
             const int g = tid >> 4, p = tid & 15;
             const _Float16 *q0 = a.q + ((size_t)b * a.Hq + (size_t)h * a.G) * kD;
             *reinterpret_cast<uint4 *>(&qsh[g][p * 8]) = *reinterpret_cast<const uint4 *>(q0 + (size_t)g * kD + p * 8);
         }
     }
-    uint32_t bstar = kHistBins - 1, krem_unit = 1;
-    if constexpr (SMODE != 0) {
-        // ---- 0. Algorithm 1 steps 1-2 right here: stream the chunk's label rows, keys go to LDS
-        // only; with one workgroup per unit the threshold bin comes out of its own histogram.
-        // Same arithmetic and order as k_score.  SMODE = r for fp16 labels (a multiple of 4, up to 32); SMODE = -8 /
-        // -16 for the 4-bit label cache of up to 8 / 16 channels (one / two words per token).
-        constexpr bool kQ4 = SMODE < 0;
-        constexpr int RR = kQ4 ? -SMODE : SMODE;
-        __shared__ uint32_t hist_own[kAliasHist ? 1 : kHistBins];
-        auto hist_at = [&](int i) -> uint32_t & {
-            if constexpr (kAliasHist) return reinterpret_cast<uint32_t *>(&wpart[0][0][0])[i];
-            else return hist_own[i];
-        };
-        __shared__ float qs_sh[RR];
-        if constexpr (kQ4) {
-            // label query of the group times the step of each channel (amax / 7); zero beyond r
-            int c_q = 0;
-            if (tid < a.r) c_q = a.channels[h * a.r + tid];
-            float a_q = 0.0f;
-            for (int g0 = 0; g0 < a.G; g0 += 8) {
-                const int ng = min(8, a.G - g0);
-                if (g0) __syncthreads();
-                if (tid >= 128 && tid - 128 < ng * 16) {
-                    const int g = (tid - 128) >> 4, pp = (tid - 128) & 15;
-                    const _Float16 *src = a.q + ((size_t)b * a.Hq + (size_t)h * a.G + g0 + g) * kD + pp * 8;
-                    *reinterpret_cast<uint4 *>(&qrow_sh[g][pp * 8]) = *reinterpret_cast<const uint4 *>(src);
-                }
-                if (g0 == 0)
-                    for (int i = tid; i < kHistBins; i += WGT) hist_at(i) = 0u;
-                __syncthreads();
-                if (tid < a.r)
-                    for (int g = 0; g < ng; ++g) a_q = a_q + (float)qrow_sh[g][c_q];
-            }
-            if (tid < RR) qs_sh[tid] = tid < a.r ? a_q * (a.amax[(size_t)u * a.r + tid] / 7.0f) : 0.0f;
-            __syncthreads();
-            float wr[RR];
+    // ---- 1. the chunk's keys come from the scoring launch, with the unit's threshold bin;
+    // all of the thread's key loads are in flight together; the keys then live in LDS
+    const uint32_t bstar = ctl->bstar, krem_unit = ctl->krem;
+    uint4 kv[kMaxPass];
 #pragma unroll
-            for (int j = 0; j < RR; ++j) wr[j] = qs_sh[j];
-            // 16-byte loads of four (two) tokens, four loads per thread in flight
-            constexpr int WW = RR / 8, TPL = 4 / WW;
-            const uint32_t *codes = reinterpret_cast<const uint32_t *>(a.label) + (size_t)u * a.L_max * WW;
-            auto nib = [](uint32_t word, int i) { return (float)(((int32_t)(word << (28 - 4 * i))) >> 28); };
-            const int t_lastq = (t1 - 1) & ~(TPL - 1);
-            for (int tb = t0 + tid * TPL; tb < t1; tb += WGT * TPL * 4) {
-                uint4 cv[4];
+    for (int p = 0; p < kMaxPass; ++p) {
+        const int t = t0 + (p * WGT + tid) * 4;
+        kv[p] = make_uint4(0u, 0u, 0u, 0u);
+        if (p < n_pass && t < t1) kv[p] = *reinterpret_cast<const uint4 *>(ku + t);
+    }
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    cv[i] = stream_load<ST>(reinterpret_cast<const uint4 *>(codes + (size_t)min(tb + i * WGT * TPL, t_lastq) * WW));
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t c4[4] = {cv[i].x, cv[i].y, cv[i].z, cv[i].w};
-#pragma unroll
-                    for (int e = 0; e < TPL; ++e) {
-                        const int t = tb + i * WGT * TPL + e;
-                        float acc = 0.0f;
-#pragma unroll
-                        for (int w = 0; w < WW; ++w)
-#pragma unroll
-                            for (int j = 0; j < 8; ++j)
-                                acc = __builtin_fmaf(wr[w * 8 + j], nib(c4[e * WW + w], j), acc);
-                        if (t < t1) {
-                            const uint32_t key = score_key(acc);
-                            keys_sh[t - t0] = key;
-                            atomicAdd(&hist_at(key >> kKeyShift), 1u);
-                        }
-                    }
-                }
-            }
-        }
-        if constexpr (!kQ4) {
-        const _Float16 *lab = a.label + (size_t)u * a.L_max * SMODE;
-        // A token's label row is NV pieces: of eight channels, or of four when eight do not divide it.
-        // (more than 16 channels: half as many rows in flight)
-        constexpr int PE = RR % 8 ? 4 : 8;
-        constexpr int NV = RR / PE;
-        using Piece = typename std::conditional<PE == 8, half8, half4>::type;
-        constexpr bool kPairs = RR == 16;
-        constexpr int SD = RR > 16 ? kScoreDepth / 2 : ST ? kScoreDepth : 2 * kScoreDepth;  // (a mostly idle device: fewer round trips)
-        Piece v[SD][NV];
-        // (rows past the end of the chunk re-read its last row; their scores are dropped)
-        // Rows of two 16-byte pieces (16 channels): a wavefront's two loads take 64 consecutive
-        // pieces each -- whole cache lines, so they can carry the streaming mark --, which leaves
-        // every lane with the same half of two tokens; neighbouring lanes then swap one piece, and
-        // the even lane holds token l/2 of the wavefront's 64, the odd lane token 32 + l/2, whole.
-        // (One token per lane straight away means every load takes every other 16 bytes of its
-        //  lines: measured 2 us per layer slower on the batch-8 workload.)
-        const int lane_ = tid & 63;
-        auto token_of = [&](int tb, int i) {
-            if constexpr (kPairs) return tb - lane_ + i * WGT + (lane_ >> 1) + ((lane_ & 1) ? 32 : 0);
-            else return tb + i * WGT;
-        };
-        auto issue = [&](int tb) {
-#pragma unroll
-            for (int i = 0; i < SD; ++i) {
-                if constexpr (kPairs) {
-                    const int p0 = 2 * (tb - lane_ + i * WGT) + lane_, p_last = 2 * t1 - 1;
-                    const half8 *pieces = reinterpret_cast<const half8 *>(lab);
-                    v[i][0] = label_load<1, ST>(pieces + min(p0, p_last));
-                    v[i][1] = label_load<1, ST>(pieces + min(p0 + 64, p_last));
-                } else {
-                    const Piece *row = reinterpret_cast<const Piece *>(lab + (size_t)min(tb + i * WGT, t1 - 1) * SMODE);
-#pragma unroll
-                    for (int j = 0; j < NV; ++j) v[i][j] = label_load<NV, ST>(row + j);
-                }
-            }
-        };
-        // (kPairs) the lane's two pieces -> its token's two halves
-        auto own_row = [&](Piece (&r)[NV]) {
-            if constexpr (kPairs) {
-                const bool odd = lane_ & 1;
-                const half8 got = swap_pairs(odd ? r[0] : r[1]);
-                if (odd) r[0] = got;
-                else r[1] = got;
-            }
-        };
-        int c_q = 0;
-        if (tid < SMODE) c_q = a.channels[h * SMODE + tid];
-        float a_q = 0.0f;
-        for (int g0 = 0; g0 < a.G; g0 += 8) {
-            const int ng = min(8, a.G - g0);
-            if (g0) __syncthreads();
-            if (tid >= 128 && tid - 128 < ng * 16) {
-                const int g = (tid - 128) >> 4, pp = (tid - 128) & 15;
-                const _Float16 *src = a.q + ((size_t)b * a.Hq + (size_t)h * a.G + g0 + g) * kD + pp * 8;
-                *reinterpret_cast<uint4 *>(&qrow_sh[g][pp * 8]) = *reinterpret_cast<const uint4 *>(src);
-            }
-            if (g0 == 0) {
-                issue(t0 + tid);
-                __builtin_amdgcn_sched_barrier(0);
-                for (int i = tid; i < kHistBins; i += WGT) hist_at(i) = 0u;
-            }
-            __syncthreads();
-            if (tid < SMODE)
-                for (int g = 0; g < ng; ++g) a_q = a_q + (float)qrow_sh[g][c_q];
-        }
-        if (tid < SMODE) qs_sh[tid] = a_q;
-        __syncthreads();
-        float qs[SMODE];
-#pragma unroll
-        for (int j = 0; j < SMODE; ++j) qs[j] = qs_sh[j];
-        // (kPairs: a lane's token is not the one of its place, so a wavefront stays together)
-        auto more = [&](int tb) { return (kPairs ? tb - lane_ : tb) < t1; };
-        for (int tb = t0 + tid; more(tb);) {
-#pragma unroll
-            for (int i = 0; i < SD; ++i) {
-                own_row(v[i]);
-                float acc = 0.0f;
-#pragma unroll
-                for (int j = 0; j < NV; ++j)
-#pragma unroll
-                    for (int e = 0; e < PE; ++e) acc = __builtin_fmaf(qs[j * PE + e], (float)v[i][j][e], acc);
-                const int t = token_of(tb, i);
-                if (t < t1) {
-                    const uint32_t key = score_key(acc);
-                    keys_sh[t - t0] = key;
-                    atomicAdd(&hist_at(key >> kKeyShift), 1u);
-                }
-            }
-            tb += WGT * SD;
-            if (more(tb)) issue(tb);
-        }
-        }  // fp16 labels
-        DS_PRIO(3);
-        if (refuse_if_poisoned()) return;
-        __syncthreads();
-        DS_TR(11);
-        if (gridDim.x == 1) {
-            hist_select<kHistBins / WGT, true, NW>([&](int bin) { return hist_at(bin); }, (uint32_t)a.k_eff, s_w, s_res);
-            bstar = s_res[0];
-            krem_unit = s_res[1];
-            __syncthreads();
-        } else if constexpr (NW == 4) {
-            {
-                // Several workgroups per unit: the chunk histograms meet in the unit's histograms in
-                // memory (as in k_score).  Every workgroup then waits until all of the unit's have
-                // arrived and finds the threshold bin itself, with one round of loads: the 256 coarse
-                // bins, and with them the fine bins of the three coarse bins around the one that its
-                // own histogram points to (another round only if the unit's lies elsewhere).  Nobody
-                // has to publish anything; the histograms are cleared at the launch's end, by the
-                // workgroup that merges the unit, when every workgroup has long read them.  (The last
-                // to arrive finding the bin and publishing it measured the same or slower.)
-                uint32_t *hu = a.hist + (size_t)u * kHistBins;
-                uint32_t *cuh = a.coarse + (size_t)u * 256;
-                {
-                    uint32_t cbin[kHistBins / WGT], cc = 0;
-    #pragma unroll
-                    for (int i = 0; i < kHistBins / WGT; ++i) {
-                        cbin[i] = hist_at(tid + i * WGT);
-                        cc += hist_at(tid * 16 + ((i + tid) & 15));  // (an order of its own per lane: see hist_select)
-                    }
-    #pragma unroll
-                    for (int i = 0; i < kHistBins / WGT; ++i)
-                        if (cbin[i]) atomicAdd(&hu[tid + i * WGT], cbin[i]);
-                    if (cc) atomicAdd(&cuh[tid], cc);
-                }
-                // (No wait for the adds to be performed before the arrival: an arrival that overtakes
-                //  its workgroup's adds is caught by the reader, who checks that the coarse counts add
-                //  up to L and the fine counts of the unit's coarse bin to its count, and looks again
-                //  if they do not.  One round trip less on every workgroup's path.)
-                __syncthreads();
-                uint32_t seen = 0;
-                if (tid == 0)
-                    seen = __hip_atomic_fetch_add(&ctl->arrive_a, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u;
-                // (while the arrival is under way) the coarse bin holding the chunk's share of k
-                uint32_t cb0;
-                {
-                    const uint32_t n_tok = (uint32_t)(t1 - t0);
-                    uint32_t k_loc = (uint32_t)(((unsigned long long)a.k_eff * n_tok + (uint32_t)a.L - 1u) / (uint32_t)a.L);
-                    k_loc = min(max(k_loc, 1u), n_tok);
-                    hist_select<kHistBins / WGT, true, NW>([&](int bin) { return hist_at(bin); }, k_loc, s_w, s_res);
-                    cb0 = min(max(s_res[0] >> 4, 1u) - 1u, 253u);  // fine bins of coarse bins cb0 .. cb0 + 2
-                }
-                if (tid == 0) {
-                    const uint32_t n_wg = gridDim.x;
-                    uint32_t ok = 1u;
-                    if (seen != n_wg) {
-                        ok = 0u;
-                        for (uint32_t it = 0; it < a.spin_limit; ++it) {
-                            if (ld_dev(&ctl->arrive_a) == n_wg) { ok = 1u; break; }
-                            __builtin_amdgcn_s_sleep(1);
-                        }
-                    }
-                    s_ok = ok;
-                    if (!ok) raise_err(9u);
-                }
-                __syncthreads();
-                DS_TR(12);
-                if (s_ok) {
-                    __shared__ uint32_t s_fine[16], s_cbn, s_valid;
-                    for (uint32_t attempt = 0;; ++attempt) {
-                        uint32_t fv = 0;
-                        if (tid < 48) fv = ld_dev(hu + cb0 * 16 + tid);
-                        const uint32_t myc = ld_dev(cuh + 255 - tid);  // (thread = coarse bin, from the top)
-                        if (tid == 0) {
-                            s_res[0] = 0u;
-                            s_res[1] = 1u;
-                            s_cbn = 0xffffffffu;
-                        }
-                        uint32_t tot;
-                        const uint32_t above = block_exclusive_scan<NW>(myc, s_w, &tot);
-                        if (above < (uint32_t)a.k_eff && above + myc >= (uint32_t)a.k_eff) {
-                            s_res[0] = 255u - (uint32_t)tid;
-                            s_res[1] = (uint32_t)a.k_eff - above;
-                            s_cbn = myc;
-                        }
-                        __syncthreads();
-                        const uint32_t cb = s_res[0], rank = s_res[1];
-                        if (cb - cb0 < 3u) {
-                            if (tid < 48 && (uint32_t)(tid >> 4) == cb - cb0) s_fine[15 - (tid & 15)] = fv;
-                        } else if (tid < 16) {
-                            s_fine[tid] = ld_dev(hu + cb * 16 + 15 - tid);
-                        }
-                        __syncthreads();
-                        if (tid == 0) {
-                            // (s_fine runs from the coarse bin's top fine bin down)
-                            uint32_t fsum = 0;
-                            for (int i = 0; i < 16; ++i) fsum += s_fine[i];
-                            const bool valid = tot == (uint32_t)a.L && fsum == s_cbn;
-                            uint32_t before = 0, bin = cb * 16, krem = 1;
-                            for (int i = 0; i < 16; ++i) {
-                                if (before + s_fine[i] >= rank) {
-                                    bin = cb * 16 + 15 - i;
-                                    krem = rank - before;
-                                    break;
-                                }
-                                before += s_fine[i];
-                            }
-                            s_T[0] = bin;
-                            s_T[1] = krem;
-                            s_valid = valid ? 1u : 0u;
-                            // (counts that never add up: a workspace that was not cleared, or adds that
-                            //  do not arrive)
-                            if (!valid && attempt + 1u >= a.spin_limit) {
-                                raise_err(9u);
-                                s_T[0] = (uint32_t)(kHistBins - 1);
-                                s_T[1] = 1u;
-                                s_valid = 2u;
-                            }
-                        }
-                        __syncthreads();
-                        if (s_valid) break;
-                        __builtin_amdgcn_s_sleep(8);
-                    }
-                } else if (tid == 0) {
-                    s_T[0] = (uint32_t)(kHistBins - 1);
-                    s_T[1] = 1u;
-                }
-            }
-            __syncthreads();
-            bstar = s_T[0];
-            krem_unit = s_T[1];
-            __syncthreads();
-        }
-        DS_TR(10);
-    } else {
-        // ---- 1. the chunk's keys come from the scoring launch, with the unit's threshold bin;
-        // all of the thread's key loads are in flight together; the keys then live in LDS
-        bstar = ctl->bstar;
-        krem_unit = ctl->krem;
-        uint4 kv[kMaxPass];
-#pragma unroll
-        for (int p = 0; p < kMaxPass; ++p) {
-            const int t = t0 + (p * WGT + tid) * 4;
-            kv[p] = make_uint4(0u, 0u, 0u, 0u);
-            if (p < n_pass && t < t1) kv[p] = *reinterpret_cast<const uint4 *>(ku + t);
-        }
-#pragma unroll
-        for (int p = 0; p < kMaxPass; ++p) {
-            const int lt = (p * WGT + tid) * 4;
-            if (p < n_pass && t0 + lt < t1) *reinterpret_cast<uint4 *>(keys_sh + lt) = kv[p];
-        }
+    for (int p = 0; p < kMaxPass; ++p) {
+        const int lt = (p * WGT + tid) * 4;
+        if (p < n_pass && t0 + lt < t1) *reinterpret_cast<uint4 *>(keys_sh + lt) = kv[p];
     }
     // ---- classify the chunk's keys against bin b*
     const uint32_t lo_key = bstar << kKeyShift;
@@ -609,10 +250,6 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     int n_def = 0;
     uint32_t n_cand = 0;
     uint32_t early_base = 0;  // (thread 0, several workgroups per unit, lists made by the single scan)
-    // A workgroup that owns a CU (RPS > 4) has nobody else to hide its list work behind, so
-    // instructions count: it keeps the candidates' masks until the exact threshold is in (any fixed
-    // order of the row list will do; only the index list has to be in token order).
-    constexpr bool kAllKeys = RPS > 4;
     // Each thread owns n_pass groups of four consecutive keys (group p of thread t: keys
     // 4 (p WGT + t) ..: a wavefront's loads then cover the LDS banks evenly).  One look at each key:
     // which of the thread's keys are definite and which are candidates goes into bit masks, and the
@@ -620,7 +257,7 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     // this place in the chunk:
     auto key_slot = [&](int j) { return ((j >> 2) * WGT + tid) * 4 + (j & 3); };
     uint32_t mdef[2] = {0u, 0u}, mcan[2] = {0u, 0u};
-    if constexpr (SMODE == 0 || kAllKeys) __syncthreads();  // the keys were stored by other threads
+    __syncthreads();  // the keys were stored by other threads
     {
         // Two groups are read at a time, whatever lies past the chunk's end among them, and the
         // masks cut to the chunk afterwards: no bounds in the loop, 32-bit masks at fixed places.
@@ -664,38 +301,31 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
         const uint32_t ex = block_exclusive_scan<NW>(packed, s_w, &total);
         DS_TR(13);
         // the chunk's place in the unit's candidate list is fetched while the lists are written
-        if (!kAllKeys && gridDim.x != 1 && tid == 0 && (total >> 16))
+        if (gridDim.x != 1 && tid == 0 && (total >> 16))
             early_base = (uint32_t)__hip_atomic_fetch_add(cand_arrive, (unsigned long long)(total >> 16), __ATOMIC_RELAXED,
                                                           __HIP_MEMORY_SCOPE_AGENT);
         n_def = (int)(total & 0xffffu);
         n_cand = total >> 16;
-        // the definite rows from the front of the list, the candidates behind them, or (kAllKeys)
-        // from its back; both in the thread's key order
+        // the definite rows from the front of the list, the candidates behind them; both in the
+        // thread's key order
         int dpos = (int)(ex & 0xffffu);
-        int cp = kAllKeys ? a.ch - 1 - (int)(ex >> 16) : n_def + (int)(ex >> 16);
+        int cp = n_def + (int)(ex >> 16);
 #pragma unroll
         for (int w = 0; w < 2; ++w) {
             for (uint32_t m = mdef[w]; m; m &= m - 1u) sel[dpos++] = (uint16_t)key_slot(w * 32 + __builtin_ctz(m));
             for (uint32_t m = mcan[w]; m; m &= m - 1u) {
-                sel[cp] = (uint16_t)key_slot(w * 32 + __builtin_ctz(m));
-                cp += kAllKeys ? -1 : 1;
+                sel[cp++] = (uint16_t)key_slot(w * 32 + __builtin_ctz(m));
             }
         }
     }
-    // where the chunk's i-th candidate waits in the row list: behind the definite rows, or (the
-    // variant that looks at each key once) at the list's end, filled from the back
-    auto cand_slot = [&](uint32_t i) { return kAllKeys ? a.ch - 1 - (int)i : n_def + (int)i; };
+    // where the chunk's i-th candidate waits in the row list: behind the definite rows
+    auto cand_slot = [&](uint32_t i) { return n_def + (int)i; };
     // A unit with this one workgroup keeps everything in LDS: no candidate list in memory, no
     // arrival, nothing to publish.
     const bool single = gridDim.x == 1;
     if (!single && tid == 0) {
         // candidate count of the unit (low word) and arrivals (high word) share one 64-bit counter
-        if constexpr (kAllKeys)
-            s_base = n_cand ? (uint32_t)__hip_atomic_fetch_add(cand_arrive, (unsigned long long)n_cand, __ATOMIC_RELAXED,
-                                                              __HIP_MEMORY_SCOPE_AGENT)
-                            : 0u;
-        else
-            s_base = early_base;
+        s_base = early_base;
         if (a.idx_out) st_dev(a.ndef + (size_t)u * a.n_ch + c, (uint32_t)n_def);
     }
     __syncthreads();
@@ -893,7 +523,7 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     // that at most one round of the workgroup runs partly empty.
     // (the variants for calls that move little data run on a mostly idle device, where a round
     //  trip is all that a round of rows costs: eight rows per slot in flight there)
-    constexpr int kRowsInFlight = !ST ? 8 : (RPS > 4 || GT > 2) ? RPS : kRowsPerSlotVector;
+    constexpr int kRowsInFlight = !ST ? 8 : GT > 2 ? kRowsPerSlot : kRowsPerSlotVector;
     constexpr int kRound = (GT >= 4) ? 64 : 4 * NW * kRowsInFlight;
     const int n_first = (n_def / kRound) * kRound;
     auto row_def = [&](int ri) { return t0 + (int)sel[ri]; };
@@ -927,41 +557,22 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
         int all_base = 0;
         // the row list in thread-major order (any fixed order will do); an index list, if wanted,
         // is written in token order by the pass loop further down
-        if constexpr (kAllKeys) {
-            uint32_t msel[2] = {0u, 0u};
-#pragma unroll
-            for (int w = 0; w < 2; ++w)
-                for (uint32_t m = mcan[w]; m; m &= m - 1u) {
-                    const int bit = __builtin_ctz(m);
-                    const int lt = key_slot(w * 32 + bit);
-                    if (is_selected(keys_sh[lt], t0 + lt, T, tcut)) msel[w] |= 1u << bit;
-                }
-            uint32_t total;
-            int cp = n_def + (int)block_exclusive_scan<NW>((uint32_t)(__builtin_popcount(msel[0]) + __builtin_popcount(msel[1])),
-                                                       s_w, &total);
-#pragma unroll
-            for (int w = 0; w < 2; ++w)
-                for (uint32_t m = msel[w]; m; m &= m - 1u) sel[cp++] = (uint16_t)key_slot(w * 32 + __builtin_ctz(m));
-            n_sel = (int)total;
-        }
         // The chunk's candidates -- already listed, behind the definite rows -- are all there is to
         // look at for the row list: one scan per 256 of them.  The selected ones close up to the
         // definite rows in place (a batch is read before it is written, and what it writes never
         // reaches the next batch).
-        if constexpr (!kAllKeys) {
-            for (uint32_t c0 = 0; c0 < n_cand; c0 += WGT) {
-                const uint32_t i = c0 + tid;
-                int lt = 0;
-                bool hit = false;
-                if (i < n_cand) {
-                    lt = sel[cand_slot(i)];
-                    hit = is_selected(keys_sh[lt], t0 + lt, T, tcut);
-                }
-                uint32_t total;
-                const uint32_t ex = block_exclusive_scan<NW>(hit ? 1u : 0u, s_w, &total);
-                if (hit) sel[n_def + n_sel + (int)ex] = (uint16_t)lt;
-                n_sel += (int)total;
+        for (uint32_t c0 = 0; c0 < n_cand; c0 += WGT) {
+            const uint32_t i = c0 + tid;
+            int lt = 0;
+            bool hit = false;
+            if (i < n_cand) {
+                lt = sel[cand_slot(i)];
+                hit = is_selected(keys_sh[lt], t0 + lt, T, tcut);
             }
+            uint32_t total;
+            const uint32_t ex = block_exclusive_scan<NW>(hit ? 1u : 0u, s_w, &total);
+            if (hit) sel[n_def + n_sel + (int)ex] = (uint16_t)lt;
+            n_sel += (int)total;
         }
         // the chunk's slice of the index list, in token order: one scan per 1024 keys
         for (int p = 0; p < (io ? n_pass : 0); ++p) {
@@ -1016,15 +627,14 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
             wg_store_partial_mfma<GT>(st, wpart, n_heads, po, (size_t)a.n_ch * kPartStride, od);
         } else {
             // (the query rows have been in LDS since the kernel's first steps, barriers passed)
-            const _Float16(*qrows)[kD] = SMODE != 0 ? qrow_sh : qsh;
             RowState<GT> st;
             st.init();
             DS_PRIO(0);
-            attend_rows<GT, kRowsInFlight, NW, ST>(Ku, Vu, row_bytes, n_first, row_def, qrows, st);
+            attend_rows<GT, kRowsInFlight, ST>(Ku, Vu, row_bytes, n_first, row_def, qsh, st);
             DS_PRIO(3);
             if (g0 == 0) { DS_TR(3); settle(); }
             DS_PRIO(2);
-            attend_rows<GT, kRowsInFlight, NW, ST>(Ku, Vu, row_bytes, n_def - n_first + n_sel, row_rest, qrows, st);
+            attend_rows<GT, kRowsInFlight, ST>(Ku, Vu, row_bytes, n_def - n_first + n_sel, row_rest, qsh, st);
             DS_PRIO(3);
             DS_TR(5);
             wg_store_partial<GT, NW>(st, wpart, po, (size_t)a.n_ch * kPartStride, od);
@@ -1057,19 +667,11 @@ __global__ __launch_bounds__((RPS > 4 ? 1024 : 256), (RPS > 4 ? 1 : (!ST ? 2 : G
     }
     if (!unit_ok) {
         poison_out();
-    } else if constexpr (NW == 4) {  // (written for 256 threads; the wider variant never gets here)
+    } else {
         merge_partials<8>(a.part + (size_t)u * a.G * a.n_ch * kPartStride, a.G, a.n_ch,
                        a.out + (size_t)u * a.G * kD, red, red_ml, [](int, bool) {});
     }
     DS_TR(7);
-    if constexpr (SMODE != 0 && NW == 4) {
-        // every workgroup of the unit has long read the unit's histograms and passed their arrival
-        // counter: clean for the next call (off everybody's path but the launch's very end)
-        uint4 *hu = reinterpret_cast<uint4 *>(a.hist + (size_t)u * kHistBins);
-        for (int i = tid; i < kHistBins / 4; i += WGT) hu[i] = make_uint4(0u, 0u, 0u, 0u);
-        a.coarse[(size_t)u * 256 + tid] = 0u;
-        if (tid == 0) ctl->arrive_a = 0u;
-    }
 }
 
 // ---------------------------------------------------------------- launchers
@@ -1120,40 +722,19 @@ hipError_t launch_attend_sparse(const void *q, const void *K, const void *V, voi
     return hipGetLastError();
 }
 
-// Whether k_refine_attend can take this plan's chunks: keys loaded from memory come in at most
-// eight passes of 1024; a workgroup that scores its unit itself writes them to LDS directly
-// (16-bit row offsets: up to 16384 tokens).
+// Whether the attention launch can take this plan's chunks: a workgroup keeps its chunk's keys in registers, or
+// (several chunks per unit behind a scoring launch) loads them in at most eight passes of 1024.
 bool refine_attend_ok(const Plan &p, bool scores_itself)
 {
-    return p.ch <= (scores_itself ? 16384 : 8192) && (p.ch & 3) == 0;
+    return p.ch <= (scores_itself || p.n_ch == 1 ? kDecodeTokens : 8192) && (p.ch & 3) == 0;
 }
 
 // ---- the instantiation that serves a launch, by function pointer
-using RaFn = void (*)(AttendArgs);
 struct RaKernel {
     RaFn fn;
     int threads;
+    size_t shmem;
 };
-
-// smode: 0 = keys and threshold bin come from the scoring launch; 4 .. 32 = fp16 labels of that
-// many channels scored here; -8 / -16 = 4-bit labels of up to that many channels scored here.
-template <int GT, int RPS, bool ST = true>
-static RaFn ra_fn(int smode)
-{
-    switch (smode) {
-    case 0: return RPS > 4 ? nullptr : static_cast<RaFn>(k_refine_attend<GT, 0, 4, ST>);
-    case 4: return k_refine_attend<GT, 4, RPS, ST>;
-    case 8: return k_refine_attend<GT, 8, RPS, ST>;
-    case 12: return k_refine_attend<GT, 12, RPS, ST>;
-    case 16: return k_refine_attend<GT, 16, RPS, ST>;
-    case 20: return k_refine_attend<GT, 20, RPS, ST>;
-    case 24: return k_refine_attend<GT, 24, RPS, ST>;
-    case 28: return k_refine_attend<GT, 28, RPS, ST>;
-    case 32: return k_refine_attend<GT, 32, RPS, ST>;
-    case -8: return k_refine_attend<GT, -8, RPS, ST>;
-    default: return k_refine_attend<GT, -16, RPS, ST>;
-    }
-}
 
 // Whether a sparse decode call marks its loads of label and K/V rows as streaming: when it moves
 // 16 MiB or more (the headline shape moves 96 MiB).  A call of a few MiB that finds its rows in the
@@ -1164,27 +745,39 @@ static bool streams_past_caches(const Plan &p, const ds_shape_t &s)
     return (size_t)p.units * per_unit >= ((size_t)16 << 20);
 }
 
-static size_t ra_shmem(const Plan &p) { return (size_t)p.ch * 4 + (size_t)p.ch * 2 + (size_t)p.n_ch * 4; }
+#ifdef DS_TRACE
+static int g_last_decode = 0;
+#endif
 
+static RaFn decode_kernel(int gt, int smode, DecodeVariant v)
+{
+    switch (gt) {
+    case 16: return decode_fn<16>(smode, v);
+    case 8: return decode_fn<8>(smode, v);
+    case 4: return decode_fn<4>(smode, v);
+    case 2: return decode_fn<2>(smode, v);
+    default: return decode_fn<1>(smode, v);
+    }
+}
+
+// smode: 0 = keys and threshold bin come from the scoring launch; 4 .. 32 = fp16 labels of that
+// many channels scored here; -8 / -16 = 4-bit labels of up to that many channels scored here.
 static RaKernel ra_kernel(const Plan &p, const ds_shape_t &s, int smode)
 {
     const int gt = pick_gt(p.G);
-    // one workgroup per unit that has a CU to itself: 1024 threads, eight rows per slot in flight.
-    // More than 64 KiB of LDS let no second one in; with less, units of more than 6K tokens that
-    // leave a quarter of the CUs without one (128 units of 8K tokens 23.1 -> 21.6 us against 256
-    // threads; 192 units 24.0 -> 24.1, 256 units 26.4 -> 27.0, 32 units of 6K 15.8 -> 17.6).
-    const bool own_cu = smode && gt == 1 && p.n_ch == 1 &&
-                        (ra_shmem(p) > (64u << 10) || (p.ch > 6144 && p.units * 4 < p.cus * 3));
-    if (gt <= 2 && !streams_past_caches(p, s) && !own_cu)
-        return {gt == 2 ? ra_fn<2, kRowsPerSlot, false>(smode) : ra_fn<1, kRowsPerSlot, false>(smode), 256};
-    if (own_cu) return {ra_fn<1, 8>(smode), 1024};
-    switch (gt) {
-    case 16: return {ra_fn<16, kRowsPerSlot>(smode), 256};
-    case 8: return {ra_fn<8, kRowsPerSlot>(smode), 256};
-    case 4: return {ra_fn<4, kRowsPerSlot>(smode), 256};
-    case 2: return {ra_fn<2, kRowsPerSlot>(smode), 256};
-    default: return {ra_fn<1, kRowsPerSlot>(smode), 256};
+    const bool st = streams_past_caches(p, s);
+    if (smode == 0 && p.n_ch > 1) {
+        const size_t shmem = (size_t)p.ch * 6 + (size_t)p.n_ch * 4;
+        switch (gt) {
+        case 16: return {k_attend_behind_scoring<16, true>, kWG, shmem};
+        case 8: return {k_attend_behind_scoring<8, true>, kWG, shmem};
+        case 4: return {k_attend_behind_scoring<4, true>, kWG, shmem};
+        case 2: return {st ? k_attend_behind_scoring<2, true> : k_attend_behind_scoring<2, false>, kWG, shmem};
+        default: return {st ? k_attend_behind_scoring<1, true> : k_attend_behind_scoring<1, false>, kWG, shmem};
+        }
     }
+    const DecodeVariant v = decode_variant(p, st);
+    return {decode_kernel(gt, smode, v), v == DECODE_NARROW ? 256 : 512, ((size_t)p.ch * 2 + 15) & ~(size_t)15};
 }
 
 // 0 when the labels cannot be scored in the attention launch
@@ -1198,8 +791,9 @@ static int ra_smode(const ds_shape_t &s, bool scores_itself, bool q4)
 // What the runtime says of a kernel, asked once per (kernel, dynamic LDS): more than 64 KiB of
 // dynamic LDS has to be granted first (all that the compute unit has beyond the kernel's static
 // arrays); then the number of its workgroups that one compute unit holds at a time.
-static int ra_workgroups_per_cu(const RaKernel &k, size_t shmem, const DeviceCaps &caps)
+static int ra_workgroups_per_cu(const RaKernel &k, const DeviceCaps &caps)
 {
+    const size_t shmem = k.shmem;
     struct Key {
         const void *fn;
         size_t shmem;
@@ -1239,9 +833,8 @@ static int ra_workgroups_per_cu(const RaKernel &k, size_t shmem, const DeviceCap
 // with a single workgroup waits for nobody.
 static bool ra_fits(const RaKernel &k, const Plan &p, int smode)
 {
-    if (!k.fn) return false;
     const DeviceCaps caps = device_caps();
-    const int per_cu = ra_workgroups_per_cu(k, ra_shmem(p), caps);
+    const int per_cu = ra_workgroups_per_cu(k, caps);
     if (per_cu < 1) return false;
     if (p.n_ch == 1) return true;
     if (smode != 0) return (int64_t)p.n_ch * ((p.units + p.unit_groups - 1) / p.unit_groups) <= (int64_t)per_cu * caps.cus;
@@ -1256,16 +849,15 @@ bool refine_attend_fits(const Plan &p, const ds_shape_t &s, bool scores_itself, 
     return ra_fits(ra_kernel(p, s, smode), p, smode);
 }
 
-// score_label / score_channels: non-null to run the scoring in the same launch (fp16 labels of
-// as many channels as attend_scores_r allows; with score_amax the 4-bit label cache of up to 16 channels, whose token rows
+// score_label: non-null to run the scoring in the same launch (fp16 labels of as many channels as
+// attend_scores_r allows; with amax the 4-bit label cache of up to 16 channels, whose token rows
 // must be 16-byte loadable: L_max % 4 == 0 for one word per token, L_max % 2 == 0 for two);
-// otherwise the keys and the threshold bin of a preceding k_score launch are read from the
-// workspace.  kNotResident, with nothing enqueued, when the device cannot hold the workgroups
-// that would wait for each other.
+// otherwise the keys of a preceding k_score launch are read from the workspace.  channels and amax are
+// those of the label query either way.  kNotResident, with nothing enqueued, when the device cannot
+// hold the workgroups that would wait for each other.
 hipError_t launch_refine_attend(const void *q, const void *K, const void *V, void *ws, float *out,
                                 int32_t *idx_out, const Plan &p, const ds_shape_t &s, hipStream_t st,
-                                int kv_stride, const void *score_label, const int32_t *score_channels,
-                                const float *score_amax)
+                                int kv_stride, const int32_t *channels, const float *amax, const void *score_label)
 {
     AttendArgs a{};
     a.q = static_cast<const _Float16 *>(q);
@@ -1275,10 +867,10 @@ hipError_t launch_refine_attend(const void *q, const void *K, const void *V, voi
     a.ctl = reinterpret_cast<const UnitCtl *>(wsp(ws, p.off_ctl));
     a.ctl_rw = reinterpret_cast<UnitCtl *>(wsp(ws, p.off_ctl));
     a.out = out;
-    a.offs = reinterpret_cast<const uint32_t *>(wsp(ws, p.off_offs));
-    a.offs_rw = reinterpret_cast<uint32_t *>(wsp(ws, p.off_offs));
     a.cand = reinterpret_cast<uint2 *>(wsp(ws, p.off_cand));
     a.ndef = reinterpret_cast<uint32_t *>(wsp(ws, p.off_ndef));
+    a.offs = reinterpret_cast<const uint32_t *>(wsp(ws, p.off_offs));
+    a.offs_rw = reinterpret_cast<uint32_t *>(wsp(ws, p.off_offs));
     a.idx_out = idx_out;
     a.part = reinterpret_cast<float *>(wsp(ws, p.off_part));
     a.Hq = s.Hq; a.Hkv = s.Hkv; a.G = p.G; a.L = s.L; a.L_max = s.L_max;
@@ -1286,16 +878,18 @@ hipError_t launch_refine_attend(const void *q, const void *K, const void *V, voi
     a.spin_limit = tune_get(5) ? (uint32_t)tune_get(5) : 1u << 21;
     a.kv_stride = kv_stride;
     a.label = static_cast<const _Float16 *>(score_label);
-    a.channels = score_channels;
+    a.channels = channels;
     a.hist = reinterpret_cast<uint32_t *>(wsp(ws, p.off_hist));
     a.coarse = reinterpret_cast<uint32_t *>(wsp(ws, p.off_coarse));
-    a.amax = score_amax;
+    a.amax = amax;
     a.r = s.r;
-    const int smode = ra_smode(s, score_label != nullptr, score_amax != nullptr);
+    const int smode = ra_smode(s, score_label != nullptr, amax != nullptr);
     if (score_label && smode == 0) return hipErrorInvalidValue;
     const RaKernel k = ra_kernel(p, s, smode);
-    if (!k.fn) return hipErrorInvalidValue;
     if (!ra_fits(k, p, smode)) return kNotResident;
+#ifdef DS_TRACE
+    g_last_decode = smode != 0 || p.n_ch == 1 ? pick_gt(p.G) : 0;
+#endif
     // (a launch that scores as well may take a share of the units at a time: see make_plan)
     const int groups = smode != 0 ? std::max(1, p.unit_groups) : 1;
     const int per_group = (p.units + groups - 1) / groups;
@@ -1306,9 +900,9 @@ hipError_t launch_refine_attend(const void *q, const void *K, const void *V, voi
         hipEvent_t ev_a = nullptr, ev_b = nullptr;
         hipError_t e;
         if (prof_events(KID_REFINE_ATTEND, &ev_a, &ev_b))
-            e = hipExtLaunchKernel(reinterpret_cast<const void *>(k.fn), grid, block, args, ra_shmem(p), st, ev_a, ev_b, 0);
+            e = hipExtLaunchKernel(reinterpret_cast<const void *>(k.fn), grid, block, args, k.shmem, st, ev_a, ev_b, 0);
         else
-            e = hipLaunchKernel(reinterpret_cast<const void *>(k.fn), grid, block, args, ra_shmem(p), st);
+            e = hipLaunchKernel(reinterpret_cast<const void *>(k.fn), grid, block, args, k.shmem, st);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1350,9 +944,16 @@ hipError_t launch_attend_rows(const void *q, const void *KV_rows, void *ws, floa
 }  // namespace ds
 
 #ifdef DS_TRACE
+// the stamps of the last decode launch that scored itself, or else of this file's kernels
 extern "C" int ds_trace_read_attend(void *dst, size_t bytes)
 {
-    return (int)hipMemcpyFromSymbol(dst, HIP_SYMBOL(ds::g_trace), bytes, 0, hipMemcpyDeviceToHost);
+    switch (ds::g_last_decode) {
+    case 16: return ds::trace_read<16>(dst, bytes);
+    case 8: return ds::trace_read<8>(dst, bytes);
+    case 4: return ds::trace_read<4>(dst, bytes);
+    case 2: return ds::trace_read<2>(dst, bytes);
+    case 1: return ds::trace_read<1>(dst, bytes);
+    default: return (int)hipMemcpyFromSymbol(dst, HIP_SYMBOL(ds::g_trace), bytes, 0, hipMemcpyDeviceToHost);
+    }
 }
 #endif
-

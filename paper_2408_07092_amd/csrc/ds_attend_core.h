@@ -14,7 +14,35 @@
 
 #include "ds_device.h"
 
+#define DS_PRIO(x) __builtin_amdgcn_s_setprio(x)
+
 namespace ds {
+
+struct AttendArgs {
+    const _Float16 *q, *K, *V;
+    const uint32_t *keys;
+    const UnitCtl *ctl;
+    const uint32_t *offs;
+    int32_t *idx_out;
+    float *part;
+    float *out;
+    UnitCtl *ctl_rw;
+    int Hq, Hkv, G, L, L_max, key_stride, ch, n_ch, k, k_eff, n_rows;
+    int kv_stride;       // halves from one token's K (V) row to the next: d, or 2d when K|V interleave
+    int unit0;           // k_refine_attend: first unit of this launch (a launch may take a share of the units)
+    // k_refine_attend only
+    uint2 *cand;         // [units][L] (key, token) of the keys in bin b*, unordered
+    uint32_t *ndef;      // [units][n_ch] keys above bin b* per chunk
+    uint32_t *offs_rw;   // [units][n_ch] offset of the chunk in the ascending index list
+    uint32_t spin_limit;
+    // k_refine_attend with the scoring done in the same launch (one workgroup per unit)
+    const _Float16 *label;     // [units][L_max][r]
+    const int32_t *channels;   // [Hkv][r]
+    uint32_t *hist, *coarse;   // unit histograms (4096 / 256 bins), zero between calls
+    const float *amax;         // 4-bit label cache: [units][r] largest magnitude per channel
+    int r;                     // label channels (4-bit label cache; fp16 labels have it in the kernel's type)
+};
+using RaFn = void (*)(AttendArgs);
 
 constexpr float kScaleLog2 = 1.4426950408889634f * 0.08838834764831845f;  // log2(e) / sqrt(128)
 
@@ -31,6 +59,24 @@ __device__ __forceinline__ float row16_sum(float v)
     v += dpp_move<0x141>(v);  // row_half_mirror
     v += dpp_move<0x140>(v);  // row_mirror
     return v;
+}
+
+// Sum and maximum over the four rows of 16 lanes, (row 0 + row 1) + (row 2 + row 3), by lane swaps in
+// registers (a shuffle goes through LDS, a dependent round trip of about 130 clocks each).
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float rows_sum(float v)
+{
+    u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r.x) + __uint_as_float(r.y);
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+__device__ __forceinline__ float rows_max(float v)
+{
+    u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
 }
 
 __device__ __forceinline__ float dot8(half8 a, half8 b)
@@ -71,78 +117,16 @@ __device__ __forceinline__ half8 row_load(const half8 *p)
 }
 
 // The calling wavefront's share of the workgroup's n rows: with RPS rows per 16-lane slot in
-// flight, rows wave*4*RPS + NW*4*RPS*i ..  (NW wavefronts; RPS = 4: 64 rows of a 256-thread
-// workgroup per round trip and 8 loads per lane; larger RPS for a workgroup that has a CU to itself).
+// flight, rows wave*4*RPS + 16*RPS*i ..  (RPS = 4: 64 rows of the workgroup per round trip and 8 loads
+// per lane).
 // row_of(ri) gives the row number of list entry ri; a row's K (V) bytes start at
 // Ku (Vu) + row * row_bytes.  qsh holds the GT query rows in LDS.
-template <int GT, int RPS = 4, int NW = 4, bool ST = true, class RowOf>
+template <int GT, int RPS = 4, bool ST = true, class RowOf>
 __device__ __forceinline__ void attend_rows(const char *Ku, const char *Vu, uint32_t row_bytes, int n,
                                             RowOf row_of, const _Float16 (*qsh)[kD], RowState<GT> &st)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int slot = lane >> 4, part = lane & 15;
-    if constexpr (NW > 4) {
-        // A workgroup with a CU to itself has nobody else to cover its memory latency, so the
-        // RPS rows of a slot travel in two halves, the loads of one
-        // issued before the other is folded in.  Rows reach a slot's state in the same order and
-        // the same groups of four as in the plain loop below.
-        constexpr int HB = RPS / 2;
-        const int base = wave * 4 * RPS;
-        if (base >= n) return;
-        half8 k0[HB], v0[HB], k1[HB], v1[HB];
-        // first row of the wavefront's h-th half
-        auto first_row = [&](int h) { return base + (h >> 1) * 4 * NW * RPS + (h & 1) * 4 * HB; };
-        auto issue = [&](half8 (&kr)[HB], half8 (&vr)[HB], int rr) {
-#pragma unroll
-            for (int i = 0; i < HB; ++i) {
-                const uint32_t off = (uint32_t)row_of(min(rr + i * 4 + slot, n - 1)) * row_bytes + (uint32_t)part * 16u;
-                kr[i] = row_load<ST>(reinterpret_cast<const half8 *>(Ku + off));
-                vr[i] = row_load<ST>(reinterpret_cast<const half8 *>(Vu + off));
-            }
-        };
-        auto fold = [&](half8 (&kr)[HB], half8 (&vr)[HB], int rr) {
-#pragma unroll
-            for (int g = 0; g < GT; ++g) {
-                const half8 qv = *reinterpret_cast<const half8 *>(&qsh[g][part * 8]);
-#pragma unroll
-                for (int i0 = 0; i0 < HB; i0 += 4) {
-                    float s[4];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        s[i] = row16_sum(dot8(qv, kr[i0 + i])) * kScaleLog2;
-                        if (rr + (i0 + i) * 4 + slot >= n) s[i] = kNegInf;
-                    }
-                    const float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-                    const float mn = fmaxf(st.m[g], mx);
-                    if (mn != kNegInf) {
-                        const float sc = (st.m[g] == kNegInf) ? 0.0f : __builtin_amdgcn_exp2f(st.m[g] - mn);
-                        st.m[g] = mn;
-                        st.l[g] *= sc;
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) st.acc[g][j] *= sc;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float p = __builtin_amdgcn_exp2f(s[i] - mn);
-                            st.l[g] += p;
-#pragma unroll
-                            for (int j = 0; j < 8; ++j)
-                                st.acc[g][j] = __builtin_fmaf(p, (float)vr[i0 + i][j], st.acc[g][j]);
-                        }
-                    }
-                }
-            }
-        };
-        issue(k0, v0, first_row(0));
-        for (int h = 0; first_row(h) < n; h += 2) {
-            issue(k1, v1, first_row(h + 1));
-            __builtin_amdgcn_sched_barrier(0);
-            fold(k0, v0, first_row(h));
-            issue(k0, v0, first_row(h + 2));
-            __builtin_amdgcn_sched_barrier(0);
-            if (first_row(h + 1) < n) fold(k1, v1, first_row(h + 1));
-        }
-        return;
-    }
     for (int r0 = wave * 4 * RPS; r0 < n; r0 += 16 * RPS) {
         // all row loads of the pass are issued before the first use; lanes past the
         // end re-read the last row of the list (in bounds) and mask its score below
@@ -256,19 +240,12 @@ __device__ __forceinline__ void wg_store_partial(const RowState<GT> &st,
     const int slot = lane >> 4, part = lane & 15;
 #pragma unroll
     for (int g = 0; g < GT; ++g) {
-        float mm = fmaxf(st.m[g], __shfl_xor(st.m[g], 16));
-        mm = fmaxf(mm, __shfl_xor(mm, 32));
+        const float mm = rows_max(st.m[g]);
         const float w = (st.m[g] == kNegInf) ? 0.0f : __builtin_amdgcn_exp2f(st.m[g] - mm);
-        float lv = st.l[g] * w;
-        lv += __shfl_xor(lv, 16);
-        lv += __shfl_xor(lv, 32);
+        const float lv = rows_sum(st.l[g] * w);
         float av[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            av[j] = st.acc[g][j] * w;
-            av[j] += __shfl_xor(av[j], 16);
-            av[j] += __shfl_xor(av[j], 32);
-        }
+        for (int j = 0; j < 8; ++j) av[j] = rows_sum(st.acc[g][j] * w);
         if (slot == 0) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) wpart[wave][g][4 + part * 8 + j] = av[j];
@@ -326,6 +303,52 @@ __device__ __forceinline__ void load_q_mfma(const _Float16 *q_unit, int n_heads,
     }
 }
 
+// Folds a tile of 16 rows, r0 .. of n, into the state: S its scores, vr its V pieces.
+__device__ __forceinline__ void mfma_fold(float4v S, const half8 (&vr)[4], int r0, int n, MfmaState &st, float *sc_lds, int lo, int hi)
+{
+    float s[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) s[r] = (r0 + 4 * hi + r < n) ? S[r] * kScaleLog2 : kNegInf;
+    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));  // over the 16 tokens of the tile, per head (token r0 is valid)
+    const float mn = fmaxf(st.m, mx);
+    const float sc = (st.m == kNegInf) ? 0.0f : __builtin_amdgcn_exp2f(st.m - mn);
+    st.m = mn;
+    float p[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(s[r] - mn + kPScaleLog2);  // (masked rows: 2^-inf = 0)
+    st.l = st.l * sc + ((p[0] + p[1]) + (p[2] + p[3]));
+    if (__any(sc != 1.0f)) {
+        // the accumulators of heads 4*hi .. 4*hi+3 live in this lane; their scale factors sit in
+        // lanes 4*hi .. 4*hi+3 of the wavefront: pass them through the wavefront's LDS words
+        if (hi == 0) sc_lds[lo] = sc;
+        const float4v f = *reinterpret_cast<const float4v *>(sc_lds + 4 * hi);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) st.O[e] *= f;
+    }
+    // P.V on the fp16 matrix cores with fp32 accumulation: V is fp16 as stored; a weight goes
+    // in as the sum of two fp16 numbers, hi = fp16(p) and lo = fp16(p - hi), which carries it to
+    // about 22 bits (the weights are scaled by kPScale beforehand, see above, so that lo stays a
+    // normal fp16 number for every weight that matters).  16 short issues per tile against 32
+    // long ones with weights and V widened to fp32 (measured: C4a 52.0 -> 49.5 us/layer).
+    half4v p_hi, p_lo;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        p_hi[r] = (_Float16)p[r];
+        p_lo[r] = (_Float16)(p[r] - (float)p_hi[r]);
+    }
+    // (the eight high parts first, then the eight low parts: two issues in a row into the
+    //  same accumulator would wait for each other)
+    half4v vb[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) vb[e] = (half4v){vr[0][e], vr[1][e], vr[2][e], vr[3][e]};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) st.O[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(p_hi, vb[e], st.O[e], 0, 0, 0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) st.O[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(p_lo, vb[e], st.O[e], 0, 0, 0);
+}
+
 // sc_lds: 16 floats of LDS private to the calling wavefront.
 // KST: whether the K loads carry the streaming mark.  A K load takes 64 bytes of each of 16 rows,
 // so two loads in a row share every 128-byte line; when the rows are gathered, the second finds
@@ -369,47 +392,7 @@ __device__ __forceinline__ void attend_rows_mfma(const char *Ku, const char *Vu,
         __builtin_amdgcn_sched_barrier(0);
         if (more) issue_k(r0 + 64);
         __builtin_amdgcn_sched_barrier(0);
-        float s[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) s[r] = (r0 + 4 * hi + r < n) ? S[r] * kScaleLog2 : kNegInf;
-        float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));  // over the 16 tokens of the tile, per head (token r0 is valid)
-        const float mn = fmaxf(st.m, mx);
-        const float sc = (st.m == kNegInf) ? 0.0f : __builtin_amdgcn_exp2f(st.m - mn);
-        st.m = mn;
-        float p[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(s[r] - mn + kPScaleLog2);  // (masked rows: 2^-inf = 0)
-        st.l = st.l * sc + ((p[0] + p[1]) + (p[2] + p[3]));
-        if (__any(sc != 1.0f)) {
-            // the accumulators of heads 4*hi .. 4*hi+3 live in this lane; their scale factors sit in
-            // lanes 4*hi .. 4*hi+3 of the wavefront: pass them through the wavefront's LDS words
-            if (hi == 0) sc_lds[lo] = sc;
-            const float4v f = *reinterpret_cast<const float4v *>(sc_lds + 4 * hi);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) st.O[e] *= f;
-        }
-        // P.V on the fp16 matrix cores with fp32 accumulation: V is fp16 as stored; a weight goes
-        // in as the sum of two fp16 numbers, hi = fp16(p) and lo = fp16(p - hi), which carries it to
-        // about 22 bits (the weights are scaled by kPScale beforehand, see above, so that lo stays a
-        // normal fp16 number for every weight that matters).  16 short issues per tile against 32
-        // long ones with weights and V widened to fp32 (measured: C4a 52.0 -> 49.5 us/layer).
-        half4v p_hi, p_lo;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            p_hi[r] = (_Float16)p[r];
-            p_lo[r] = (_Float16)(p[r] - (float)p_hi[r]);
-        }
-        // (the eight high parts first, then the eight low parts: two issues in a row into the
-        //  same accumulator would wait for each other)
-        half4v vb[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) vb[e] = (half4v){vr[0][e], vr[1][e], vr[2][e], vr[3][e]};
-#pragma unroll
-        for (int e = 0; e < 8; ++e) st.O[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(p_hi, vb[e], st.O[e], 0, 0, 0);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) st.O[e] = __builtin_amdgcn_mfma_f32_16x16x16f16(p_lo, vb[e], st.O[e], 0, 0, 0);
+        mfma_fold(S, vr, r0, n, st, sc_lds, lo, hi);
         __builtin_amdgcn_sched_barrier(0);
         if (more) issue_v(r0 + 64);
     }

@@ -1,0 +1,13 @@
+// The one-launch decode kernels of pairs of heads.
+#include "ds_device.h"
+
+namespace ds {
+DS_TRACE_BUFFER
+}
+
+#include "ds_decode_core.h"
+
+namespace ds {
+DS_DEFINE_DECODE_FN(2)
+DS_DEFINE_TRACE_READ(2)
+}  // namespace ds

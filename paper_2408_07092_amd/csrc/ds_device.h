@@ -60,9 +60,17 @@ __device__ __forceinline__ half8 swap_pairs(half8 v)
             g_trace[(((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + (stage)) & ((1 << 18) - 1)] = \
                 wall_clock64();                                                                   \
     } while (0)
+// (the same, stamped by the second wavefront)
+#define DS_TR1(stage)                                                                             \
+    do {                                                                                          \
+        if (threadIdx.x == 64)                                                                    \
+            g_trace[(((size_t)blockIdx.y * gridDim.x + blockIdx.x) * 16 + (stage)) & ((1 << 18) - 1)] = \
+                wall_clock64();                                                                   \
+    } while (0)
 #else
 #define DS_TRACE_BUFFER
 #define DS_TR(stage) do { } while (0)
+#define DS_TR1(stage) do { } while (0)
 #endif
 
 // Monotone map from a binary32 score to an unsigned key: a larger score gives a

@@ -69,7 +69,7 @@ struct Plan {
     int ch, n_ch;        // same for candidate collection, compaction and attention
     int key_stride;      // uint32 keys per unit (L rounded up to 4)
     bool refine_attend;  // ds_sparse_decode as scoring + one refine-and-attend launch
-    bool group_scores_itself;  // query groups of 3+ heads: chunks sized so that this launch can do the scoring too
+    bool chunks_score;   // several workgroups per unit: chunks chosen for a launch that does the scoring too
     int unit_groups;     // the attention launch that scores as well is enqueued this many times, a share of the units each
     size_t off_ctl, off_hist, off_coarse, off_keys, off_cand, off_ndef, off_offs, off_part;
     size_t total;
@@ -127,7 +127,7 @@ bool prof_events(int id, hipEvent_t *start, hipEvent_t *stop);
 // launchers: enqueue only; return the launch error (hipSuccess if fine)
 hipError_t launch_init(void *ws, size_t bytes, hipStream_t st);
 hipError_t launch_score(const void *q, const void *label, const int32_t *channels, void *ws,
-                        const Plan &p, const ds_shape_t &s, bool tail_refine, bool want_offsets,
+                        const Plan &p, const ds_shape_t &s, bool bins, bool tail_refine, bool want_offsets,
                         hipStream_t st, ScoreSrc src = ScoreSrc());
 hipError_t launch_cand(void *ws, const Plan &p, const ds_shape_t &s, bool want_offsets,
                        hipStream_t st);
@@ -142,15 +142,19 @@ hipError_t launch_attend_sparse(const void *q, const void *K, const void *V, voi
 // 300 to 65536 tokens, groups of 1 to 64): 20 channels 0.75, 28 0.74, 32 0.81 of the time, at worst 1.03
 // (16 pairs of 64K tokens, 32 channels).  Other widths take the scoring launch.
 constexpr bool attend_scores_r(int r) { return r % 4 == 0 && r <= 32; }
+constexpr int kDecodeTokens = 16384;  // tokens of a workgroup at most: 32 a thread of 512
 bool refine_attend_ok(const Plan &p, bool scores_itself);
+// Variants of the kernel: 512 threads; the same without the streaming mark and with
+// more rows in flight (a mostly idle device); 256 threads.
+enum DecodeVariant { DECODE_WIDE = 0, DECODE_LIGHT = 1, DECODE_NARROW = 2 };
+DecodeVariant decode_variant(const Plan &p, bool streams);
 // Returned by launch_refine_attend (nothing enqueued) when the launch would wait for workgroups
 // that the device cannot hold at the same time as the waiting ones.
 constexpr hipError_t kNotResident = hipErrorLaunchOutOfResources;
 bool refine_attend_fits(const Plan &p, const ds_shape_t &s, bool scores_itself, bool q4);
 hipError_t launch_refine_attend(const void *q, const void *K, const void *V, void *ws, float *out,
                                 int32_t *idx_out, const Plan &p, const ds_shape_t &s, hipStream_t st,
-                                int kv_stride = kD, const void *score_label = nullptr,
-                                const int32_t *score_channels = nullptr, const float *score_amax = nullptr);
+                                int kv_stride, const int32_t *channels, const float *amax, const void *score_label);
 hipError_t launch_attend_dense(const void *q, const void *K, const void *V, void *ws, float *out,
                                const DensePlan &p, const ds_shape_t &s, hipStream_t st);
 hipError_t launch_attend_rows(const void *q, const void *KV_rows, void *ws, float *out,

@@ -59,7 +59,9 @@ __device__ __forceinline__ float label_dot(const _Float16 *__restrict__ row, con
     return acc;
 }
 
-template <int RMODE>
+// BINS: the launch also finds the unit's threshold bin (for the launches that select from it: k_cand, or
+// this one's own tail).  k_refine_attend bins the keys by itself and wants nothing but them.
+template <int RMODE, bool BINS>
 __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
                                                const _Float16 *__restrict__ label,
                                                const int32_t *__restrict__ channels,
@@ -124,7 +126,8 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
                 issue(t_begin + tid);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            for (int i = tid; i < kHistBins; i += kWG) lh[i] = 0u;
+            if constexpr (BINS)
+                for (int i = tid; i < kHistBins; i += kWG) lh[i] = 0u;
         }
         __syncthreads();
         if (tid < r)
@@ -154,7 +157,7 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
                 if (t < t_end) {
                     const uint32_t key = score_key(acc);
                     put_key(ku + t, key);
-                    atomicAdd(&lh[key >> kKeyShift], 1u);
+                    if constexpr (BINS) atomicAdd(&lh[key >> kKeyShift], 1u);
                 }
             }
             t0 += kWG * UNR;
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
         auto nib = [](uint32_t word, int i) { return (float)(((int32_t)(word << (28 - 4 * i))) >> 28); };
         // One or two words per token: 16-byte loads of four or two tokens, four loads in flight;
         // w[j] = 0 beyond r (a product of zero leaves the sum as it is).
-        auto run_packed = [&](auto wc) {
+        auto run_packed = [=](auto wc) {  // (copies: by reference t_end got a place in scratch memory)
             constexpr int WW = decltype(wc)::value;  // words per token
             constexpr int TPL = 4 / WW;              // tokens per 16-byte load
             float wr[8 * WW];
@@ -193,7 +196,7 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
                         if (t < t_end) {
                             const uint32_t key = score_key(acc);
                             put_key(ku + t, key);
-                            atomicAdd(&lh[key >> kKeyShift], 1u);
+                            if constexpr (BINS) atomicAdd(&lh[key >> kKeyShift], 1u);
                         }
                     }
                 }
@@ -213,7 +216,7 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
                 }
                 const uint32_t key = score_key(acc);
                 put_key(ku + t, key);
-                atomicAdd(&lh[key >> kKeyShift], 1u);
+                if constexpr (BINS) atomicAdd(&lh[key >> kKeyShift], 1u);
             }
         }
     } else if constexpr (RMODE == -2) {
@@ -236,7 +239,7 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
                 if (t < t_end) {
                     const uint32_t key = score_key(acc[i]);
                     put_key(ku + t, key);
-                    atomicAdd(&lh[key >> kKeyShift], 1u);
+                    if constexpr (BINS) atomicAdd(&lh[key >> kKeyShift], 1u);
                 }
             }
         }
@@ -244,9 +247,10 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
         for (int t = t_begin + tid; t < t_end; t += kWG) {
             const uint32_t key = score_key(label_dot<RMODE>(lab + (size_t)t * r, qs_sh, r));
             put_key(ku + t, key);
-            atomicAdd(&lh[key >> kKeyShift], 1u);
+            if constexpr (BINS) atomicAdd(&lh[key >> kKeyShift], 1u);
         }
     }
+    if constexpr (!BINS) return;
     DS_TR(2);
     __syncthreads();
     uint32_t *hu = hist + (size_t)u * kHistBins;
@@ -630,7 +634,7 @@ hipError_t launch_init(void *ws, size_t bytes, hipStream_t st)
 }
 
 hipError_t launch_score(const void *q, const void *label, const int32_t *channels, void *ws,
-                        const Plan &p, const ds_shape_t &s, bool tail_refine, bool want_offsets,
+                        const Plan &p, const ds_shape_t &s, bool bins, bool tail_refine, bool want_offsets,
                         hipStream_t st, ScoreSrc src)
 {
     const dim3 grid(p.n_sc, p.units), block(kWG);
@@ -641,8 +645,12 @@ hipError_t launch_score(const void *q, const void *label, const int32_t *channel
     auto *offs = reinterpret_cast<uint32_t *>(wsp(ws, p.off_offs));
     const auto *qh = static_cast<const _Float16 *>(q);
     const auto *lh = static_cast<const _Float16 *>(label);
+    // (K rows without the bins take as much LDS as with them: with more workgroups to a compute unit its first-level
+    //  cache, in which a row's channels are found again, is too small: 97.8 -> 208 us for six units of 137K tokens, 16
+    //  channels)
+    const size_t shmem = (size_t)p.n_ch * 4 + (!bins && src.kind == SRC_K_ROWS ? (24u << 10) : 0u);
 #define DS_SCORE(MODE)                                                                            \
-    DS_LAUNCH(KID_SCORE, k_score<MODE>, grid, block, (size_t)p.n_ch * 4, st, qh, lh, channels, src.amax, keys, hist, \
+    DS_LAUNCH(KID_SCORE, (bins ? k_score<MODE, true> : k_score<MODE, false>), grid, block, shmem, st, qh, lh, channels, src.amax, keys, hist, \
                        coarse, ctl, offs, s.Hq, s.Hkv, p.G, s.L, s.L_max, s.r, p.key_stride, p.sc_chunk,       \
                        p.k_eff, tail_refine ? 1 : 0, want_offsets ? 1 : 0, p.ch, p.n_ch)
     if (src.kind == SRC_Q4) DS_SCORE(-3);
