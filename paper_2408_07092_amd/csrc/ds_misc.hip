@@ -71,7 +71,10 @@ __global__ __launch_bounds__(kWG) void k_label(const uint16_t *__restrict__ K,
 // Decode-step cache maintenance in one launch (Sec. 4.2: a decode step extends the label cache
 // by the new tokens' r selected channels only): the n new tokens' K and V rows go into
 // the caches at tokens [t0, t0 + n) and their r label values into the label cache.
-// 16 lanes move one 256-byte row; the label values are picked out of the new rows afterwards.
+// 16 lanes move one 256-byte row.  One token of one unit is all that a decode step has for a workgroup, so the
+// launch is latency: channel ids and rows come in with one round trip, and the label values are picked
+// out of the K rows in LDS.  (Ids, then rows, then the values out of memory again, found by 64-bit
+// divisions: three round trips in a row.)
 __global__ __launch_bounds__(kWG) void k_append_kv(const uint4 *__restrict__ k_new,
                                                    const uint4 *__restrict__ v_new, uint4 *K, uint4 *V,
                                                    const int32_t *__restrict__ channels,
@@ -79,22 +82,26 @@ __global__ __launch_bounds__(kWG) void k_append_kv(const uint4 *__restrict__ k_n
                                                    int r, int t0, int n, int kv_stride16)
 {
     __shared__ int ch_sh[kD];
-    const int u = blockIdx.y, h = u % Hkv;
-    if (threadIdx.x < r) ch_sh[threadIdx.x] = channels[h * r + threadIdx.x];
-    __syncthreads();
-    const int p = threadIdx.x & 15;
-    for (int i = blockIdx.x * 16 + (threadIdx.x >> 4); i < n; i += gridDim.x * 16) {
-        const size_t src = ((size_t)u * n + i) * 16 + p;
-        const size_t dst = ((size_t)u * L_max + t0 + i) * kv_stride16 + p;
-        K[dst] = k_new[src];
-        V[dst] = v_new[src];
-    }
-    const uint16_t *kn = reinterpret_cast<const uint16_t *>(k_new);
-    const size_t total = (size_t)n * r;
-    for (size_t e = (size_t)blockIdx.x * kWG + threadIdx.x; e < total; e += (size_t)gridDim.x * kWG) {
-        const size_t i = e / r;
-        const int j = (int)(e % r);
-        label[((size_t)u * L_max + t0 + i) * r + j] = kn[((size_t)u * n + i) * kD + ch_sh[j]];
+    __shared__ __attribute__((aligned(16))) uint16_t rows_sh[16][kD];
+    const int tid = threadIdx.x, u = blockIdx.y, h = u % Hkv;
+    const int row = tid >> 4, p = tid & 15;
+    int c = 0;
+    if (tid < r) c = channels[h * r + tid];
+    for (int i0 = blockIdx.x * 16; i0 < n; i0 += gridDim.x * 16) {
+        const int m = min(16, n - i0);
+        if (row < m) {
+            const size_t src = ((size_t)u * n + i0 + row) * 16 + p;
+            const size_t dst = ((size_t)u * L_max + t0 + i0 + row) * kv_stride16 + p;
+            const uint4 k = k_new[src], v = v_new[src];
+            *reinterpret_cast<uint4 *>(&rows_sh[row][p * 8]) = k;
+            K[dst] = k;
+            V[dst] = v;
+        }
+        if (tid < r) ch_sh[tid] = c;
+        __syncthreads();
+        uint16_t *lab = label + ((size_t)u * L_max + t0 + i0) * r;
+        for (int e = tid; e < m * r; e += kWG) lab[e] = rows_sh[(uint32_t)e / (uint32_t)r][ch_sh[(uint32_t)e % (uint32_t)r]];
+        __syncthreads();
     }
 }
 

@@ -378,3 +378,28 @@ def test_decode_many_candidates(Hq, L, k, step, one):
     assert (ds.ds_plan_describe(ds.shape(1, Hq, 1, 128, L, L, 8, k))["workgroups_per_unit"] == 1) == one
     case = Case(t["q"], t["K"], t["V"], ch, L, k)
     full_parity(case, what=f"many candidates L{L} k{k}")
+
+
+@pytest.mark.parametrize("n,r,inter", [(1, 8, False), (1, 3, True), (15, 24, False), (16, 8, True), (17, 128, False), (40, 12, False)])
+def test_append_kv_equals_the_cache_built_in_one_go(n, r, inter):
+    """Rows and label values of n new tokens, below, at and above the 16 that a workgroup takes at a time."""
+    B, Hkv, L, L_max = 2, 3, 50 + n, 60 + n
+    t = make_layer_numpy(Workload("t", B, Hkv, Hkv, 128, L, r, 1, 1), L_max=L_max)
+    ch = rand_channels(Hkv, r, seed=n)
+    K, V = to_dev(t["K"]), to_dev(t["V"])
+    k_new, v_new = K[:, :, 50:L].contiguous(), V[:, :, 50:L].contiguous()
+    shp = ds.shape(B, Hkv, Hkv, 128, L, L_max, r, 1)
+    label = torch.full((B, Hkv, L_max, r), -7.0, dtype=torch.float16, device="cuda")
+    if inter:
+        KV = torch.full((B, Hkv, L_max, 2, 128), 5.0, dtype=torch.float16, device="cuda")
+        ds.ds_append_kv(k_new, v_new, KV, None, to_dev(ch), label, shp, 50, n, ds.DS_KV_INTERLEAVED)
+        Kc, Vc = KV[:, :, :, 0], KV[:, :, :, 1]
+    else:
+        Kc, Vc = torch.full_like(K, 5.0), torch.full_like(V, 5.0)
+        ds.ds_append_kv(k_new, v_new, Kc, Vc, to_dev(ch), label, shp, 50, n, ds.DS_KV_SPLIT)
+    torch.cuda.synchronize()
+    assert torch.equal(Kc[:, :, 50:L], k_new) and torch.equal(Vc[:, :, 50:L], v_new)
+    ref = O.build_label(t["K"], ch, L)
+    assert np.array_equal(label[:, :, 50:L].cpu().numpy().view(np.uint16), np.ascontiguousarray(ref[:, :, 50:L]).view(np.uint16))
+    for x, v in ((Kc, 5.0), (Vc, 5.0), (label, -7.0)):
+        assert (x[:, :, :50] == v).all() and (x[:, :, L:] == v).all()
