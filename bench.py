@@ -315,15 +315,12 @@ def main():
 
 
 # Stage numbers that thread 0 of every workgroup of the attention launch stamps (DS_TR in
-# csrc/ds_attend.hip), in the order a workgroup passes them.
-TRACE_STAGES = [(0, "start"), (11, "chunk scored (keys in LDS)"), (12, "unit histogram complete"),
-                (10, "threshold bin known"), (13, "keys counted against the bin"),
-                (1, "lists made, candidates handed over"), (2, "arrived at unit counter"),
-                (8, "refiner: candidate loads issued"),
-                (14, "refiner: first radix pass done"), (15, "refiner: exact threshold known"),
-                (9, "refiner: published, histograms cleared"),
-                (3, "definite rows attended"), (4, "exact threshold picked up, rest listed"),
-                (5, "remaining rows attended"), (6, "partial written, arrived"), (7, "unit merged")]
+# csrc/ds_decode_core.h; "second wavefront": DS_TR1), in the order a workgroup passes them.
+TRACE_STAGES = [(0, "started"), (15, "label query known"), (11, "chunk scored, histogram in LDS"), (10, "threshold bin known"),
+                (1, "lists made"), (2, "candidates in memory, arrived"), (12, "all of the unit's have arrived"),
+                (14, "exact threshold settled"), (5, "row list complete"),
+                (8, "second wavefront: definite rows"), (13, "second wavefront: all rows"),
+                (3, "first wavefront past the rows"), (6, "partial written, arrived"), (7, "unit merged")]
 
 
 def trace_report(args, w, ds, torch, sweep):

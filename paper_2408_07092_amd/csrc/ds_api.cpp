@@ -133,18 +133,29 @@ static bool choose_chunks(int units, int L, int G, double token_bytes, int cus, 
     return found;
 }
 
-// The variant of the kernel that scores itself.
-//   - 256 threads where single-workgroup units outnumber two to a compute unit: four fit at once (1024 single heads
-//     of 1000 tokens 16.8 us with 512 threads, 12.9 with 256; of 2048 22.5 and 19.8; 256 units of 1000 7.7 and 7.8);
-//   - without the streaming mark and with four rows per slot in flight instead of two where the device is mostly
-//     idle or the call moves a few MiB (one layer of 32 heads of 4K tokens 9.4 -> 9.2 us, 128 of 6000 14.5 -> 13.8;
-//     256 of 8192 22.4 -> 22.9).
-DecodeVariant decode_variant(const Plan &p, bool streams)
+size_t decode_bytes(const Plan &p, const ds_shape_t &s)
+{
+    return (size_t)p.units * ((size_t)s.L * s.r * 2 + (size_t)p.k_eff * 2 * kD * 2);
+}
+
+// The variant of the attention kernel.
+//   - 256 threads where single-workgroup units outnumber two to a compute unit (groups of more than eight heads:
+//     one), of which four fit at once (1024 single heads of 1000 tokens 16.8 us with 512 threads, 12.9 with 256; of
+//     2048 22.5 and 19.8; 256 units of 1000 7.7 and 7.8);
+//   - single heads and pairs, one workgroup per unit and units for less than three quarters of the device: four
+//     rows per slot in flight instead of two (128 units of 6000 tokens 14.5 -> 13.8 us, of 8192 18.0 -> 17.0; 256 of 8192
+//     22.4 -> 22.9);
+//   - without the streaming mark below 16 MiB, and where so few units read less than 32 MiB, of which the memory-side
+//     cache holds several layers (eight layers of 128 units of 4096 tokens 12.4 -> 11.0 us a layer, of 64 of 6144 13.2 ->
+//     11.6; 128 of 6000 14.0 either way; 160 of 6144 14.8 -> 15.6, 128 of 8192 17.0 -> 17.9).
+DecodeVariant decode_variant(const Plan &p, const ds_shape_t &s)
 {
     const int64_t wgs = (int64_t)p.n_ch * ((p.units + p.unit_groups - 1) / p.unit_groups);
     if (wgs > (p.G > 8 ? 1 : 2) * (int64_t)p.cus && p.ch <= kDecodeTokens / 2) return DECODE_NARROW;
-    if (!streams || (p.n_ch == 1 && (int64_t)p.units * 4 < 3 * (int64_t)p.cus)) return DECODE_LIGHT;
-    return DECODE_WIDE;
+    const size_t bytes = decode_bytes(p, s);
+    const bool few = p.n_ch == 1 && (int64_t)p.units * 4 < 3 * (int64_t)p.cus;
+    if (bytes < (few ? 2 : 1) * kStreamBytes) return DECODE_LIGHT;
+    return few ? DECODE_DEEP : DECODE_WIDE;
 }
 
 bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)

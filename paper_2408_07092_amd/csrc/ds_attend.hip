@@ -736,15 +736,6 @@ struct RaKernel {
     size_t shmem;
 };
 
-// Whether a sparse decode call marks its loads of label and K/V rows as streaming: when it moves
-// 16 MiB or more (the headline shape moves 96 MiB).  A call of a few MiB that finds its rows in the
-// caches is up to 1 us of 15 slower with the mark; single heads and pairs have a variant without.
-static bool streams_past_caches(const Plan &p, const ds_shape_t &s)
-{
-    const size_t per_unit = (size_t)s.L * s.r * 2 + (size_t)p.k_eff * 2 * kD * 2;
-    return (size_t)p.units * per_unit >= ((size_t)16 << 20);
-}
-
 #ifdef DS_TRACE
 static int g_last_decode = 0;
 #endif
@@ -760,13 +751,16 @@ static RaFn decode_kernel(int gt, int smode, DecodeVariant v)
     }
 }
 
+// Whether a chunk's keys fit LDS besides its list, with as many workgroups to a compute unit as the plans count on.
+static bool keys_in_lds(const Plan &p) { return p.ch <= (p.G <= 2 ? 8192 : p.G <= 8 ? 4096 : 2048); }
+
 // smode: 0 = keys and threshold bin come from the scoring launch; 4 .. 32 = fp16 labels of that
 // many channels scored here; -8 / -16 = 4-bit labels of up to that many channels scored here.
 static RaKernel ra_kernel(const Plan &p, const ds_shape_t &s, int smode)
 {
     const int gt = pick_gt(p.G);
-    const bool st = streams_past_caches(p, s);
     if (smode == 0 && p.n_ch > 1) {
+        const bool st = decode_bytes(p, s) >= kStreamBytes;
         const size_t shmem = (size_t)p.ch * 6 + (size_t)p.n_ch * 4;
         switch (gt) {
         case 16: return {k_attend_behind_scoring<16, true>, kWG, shmem};
@@ -776,8 +770,9 @@ static RaKernel ra_kernel(const Plan &p, const ds_shape_t &s, int smode)
         default: return {st ? k_attend_behind_scoring<1, true> : k_attend_behind_scoring<1, false>, kWG, shmem};
         }
     }
-    const DecodeVariant v = decode_variant(p, st);
-    return {decode_kernel(gt, smode, v), v == DECODE_NARROW ? 256 : 512, ((size_t)p.ch * 2 + 15) & ~(size_t)15};
+    const DecodeVariant v = decode_variant(p, s);
+    return {decode_kernel(gt, smode, v), v == DECODE_NARROW ? 256 : 512,
+            (size_t)(p.ch + 7) / 8 * 16 + (keys_in_lds(p) ? (size_t)p.ch * 4 : 0)};
 }
 
 // 0 when the labels cannot be scored in the attention launch
@@ -883,6 +878,7 @@ hipError_t launch_refine_attend(const void *q, const void *K, const void *V, voi
     a.coarse = reinterpret_cast<uint32_t *>(wsp(ws, p.off_coarse));
     a.amax = amax;
     a.r = s.r;
+    a.keys_in_lds = keys_in_lds(p);
     const int smode = ra_smode(s, score_label != nullptr, amax != nullptr);
     if (score_label && smode == 0) return hipErrorInvalidValue;
     const RaKernel k = ra_kernel(p, s, smode);

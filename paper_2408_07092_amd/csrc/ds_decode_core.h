@@ -1,19 +1,31 @@
-// The decode of one layer in one launch (Algorithm 1 steps 1-5): body of k_refine_attend for label
-// caches that the launch scores itself.
+// The decode of one layer in one launch (Algorithm 1 steps 1-5): body of k_refine_attend, for label
+// caches that the launch scores itself, and for units of one workgroup behind a scoring launch.
 //
 // A workgroup owns a chunk of a unit's tokens, or the whole unit.
 //   1. Its label rows are streamed; every thread keeps the keys of its up to 32 tokens in registers.
 //   2. Threshold bin: from the chunk's histogram in LDS (one workgroup per unit), or the chunk
 //      histograms meet in the unit's histograms in memory and every workgroup finds the bin there.
 //   3. The keys are split into definite tokens (bin above: selected whatever the exact threshold is),
-//      candidates (in the bin) and the rest; the lists go to LDS and the keys are dead.
-//   4. Wavefront 0 settles the exact threshold (T, tie cut) -- alone where it can, with no barrier --
-//      while the others stream the definite rows; it then adds the workgroup's selected candidates
-//      to the row list.
-//   5. One barrier; the other wavefronts attend the rest, the partials meet.
-// What bounds it: the two streams (label rows, gathered K/V rows) at memory's rate, and between them
-// the chain of 2 to 4, which is latency: LDS round trips, barriers and, with several workgroups per
-// unit, round trips to memory.
+//      candidates (in the bin, one key in a thousand) and the rest; the lists go to LDS.
+//   4. Wavefront 0 settles the exact threshold (T, tie cut) -- among the candidates of all of the unit's
+//      workgroups, which meet in memory -- while the others stream the definite rows; it then adds
+//      the workgroup's selected candidates to the row list and raises a flag.
+//   5. The others take the rest of the list; the wavefronts' partials meet in LDS, the workgroups' in memory.
+//
+// What bounds it: the two streams (label rows, gathered K/V rows) at memory's rate, 6.1 TB/s each on 32 heads
+// of 64K tokens, and between, before and behind them a chain of latencies: 2 us to the first scores, 2.3 for the
+// unit's threshold bin, 1.3 for the lists, 1.5 for the partial, 2 for the merge.
+// Why this split (us per layer, before -> after, 32 heads of 64K tokens unless said otherwise):
+//   - A wavefront issues an instruction every 8 clocks at best, two to a SIMD fill that: 512 threads. With 1024, and
+//     every wavefront running the list work, one layer of 4K tokens took 12.6, with 512 9.2.
+//   - One wavefront does what needs no more; the others never wait at its barriers (31.1 -> 26.5 with the next two).
+//   - Bins of 1/128 octave instead of 1/8: 70 candidates in a unit where there were 1100, so that every workgroup settles
+//     the threshold alone; one that did it for the unit held the others up until 10 us after the last had arrived.
+//   - No more row loads in flight than memory needs: a workgroup's hand-over queues behind them. Eight rows per slot 34.6,
+//     four 33.1, two 32.0 (with the settling workgroup).
+//   - Fewer, larger workgroups: 8 per unit instead of 32 meet at the same lines of memory.
+// Keys kept in LDS as well, so that candidates' keys need no search in the registers, change nothing (9.0 and 9.0; 14.9 and
+// 14.9); rows held back until the candidates have been sent, so that these do not queue, cost 0.6 us at 64K.
 #pragma once
 
 #include "ds_attend_core.h"
@@ -23,7 +35,7 @@ namespace ds {
 constexpr int kKeys = 32;               // tokens of a thread at most
 constexpr int kQRow = kD + 8;           // halves from one query row in LDS to the next (spreads the matrix cores' reads over the banks)
 constexpr uint32_t kCandLds = 512;      // candidates of a workgroup that LDS holds; the others go through memory
-constexpr uint32_t kWaveSettles = 8192; // more candidates than this are refined by the whole workgroup
+constexpr uint32_t kWaveSettles = 8192; // more candidates than this are settled by the whole workgroup
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 __device__ __forceinline__ uint32_t read_lane(uint32_t x, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)x, l); }
@@ -284,7 +296,7 @@ struct VectorRows {
         const _Float16 (*q)[kQRow];
         int place;                // the slot's place among the row wavefronts' slots
     };
-    __device__ __forceinline__ int row(const Src &s, int half, int i) const { return half * HR + i * RW * 4 + s.place; }
+    __device__ __forceinline__ int row(const Src &s, int round, int i) const { return round * HR + i * RW * 4 + s.place; }
     __device__ __forceinline__ void load(const Src &s, half8 &kr, half8 &vr, int p)
     {
         const uint32_t off = (uint32_t)s.sel[p] * s.row_bytes + (uint32_t)(threadIdx.x & 15) * 16u;
@@ -306,9 +318,9 @@ struct VectorRows {
             }
         }
     }
-    __device__ __forceinline__ void fold(const Src &s, half8 (&kr)[HB], half8 (&vr)[HB], int half, int n)
+    __device__ __forceinline__ void fold(const Src &s, half8 (&kr)[HB], half8 (&vr)[HB], int round, int n)
     {
-        const bool full = (half + 1) * HR <= n;
+        const bool full = (round + 1) * HR <= n;
         const int part = threadIdx.x & 15;
 #pragma unroll
         for (int g = 0; g < GT; ++g) {
@@ -317,7 +329,7 @@ struct VectorRows {
 #pragma unroll
             for (int i = 0; i < HB; ++i) {
                 sc4[i] = row16_sum(dot8(qv, kr[i])) * kScaleLog2;
-                if (!full && row(s, half, i) >= n) sc4[i] = kNegInf;
+                if (!full && row(s, round, i) >= n) sc4[i] = kNegInf;
                 mx = fmaxf(mx, sc4[i]);
             }
             const float mn = fmaxf(st.m[g], mx);
@@ -640,7 +652,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     __shared__ __attribute__((aligned(16))) _Float16 qrow_sh[GT > 8 ? GT : 8][kQRow];
     __shared__ float qs_sh[RR];
     __shared__ uint32_t coarse_sh[256];
-    __shared__ uint32_t s_cnt[NW], s_w[NW], s_res[2], s_T[2], s_base, s_nsel, s_big, s_n, s_off, s_flag, s_ok, s_failed;
+    __shared__ uint32_t s_cnt[NW], s_w[NW], s_res[2], s_T[2], s_base, s_nsel, s_n, s_off, s_ready, s_flag, s_ok, s_failed;
     __shared__ float red_ml[2 * NW][2];
     __shared__ __attribute__((aligned(16))) float sc_sh[kMatrix ? NW : 1][16];
 
@@ -665,7 +677,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         float *ou = a.out + (size_t)u * a.G * kD;
         for (int i = tid; i < a.G * kD; i += WGT) ou[i] = __builtin_nanf("");
     };
-    if (tid == 0) s_failed = 0u;
+    if (tid == 0) s_failed = s_ready = 0u;
 
     // ---- 1. scores
     // token of key i (from t0), see LabelRows
@@ -843,11 +855,9 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         __syncthreads();
         if (wave == 0) {
             // lane l owns the coarse bins 255 - 4 l .. 252 - 4 l, from the top
-            auto find = [&](const uint32_t (&cc)[4], uint32_t want, uint32_t &bin, uint32_t &rank, uint32_t &count, uint32_t &total) {
-                const uint32_t sum = cc[0] + cc[1] + cc[2] + cc[3];
-                const uint32_t incl = (uint32_t)wave_inclusive_scan((int)sum, lane);
-                total = read_lane(incl, 63);
-                uint32_t before = incl - sum, at = 0, n = 0, bef = 0;
+            auto scan = [&](const uint32_t (&cc)[4]) { return (uint32_t)wave_inclusive_scan((int)((cc[0] + cc[1]) + (cc[2] + cc[3])), lane); };
+            auto find = [&](const uint32_t (&cc)[4], uint32_t incl, uint32_t want, uint32_t &bin, uint32_t &rank, uint32_t &count) {
+                uint32_t before = incl - ((cc[0] + cc[1]) + (cc[2] + cc[3])), at = 0, n = 0, bef = 0;
                 bool done = false;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -870,10 +880,10 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
             {
                 uint32_t k_loc = (uint32_t)(((unsigned long long)a.k_eff * (uint32_t)n_tok + (uint32_t)a.L - 1u) / (uint32_t)a.L);
                 k_loc = min(max(k_loc, 1u), (uint32_t)n_tok);
-                uint32_t cc[4], bin, rank, count, total;
+                uint32_t cc[4], bin, rank, count;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) cc[i] = coarse_sh[255 - 4 * lane - i];
-                find(cc, k_loc, bin, rank, count, total);
+                find(cc, scan(cc), k_loc, bin, rank, count);
                 cb0 = min(max(bin, 1u) - 1u, 253u);  // fine bins of the coarse bins cb0 .. cb0 + 2
                 if (lane < 48) {
                     const uint32_t x = pool[cb0 * 16 + lane];
@@ -891,11 +901,12 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
                 const uint2 hi2 = ld_dev(reinterpret_cast<const uint2 *>(cuh + 254 - 4 * lane));
                 const uint2 lo2 = ld_dev(reinterpret_cast<const uint2 *>(cuh + 252 - 4 * lane));
                 const uint32_t cc[4] = {hi2.y, hi2.x, lo2.y, lo2.x};
-                uint32_t cb, rank, count, total;
-                find(cc, (uint32_t)a.k_eff, cb, rank, count, total);
-                // lane i < 16: the coarse bin's i-th fine count from the top
-                uint32_t f = 0;
-                if (total == (uint32_t)a.L) {
+                const uint32_t incl_c = scan(cc);
+                if (read_lane(incl_c, 63) == (uint32_t)a.L) {
+                    uint32_t cb, rank, count;
+                    find(cc, incl_c, (uint32_t)a.k_eff, cb, rank, count);
+                    // lane i < 16: the coarse bin's i-th fine count from the top
+                    uint32_t f;
                     if (cb - cb0 < 3u) {
                         f = (uint32_t)__shfl((int)fv, (int)((cb - cb0) * 16u) + 15 - (lane & 15));
                     } else {
@@ -906,15 +917,15 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
                         extra = cb;
                         f = ld_dev(hu + cb * 16 + 15 - (lane & 15));
                     }
-                }
-                if (lane >= 16) f = 0u;
-                const uint32_t incl = (uint32_t)wave_inclusive_scan((int)f, lane);
-                const unsigned long long hit = __ballot(lane < 16 && incl - f < rank && incl >= rank);
-                if (total == (uint32_t)a.L && read_lane(incl, 63) == count && hit) {
-                    const int l = __builtin_ctzll(hit);
-                    bin = cb * 16u + 15u - (uint32_t)l;
-                    rk = rank - read_lane(incl - f, l);
-                    break;
+                    if (lane >= 16) f = 0u;
+                    const uint32_t incl = (uint32_t)wave_inclusive_scan((int)f, lane);
+                    const unsigned long long hit = __ballot(lane < 16 && incl - f < rank && incl >= rank);
+                    if (read_lane(incl, 63) == count && hit) {
+                        const int l = __builtin_ctzll(hit);
+                        bin = cb * 16u + 15u - (uint32_t)l;
+                        rk = rank - read_lane(incl - f, l);
+                        break;
+                    }
                 }
                 // (counts that never add up: a workspace that was not cleared, or adds that do not arrive)
                 if (attempt + 1u >= a.spin_limit) {
@@ -1096,7 +1107,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         uint32_t n_sel = 0;
         if (!big) {
             own.each([&](uint2 e, bool have) {
-                const bool hit = have && is_selected(e.x, (int)e.y, T, tcut);
+                const bool hit = have && e.y - (uint32_t)t0 < (uint32_t)n_tok && is_selected(e.x, (int)e.y, T, tcut);
                 const unsigned long long hm = __ballot(hit);
                 if (hm) {
                     if (hit) sel[n_def + (int)n_sel + (int)bits_below(hm)] = (uint16_t)(e.y - (uint32_t)t0);
@@ -1106,9 +1117,28 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         }
         if (lane == 0) {
             s_nsel = n_sel;
-            s_big = big ? 1u : 0u;
             s_n = n;
             s_off = off;
+            __hip_atomic_store(&s_ready, big ? 2u : 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        DS_TR(5);
+        if (a.idx_out && !big) {
+            // the chunk's slice of the index list, in token order: the row list as a bit mask (where the
+            // candidates were), its set bits counted; a lane takes consecutive words of it
+            uint32_t *words = reinterpret_cast<uint32_t *>(cand_sh);
+            int32_t *io = a.idx_out + (size_t)u * a.k;
+            const int n_words = (n_tok + 31) >> 5, per = (n_words + 63) >> 6, n_rows = n_def + (int)n_sel;
+            wave_lds_sync();
+            for (int i = lane; i < n_words; i += 64) words[i] = 0u;
+            wave_lds_sync();
+            for (int i = lane; i < n_rows; i += 64) atomicOr(&words[sel[i] >> 5], 1u << (sel[i] & 31));
+            wave_lds_sync();
+            uint32_t mine = 0;
+            for (int i = lane * per; i < min(n_words, (lane + 1) * per); ++i) mine += (uint32_t)__builtin_popcount(words[i]);
+            uint32_t at = off + (uint32_t)wave_inclusive_scan((int)mine, lane) - mine;
+            for (int i = lane * per; i < min(n_words, (lane + 1) * per); ++i)
+                for (uint32_t w = words[i]; w; w &= w - 1u, ++at)
+                    if (at < (uint32_t)a.k_eff) io[at] = t0 + i * 32 + __builtin_ctz(w);
         }
     } else {
         DS_PRIO(0);
@@ -1116,8 +1146,12 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         DS_TR1(8);
         DS_PRIO(3);
     }
-    __syncthreads();
-    if (s_big) {
+    // (no barrier: a wavefront goes on as soon as the list is complete; what is already on its way stays so)
+    uint32_t ready;
+    while ((ready = __hip_atomic_load(&s_ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == 0u) __builtin_amdgcn_s_sleep(1);
+    ready = (uint32_t)__builtin_amdgcn_readfirstlane((int)ready);
+    if (ready == 2u) {
+        __syncthreads();
         // (thousands of candidates, or dozens of equal ones: all wavefronts together)
         uint32_t T, n_sel = 0, total;
         int tcut;
@@ -1136,35 +1170,34 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         }
         for (uint32_t i0 = 0; i0 < n_cand; i0 += WGT) {
             const uint2 e = own_cand(min(i0 + (uint32_t)tid, n_cand - 1u));
-            const bool hit = i0 + (uint32_t)tid < n_cand && is_selected(e.x, (int)e.y, T, tcut);
+            const bool hit = i0 + (uint32_t)tid < n_cand && e.y - (uint32_t)t0 < (uint32_t)n_tok && is_selected(e.x, (int)e.y, T, tcut);
             const uint32_t ex = block_exclusive_scan<NW>(hit ? 1u : 0u, s_w, &total);
             if (hit) sel[n_def + (int)(n_sel + ex)] = (uint16_t)(e.y - (uint32_t)t0);
             n_sel += total;
         }
         if (tid == 0) s_nsel = n_sel;
         __syncthreads();
+        if (a.idx_out) {
+            const uint32_t off = s_off;
+            const int n_rows = n_def + (int)n_sel;
+            int32_t *io = a.idx_out + (size_t)u * a.k;
+            const int n_words = (n_tok + 31) >> 5;  // <= WGT
+            for (int i = tid; i < n_words; i += WGT) pool[i] = 0u;
+            __syncthreads();
+            for (int i = tid; i < n_rows; i += WGT) atomicOr(&pool[sel[i] >> 5], 1u << (sel[i] & 31));
+            __syncthreads();
+            uint32_t w = tid < n_words ? pool[tid] : 0u, total;
+            uint32_t at = off + block_exclusive_scan<NW>((uint32_t)__builtin_popcount(w), s_w, &total);
+            for (; w; w &= w - 1u, ++at)
+                if (at < (uint32_t)a.k_eff) io[at] = t0 + tid * 32 + __builtin_ctz(w);
+            __syncthreads();
+        }
     }
     const int n_rows = n_def + (int)s_nsel;
-    DS_TR(5);
+    if (a.idx_out && c == 0 && wave == 0)
+        for (int i = a.k_eff + lane; i < a.k; i += 64) a.idx_out[(size_t)u * a.k + i] = -1;
 
     // ---- 5. the other rows; partial.  (Groups of more than GT heads pass over the rows again.)
-    if (a.idx_out) {
-        // the chunk's slice of the index list, in token order: the row list as a bit mask, its set bits counted
-        const uint32_t off = s_off;
-        int32_t *io = a.idx_out + (size_t)u * a.k;
-        const int n_words = (n_tok + 31) >> 5;  // <= WGT
-        for (int i = tid; i < n_words; i += WGT) pool[i] = 0u;
-        __syncthreads();
-        for (int i = tid; i < n_rows; i += WGT) atomicOr(&pool[sel[i] >> 5], 1u << (sel[i] & 31));
-        __syncthreads();
-        uint32_t w = tid < n_words ? pool[tid] : 0u, total;
-        uint32_t at = off + block_exclusive_scan<NW>((uint32_t)__builtin_popcount(w), s_w, &total);
-        for (; w; w &= w - 1u, ++at)
-            if (at < (uint32_t)a.k_eff) io[at] = t0 + tid * 32 + __builtin_ctz(w);
-        if (c == 0)
-            for (int i = a.k_eff + tid; i < a.k; i += WGT) io[i] = -1;
-        __syncthreads();
-    }
     for (int g0 = 0; g0 < a.G; g0 += GT) {
         const int n_heads = min(GT, a.G - g0);
         if (g0) {
@@ -1224,12 +1257,11 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
 // The decode kernel.  Four wavefronts per SIMD are what the plans count on (two workgroups of 512 threads
 // to a compute unit, 128 registers); groups of more than eight heads need more, and get three (one workgroup of
 // 512 threads, or three of 256).
-template <int GT, int SMODE, int THREADS, bool ST>
-__global__ __launch_bounds__(THREADS, GT > 8 ? 3 : 4) void k_refine_attend(AttendArgs a)
+// FORM: 10 wavefronts + rows of a 16-lane slot in flight, two or four (single heads and pairs).
+template <int GT, int SMODE, int FORM, bool ST>
+__global__ __launch_bounds__(FORM / 10 * 64, GT > 8 ? 3 : 4) void k_refine_attend(AttendArgs a)
 {
-    // rows of a 16-lane slot in flight (single heads and pairs): two; on a mostly idle device, where a
-    // round trip is all that a round costs, two rounds of two
-    decode_unit<GT, SMODE, THREADS / 64, ST, 2, (ST ? 1 : 2)>(a);
+    decode_unit<GT, SMODE, FORM / 10, ST, 2, FORM % 10 / 2>(a);
 }
 
 // The instantiation for labels of this kind (see ra_kernel).
@@ -1242,31 +1274,33 @@ int trace_read(void *dst, size_t bytes);
 #endif
 
 // Defines them for heads per pass GT, in a source file of its own each (they compile side by side).
-template <int GT, int THREADS, bool ST>
+template <int GT, int FORM, bool ST>
 static RaFn decode_fn_of(int smode)
 {
     switch (smode) {
-    case 0: return k_refine_attend<GT, 0, THREADS, ST>;
-    case 4: return k_refine_attend<GT, 4, THREADS, ST>;
-    case 8: return k_refine_attend<GT, 8, THREADS, ST>;
-    case 12: return k_refine_attend<GT, 12, THREADS, ST>;
-    case 16: return k_refine_attend<GT, 16, THREADS, ST>;
-    case 20: return k_refine_attend<GT, 20, THREADS, ST>;
-    case 24: return k_refine_attend<GT, 24, THREADS, ST>;
-    case 28: return k_refine_attend<GT, 28, THREADS, ST>;
-    case 32: return k_refine_attend<GT, 32, THREADS, ST>;
-    case -8: return k_refine_attend<GT, -8, THREADS, ST>;
-    default: return k_refine_attend<GT, -16, THREADS, ST>;
+    case 0: return k_refine_attend<GT, 0, FORM, ST>;
+    case 4: return k_refine_attend<GT, 4, FORM, ST>;
+    case 8: return k_refine_attend<GT, 8, FORM, ST>;
+    case 12: return k_refine_attend<GT, 12, FORM, ST>;
+    case 16: return k_refine_attend<GT, 16, FORM, ST>;
+    case 20: return k_refine_attend<GT, 20, FORM, ST>;
+    case 24: return k_refine_attend<GT, 24, FORM, ST>;
+    case 28: return k_refine_attend<GT, 28, FORM, ST>;
+    case 32: return k_refine_attend<GT, 32, FORM, ST>;
+    case -8: return k_refine_attend<GT, -8, FORM, ST>;
+    default: return k_refine_attend<GT, -16, FORM, ST>;
     }
 }
 #define DS_DEFINE_DECODE_FN(GT)                                                                       \
     template <>                                                                                       \
     RaFn decode_fn<GT>(int smode, DecodeVariant v)                                                    \
     {                                                                                                 \
-        if (v == DECODE_NARROW) return decode_fn_of<GT, 256, true>(smode);                            \
-        if constexpr (GT <= 2)                                                                        \
-            if (v == DECODE_LIGHT) return decode_fn_of<GT, 512, false>(smode);                        \
-        return decode_fn_of<GT, 512, true>(smode);                                                    \
+        if (v == DECODE_NARROW) return decode_fn_of<GT, 42, true>(smode);                             \
+        if constexpr (GT <= 2) {                                                                      \
+            if (v == DECODE_LIGHT) return decode_fn_of<GT, 84, false>(smode);                         \
+            if (v == DECODE_DEEP) return decode_fn_of<GT, 84, true>(smode);                           \
+        }                                                                                             \
+        return decode_fn_of<GT, 82, true>(smode);                                                     \
     }
 #ifdef DS_TRACE
 #define DS_DEFINE_TRACE_READ(GT)                                                                      \

@@ -144,10 +144,12 @@ hipError_t launch_attend_sparse(const void *q, const void *K, const void *V, voi
 constexpr bool attend_scores_r(int r) { return r % 4 == 0 && r <= 32; }
 constexpr int kDecodeTokens = 16384;  // tokens of a workgroup at most: 32 a thread of 512
 bool refine_attend_ok(const Plan &p, bool scores_itself);
-// Variants of the kernel: 512 threads; the same without the streaming mark and with
-// more rows in flight (a mostly idle device); 256 threads.
-enum DecodeVariant { DECODE_WIDE = 0, DECODE_LIGHT = 1, DECODE_NARROW = 2 };
-DecodeVariant decode_variant(const Plan &p, bool streams);
+// Variants of the kernel: 512 threads; the same with twice the rows in flight (a mostly idle device), and
+// without the streaming mark besides (calls of a few MiB); 256 threads.
+enum DecodeVariant { DECODE_WIDE, DECODE_DEEP, DECODE_LIGHT, DECODE_NARROW };
+DecodeVariant decode_variant(const Plan &p, const ds_shape_t &s);
+size_t decode_bytes(const Plan &p, const ds_shape_t &s);  // label and K/V rows that a sparse decode call reads
+constexpr size_t kStreamBytes = 16u << 20;                // from here on they are marked as streaming
 // Returned by launch_refine_attend (nothing enqueued) when the launch would wait for workgroups
 // that the device cannot hold at the same time as the waiting ones.
 constexpr hipError_t kNotResident = hipErrorLaunchOutOfResources;

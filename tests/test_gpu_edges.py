@@ -380,6 +380,54 @@ def test_decode_many_candidates(Hq, L, k, step, one):
     full_parity(case, what=f"many candidates L{L} k{k}")
 
 
+@pytest.mark.parametrize("Hq,Hkv,L,r,k,cus,scores", [
+    # end bins: scores far below and far above the label query's size all fall into one bin
+    (1, 1, 3000, 8, 187, 0, "tiny"), (2, 1, 12000, 16, 750, 0, "tiny"), (4, 1, 9000, 12, 563, 0, "tiny"),
+    (1, 1, 3000, 8, 187, 0, "huge"), (3, 1, 9000, 8, 563, 0, "huge"), (1, 1, 12000, 4, 750, 0, "huge"),
+    # thresholds on the negative side, and at either end of the list
+    (1, 1, 4097, 8, 256, 0, "negative"), (2, 1, 9001, 8, 562, 0, "negative"), (8, 1, 20000, 8, 1250, 0, "negative"),
+    (1, 1, 4096, 8, 2900, 0, "plain"), (1, 1, 20000, 8, 19999, 0, "plain"), (4, 1, 9000, 8, 1, 0, "plain"),
+    # most tokens of a unit in one chunk of it
+    (1, 1, 40000, 8, 2500, 0, "front"), (7, 1, 30000, 12, 1875, 0, "front"), (1, 1, 40000, 8, 20000, 0, "front"),
+    # one workgroup of 16384 tokens, 32 keys to a thread: its edges (planned for eight compute units)
+    (6, 6, 16384, 8, 1024, 8, "plain"), (6, 6, 16383, 4, 1024, 8, "plain"), (24, 6, 16384, 8, 1024, 8, "plain"),
+    (24, 6, 8193, 16, 512, 8, "plain"), (30, 6, 15873, 8, 900, 8, "negative"),
+    # 256 threads: more units than two to a compute unit (groups of more than eight heads: than one)
+    (17, 17, 300, 8, 19, 8, "plain"), (34, 17, 8192, 8, 300, 8, "plain"), (68, 17, 513, 24, 32, 8, "plain"),
+    (180, 9, 700, 8, 44, 8, "plain"), (17, 17, 2048, 8, 1500, 8, "tiny"),
+    # groups of more than eight and of more than sixteen heads, one and several workgroups per unit
+    (9, 1, 2000, 8, 125, 0, "plain"), (16, 1, 17000, 8, 1062, 0, "plain"), (33, 1, 9000, 8, 562, 0, "plain"),
+    (40, 2, 1000, 32, 62, 0, "negative"),
+    # more rows in flight: 36 MiB by units for a quarter of the device
+    (64, 64, 6144, 32, 384, 0, "plain"),
+])
+def test_decode_bins_lists_and_variants(Hq, Hkv, L, r, k, cus, scores):
+    """The decode launch at the edges of its first-level bins (16 octaves of either sign around the
+    label query's largest value, the rest in the end bins), of its candidate lists and of the rules
+    that choose its form: index lists equal to the oracle's, outputs within the parity bounds."""
+    t = make_layer_numpy(Workload("t", 1, Hq, Hkv, 128, L, r, k, 1))
+    ch = rand_channels(Hkv, r, seed=L + r)
+    rng = np.random.default_rng(L + k)
+    if scores != "plain":
+        for h in range(Hkv):
+            x = np.abs(rng.standard_normal((L, r)))
+            scale = {"tiny": 1e-6, "huge": 2e4, "negative": -1.0, "front": 1.0}[scores]
+            if scores == "front":
+                x[L // 5:] -= 4.0
+            t["K"][0, h][:, ch[h]] = np.clip(x * scale, -6e4, 6e4).astype(np.float16)
+            t["q"].reshape(1, Hkv, Hq // Hkv, 128)[0, h][:, ch[h]] = np.float16(0.01 if scores == "huge" else 0.5)
+    if cus:
+        ds.ds_pretend_device(cus, 8, 160 << 10)
+    try:
+        plan = ds.ds_plan_describe(ds.shape(1, Hq, Hkv, 128, L, L, r, k))
+        assert plan["scores_itself"] == 1
+        if cus:
+            assert plan["workgroups_per_unit"] == 1
+        full_parity(Case(t["q"], t["K"], t["V"], ch, L, k), what=f"Hq{Hq} Hkv{Hkv} L{L} r{r} k{k} {scores}")
+    finally:
+        ds.ds_pretend_device(0, 0, 0)
+
+
 @pytest.mark.parametrize("n,r,inter", [(1, 8, False), (1, 3, True), (15, 24, False), (16, 8, True), (17, 128, False), (40, 12, False)])
 def test_append_kv_equals_the_cache_built_in_one_go(n, r, inter):
     """Rows and label values of n new tokens, below, at and above the 16 that a workgroup takes at a time."""

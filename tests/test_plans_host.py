@@ -177,3 +177,42 @@ def test_chunks_behind_a_scoring_launch_fit_at_once(units, G, L, chunk):
         p = ds.ds_plan_describe(ds.shape(1, units * G, units, 128, L, L, r, L // 16), kind)
         assert p["scores_itself"] == 0 and p["tokens_per_workgroup"] == chunk
         assert p["workgroups"] <= 4 * 256 or chunk == 4096
+
+
+@pytest.mark.parametrize("units,G,L,r,lo,hi", [
+    # (units, heads per unit, tokens, channels, workgroups per unit within a few percent of the fastest measured)
+    (32, 1, 65536, 8, 7, 8), (32, 1, 262144, 8, 16, 16), (128, 1, 32768, 8, 4, 4), (64, 1, 16384, 8, 4, 4),
+    (32, 1, 16384, 8, 6, 8), (32, 1, 8192, 8, 3, 6), (1, 1, 262144, 8, 25, 64), (96, 1, 30000, 8, 4, 5),
+    (12, 7, 20011, 12, 6, 12), (8, 8, 131072, 8, 14, 26), (128, 8, 32768, 8, 2, 4), (32, 8, 65536, 8, 8, 16),
+    # one workgroup per unit, or several
+    (192, 4, 9000, 8, 1, 1), (192, 8, 16384, 16, 1, 1), (191, 4, 9000, 8, 2, 4), (192, 4, 16385, 8, 2, 4),
+    (192, 1, 16384, 8, 1, 1), (192, 1, 16385, 8, 2, 4), (1024, 8, 12000, 8, 1, 1),
+])
+def test_chunks_of_a_launch_that_scores_itself(units, G, L, r, lo, hi):
+    """Workgroups per unit of the decode launch; several of them are resident at once, and none has
+    more than 16384 tokens."""
+    p = ds.ds_plan_describe(ds.shape(1, units * G, units, 128, L, L, r, L // 16))
+    n, ch, launches = p["workgroups_per_unit"], p["tokens_per_workgroup"], p["launches_planned"]
+    assert p["scores_itself"] == 1 and lo <= n <= hi and ch <= 16384 and (n - 1) * ch < L <= n * ch
+    assert n == 1 or -(-units // launches) * n <= 2 * 256
+
+
+@pytest.mark.parametrize("units,G,L,r,kind", [
+    (32, 1, 65536, 8, 0), (12, 7, 20011, 12, 0), (5, 16, 40000, 32, 0), (300, 2, 20000, 4, 0), (700, 4, 20000, 8, 2),
+    (1, 1, 1000000, 8, 0), (2, 33, 100000, 16, 2), (200, 1, 100000, 24, 0),
+])
+def test_decode_plans_of_every_device_size_are_within_bounds(units, G, L, r, kind):
+    """On devices of 8 to 256 compute units: chunks cover the tokens, fit the kernels, and are no more
+    than the workspace has partials for."""
+    for cus in (8, 64, 120, 256):
+        ds.ds_pretend_device(cus, 8, 160 << 10)
+        shp = ds.shape(1, units * G, units, 128, L, (L + 3) // 4 * 4, r, L // 16)
+        p = ds.ds_plan_describe(shp, kind)
+        n, ch = p["workgroups_per_unit"], p["tokens_per_workgroup"]
+        assert (n - 1) * ch < L <= n * ch and ch % 4 == 0
+        prefix = units * (64 + 4096 * 4 + 256 * 4 + 4 * ((L + 3) // 4) * 4 + 8 * L)
+        assert prefix + units * G * n * 132 * 4 <= ds.ds_workspace_bytes(shp)
+        if p["scores_itself"]:
+            assert ch <= 16384 and p["launches_planned"] <= 3
+            per_cu = 1 if cus < 128 else 3 if G > 8 else 2
+            assert n == 1 or -(-units // p["launches_planned"]) * n <= per_cu * cus
