@@ -878,6 +878,7 @@ hipError_t launch_refine_attend(const void *q, const void *K, const void *V, voi
     a.coarse = reinterpret_cast<uint32_t *>(wsp(ws, p.off_coarse));
     a.amax = amax;
     a.r = s.r;
+    a.k_share = (float)p.k_eff / (float)s.L;
     a.keys_in_lds = keys_in_lds(p);
     const int smode = ra_smode(s, score_label != nullptr, amax != nullptr);
     if (score_label && smode == 0) return hipErrorInvalidValue;

@@ -160,11 +160,11 @@ __device__ __forceinline__ bool wave_settle(Held &c, uint32_t krem, uint32_t lo_
         wave_lds_sync();
         if (lane < m) mine = small[lane];
     }
+    // (key and inverted token as one number: sorts before <=> larger)
+    const unsigned long long me = (unsigned long long)mine.x << 32 | (0xffffffffu - mine.y);
     uint32_t before = 0;
-    for (uint32_t j = 0; j < m; ++j) {
-        const uint32_t ox = read_lane(mine.x, (int)j), oy = read_lane(mine.y, (int)j);
-        before += (ox > mine.x || (ox == mine.x && oy < mine.y)) ? 1u : 0u;
-    }
+    for (uint32_t j = 0; j < m; ++j)
+        before += ((unsigned long long)read_lane((uint32_t)(me >> 32), (int)j) << 32 | read_lane((uint32_t)me, (int)j)) > me ? 1u : 0u;
     const unsigned long long hit = __ballot(lane < m && before + 1u == krem);
     if (hit == 0ull) return false;
     const int l = __builtin_ctzll(hit);
@@ -542,14 +542,19 @@ __device__ __forceinline__ void merge_unit(const float *part_unit, int G, int n_
 }
 
 // The wavefronts' states of n_heads heads in wpart[wave][head] = {m, l, -, -, acc[128]} merged in wave
-// order, 128 threads a head: the result to out_direct, or the workgroup's partial to po.
+// order: the result to out_direct, or the workgroup's partial to po.  128 threads a head where that takes one
+// round of heads, else 32 threads a head, four channels each (the quotients are what costs: with 32 threads
+// one layer of 4K tokens 8.83 -> 8.99 us, with 128 eight units of 32K in groups of 8 18.9 -> 19.4).
 template <int GH, int NW>
 __device__ __forceinline__ void combine_waves(const float (*wpart)[GH][kPartStride], int n_heads, float *po, size_t head_stride,
                                               float *out_direct)
 {
-    const int d = threadIdx.x & (kD - 1);
-    for (int g = threadIdx.x >> 7; g < n_heads; g += NW / 2) {
-        float mw[NW], M = kNegInf, A = 0.0f, Ls = 0.0f;
+    constexpr int CH = GH <= NW / 2 ? 1 : 4, TPH = kD / CH;  // channels of a thread, threads of a head
+    const int d = (threadIdx.x % TPH) * CH;
+    for (int g = threadIdx.x / TPH; g < n_heads; g += 64 * NW / TPH) {
+        float mw[NW], M = kNegInf, Ls = 0.0f, A[CH];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) A[c] = 0.0f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             mw[w] = wpart[w][g][0];
@@ -558,18 +563,23 @@ __device__ __forceinline__ void combine_waves(const float (*wpart)[GH][kPartStri
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
             const float f = (mw[w] == kNegInf) ? 0.0f : __builtin_amdgcn_exp2f(mw[w] - M);
-            A += f * wpart[w][g][4 + d];
+#pragma unroll
+            for (int c = 0; c < CH; ++c) A[c] += f * wpart[w][g][4 + d + c];
             Ls += f * wpart[w][g][1];
         }
         if (out_direct) {
-            out_direct[(size_t)g * kD + d] = A / Ls;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) out_direct[(size_t)g * kD + d + c] = A[c] / Ls;
         } else {
             float *pg = po + (size_t)g * head_stride;
-            st_dev(pg + 4 + d, A);
-            if (d == 0) {
-                st_dev(pg + 0, M);
-                st_dev(pg + 1, Ls);
+            if constexpr (CH == 1) {
+                st_dev(pg + 4 + d, A[0]);
+            } else {
+#pragma unroll
+                for (int c = 0; c < CH; c += 2)
+                    st_dev(reinterpret_cast<uint2 *>(pg + 4 + d + c), make_uint2(__float_as_uint(A[c]), __float_as_uint(A[c + 1])));
             }
+            if (d == 0) st_dev(reinterpret_cast<uint2 *>(pg), make_uint2(__float_as_uint(M), __float_as_uint(Ls)));
         }
     }
 }
@@ -650,7 +660,6 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     __shared__ __attribute__((aligned(16))) uint32_t pool[kPool];
     __shared__ __attribute__((aligned(16))) uint2 cand_sh[kCandLds], small_sh[64];
     __shared__ __attribute__((aligned(16))) _Float16 qrow_sh[GT > 8 ? GT : 8][kQRow];
-    __shared__ float qs_sh[RR];
     __shared__ uint32_t coarse_sh[256];
     __shared__ uint32_t s_cnt[NW], s_w[NW], s_res[2], s_T[2], s_base, s_nsel, s_n, s_off, s_ready, s_flag, s_ok, s_failed;
     __shared__ float red_ml[2 * NW][2];
@@ -659,7 +668,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int u = blockIdx.y + a.unit0, c = blockIdx.x;
-    const int b = u / a.Hkv, hk = u % a.Hkv;
+    const int hk = u % a.Hkv;
     const int t0 = c * a.ch, n_tok = min(a.L, t0 + a.ch) - t0;
     const bool single = gridDim.x == 1;
     uint2 *cu = a.cand + (size_t)u * a.L;
@@ -716,9 +725,18 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         }
     };
     // label query of the group; the first two batches of label rows are on their way meanwhile
-    int c_q = 0;
-    if (tid < a.r) c_q = a.channels[hk * a.r + tid];
-    float a_q = 0.0f;
+    // (every wavefront forms it for itself, a channel to a lane: one barrier less than by one of them)
+    constexpr int QL = (RR + 63) / 64;
+    const bool scaled = LR::kQ4 || (LR::kKeysGiven && a.amax);
+    int c_q[QL];
+    float a_q[QL], step[QL];
+#pragma unroll
+    for (int x = 0; x < QL; ++x) {
+        const int j = lane + 64 * x;
+        c_q[x] = j < a.r ? a.channels[hk * a.r + j] : 0;
+        step[x] = scaled && j < a.r ? a.amax[(size_t)u * a.r + j] : 0.0f;
+        a_q[x] = 0.0f;
+    }
     for (int g0 = 0; g0 < a.G; g0 += 8) {
         const int ng = min(8, a.G - g0);
         if (g0) __syncthreads();
@@ -726,7 +744,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         const int qg = (tid - 128) >> 4, qp = (tid - 128) & 15;
         const bool has_q = tid >= 128 && tid < 256;  // (rows that there are not: zeros)
         if (has_q && qg < ng)
-            qv = *reinterpret_cast<const uint4 *>(a.q + ((size_t)b * a.Hq + (size_t)hk * a.G + g0 + qg) * kD + qp * 8);
+            qv = *reinterpret_cast<const uint4 *>(a.q + ((size_t)u * a.G + g0 + qg) * kD + qp * 8);
         if (g0 == 0) {
             // (no wavefront's label loads before the query's: they share one queue)
             __builtin_amdgcn_s_barrier();
@@ -739,25 +757,31 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         }
         if (has_q) *reinterpret_cast<uint4 *>(&qrow_sh[qg][qp * 8]) = qv;
         __syncthreads();
-        if (tid < a.r)
-            for (int g = 0; g < ng; ++g) a_q = a_q + (float)qrow_sh[g][c_q];
+#pragma unroll
+        for (int x = 0; x < QL; ++x) {
+            _Float16 y[8];  // (all eight on their way at once; zeros where there is no head)
+#pragma unroll
+            for (int g = 0; g < 8; ++g) y[g] = qrow_sh[g][c_q[x]];
+#pragma unroll
+            for (int g = 0; g < 8; ++g) a_q[x] = a_q[x] + (float)y[g];
+        }
     }
-    if (tid < RR) {
-        if (LR::kQ4 || (LR::kKeysGiven && a.amax)) a_q = tid < a.r ? a_q * (a.amax[(size_t)u * a.r + tid] / 7.0f) : 0.0f;
-        qs_sh[tid] = a_q;
+#pragma unroll
+    for (int x = 0; x < QL; ++x) {
+        if (scaled) a_q[x] = a_q[x] * (step[x] / 7.0f);
+        if (lane + 64 * x >= a.r) a_q[x] = 0.0f;
     }
-    __syncthreads();
     DS_TR(15);
     float qs[LR::kKeysGiven ? 1 : RR], magnitude = 0.0f;  // (the largest of the label query)
     if constexpr (LR::kKeysGiven) {
-        magnitude = fmaxf(fabsf(qs_sh[lane]), fabsf(qs_sh[lane + 64]));  // (zeros beyond r)
+        magnitude = fmaxf(fabsf(a_q[0]), fabsf(a_q[QL - 1]));
 #pragma unroll
         for (int m = 1; m < 16; m *= 2) magnitude = fmaxf(magnitude, __shfl_xor(magnitude, m));
         magnitude = rows_max(magnitude);
     } else {
 #pragma unroll
         for (int j = 0; j < RR; ++j) {
-            qs[j] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qs_sh[j])));
+            qs[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(a_q[0]), j));
             magnitude = fmaxf(magnitude, fabsf(qs[j]));
         }
     }
@@ -878,8 +902,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
             };
             uint32_t cb0;
             {
-                uint32_t k_loc = (uint32_t)(((unsigned long long)a.k_eff * (uint32_t)n_tok + (uint32_t)a.L - 1u) / (uint32_t)a.L);
-                k_loc = min(max(k_loc, 1u), (uint32_t)n_tok);
+                const uint32_t k_loc = min(max((uint32_t)((float)n_tok * a.k_share), 1u), (uint32_t)n_tok);
                 uint32_t cc[4], bin, rank, count;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) cc[i] = coarse_sh[255 - 4 * lane - i];
@@ -973,7 +996,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         if (tid < 256) {
             const int g = tid >> 4, pp = tid & 15;
             uint4 x = make_uint4(0u, 0u, 0u, 0u);
-            if (g0 + g < a.G) x = *reinterpret_cast<const uint4 *>(a.q + ((size_t)b * a.Hq + (size_t)hk * a.G + g0 + g) * kD + pp * 8);
+            if (g0 + g < a.G) x = *reinterpret_cast<const uint4 *>(a.q + ((size_t)u * a.G + g0 + g) * kD + pp * 8);
             *reinterpret_cast<uint4 *>(&qrow_sh[g][pp * 8]) = x;
         }
     };

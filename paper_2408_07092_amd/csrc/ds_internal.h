@@ -27,16 +27,15 @@ struct UnitCtl {
     uint32_t ncand;     // k_cand: candidates appended so far (keys in bin bstar)
     uint32_t T;         // k_cand / k_score's tail: exact k-th largest key
     int32_t tcut;       // keys equal to T are selected iff token <= tcut
-    uint32_t arrive_a;  // workgroups that have added their chunk histogram to the unit's (k_score, or
-                        // k_refine_attend when it scores itself)
+    uint32_t arrive_a;  // k_score: workgroups that have added their chunk histogram to the unit's
     uint32_t arrive_b;  // workgroups of k_cand that finished this unit
-    uint32_t arrive_c;  // workgroups of an attention kernel whose partial is written (k_refine_attend:
-                        // the high half counts those whose wait for another workgroup ran out)
-    uint32_t cnt_a;     // k_refine_attend: the exact threshold as published by the workgroup that
+    uint32_t arrive_c;  // workgroups of an attention kernel whose partial is written (the high half counts
+                        // those whose wait for another workgroup ran out)
+    uint32_t cnt_a;     // k_attend_behind_scoring: the exact threshold as published by the workgroup that
     uint32_t cnt_b;     //   settled it, one 64-bit word {T, tie cut | 1 << 31}
     uint32_t cnt_c;
     uint32_t err;       // non-zero once a bounded wait between workgroups gave up (the first code stays)
-    uint32_t pad[4];    // pad[2..3]: k_refine_attend's 64-bit counter {candidates so far, arrivals << 32}
+    uint32_t pad[4];    // pad[2..3]: the decode kernels' 64-bit counter {candidates so far, arrivals << 32}
 };
 static_assert(sizeof(UnitCtl) == 64, "UnitCtl is one 64-byte record");
 
