@@ -197,7 +197,8 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
     // the workspace is cleared) and the workgroup remembers it for its last arrival, so that the
     // workgroup that would merge the unit writes NaN instead.  A unit whose word is up when the
     // launch starts is not computed at all: its output is NaN again.
-    __shared__ uint32_t s_failed;
+    // (One thread reads the word, which can go up at any time, and the whole workgroup goes by that copy.)
+    __shared__ uint32_t s_failed, s_sticky;
     auto raise_err = [&](uint32_t code) {
         uint32_t none = 0u;  // (the unit's first code stays)
         __hip_atomic_compare_exchange_strong(&ctl->err, &none, code, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -208,10 +209,9 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
         float *ou = a.out + (size_t)u * a.G * kD;
         for (int i = tid; i < a.G * kD; i += WGT) ou[i] = __builtin_nanf("");
     };
-    if (tid == 0) s_failed = 0u;
-    if (a.ctl[u].err != 0u) {
-        if (c == 0) poison_out();
-        return;
+    if (tid == 0) {
+        s_failed = 0u;
+        s_sticky = a.ctl[u].err;
     }
 
     if constexpr (GT <= 2) {
@@ -258,6 +258,10 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
     auto key_slot = [&](int j) { return ((j >> 2) * WGT + tid) * 4 + (j & 3); };
     uint32_t mdef[2] = {0u, 0u}, mcan[2] = {0u, 0u};
     __syncthreads();  // the keys were stored by other threads
+    if (s_sticky != 0u) {
+        if (c == 0) poison_out();
+        return;
+    }
     {
         // Two groups are read at a time, whatever lies past the chunk's end among them, and the
         // masks cut to the chunk afterwards: no bounds in the loop, 32-bit masks at fixed places.

@@ -661,7 +661,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     __shared__ __attribute__((aligned(16))) uint2 cand_sh[kCandLds], small_sh[64];
     __shared__ __attribute__((aligned(16))) _Float16 qrow_sh[GT > 8 ? GT : 8][kQRow];
     __shared__ uint32_t coarse_sh[256];
-    __shared__ uint32_t s_cnt[NW], s_w[NW], s_res[2], s_T[2], s_base, s_nsel, s_n, s_off, s_ready, s_flag, s_ok, s_failed;
+    __shared__ uint32_t s_cnt[NW], s_w[NW], s_res[2], s_T[2], s_base, s_nsel, s_n, s_off, s_ready, s_flag, s_ok, s_failed, s_sticky;
     __shared__ float red_ml[2 * NW][2];
     __shared__ __attribute__((aligned(16))) float sc_sh[kMatrix ? NW : 1][16];
 
@@ -675,7 +675,11 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     UnitCtl *ctl = a.ctl_rw + u;
     unsigned long long *cand_arrive = reinterpret_cast<unsigned long long *>(&ctl->pad[2]);
     DS_TR(0);
-    const uint32_t sticky = a.ctl[u].err;
+    // The unit's error word, raised by an earlier call or, in this one, by a workgroup that waited in vain for one
+    // that starts late.  It can change at any time, so one thread reads it and the workgroup goes by that copy:
+    // wavefronts that left on a value of their own would leave the others with lists half made, and a flag that nobody raises.
+    uint32_t sticky = 0u;
+    if (tid == 0) sticky = a.ctl[u].err;
     auto raise_err = [&](uint32_t code) {
         uint32_t none = 0u;
         __hip_atomic_compare_exchange_strong(&ctl->err, &none, code, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
@@ -756,6 +760,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
                 reinterpret_cast<uint4 *>(pool)[i * WGT + tid] = make_uint4(0u, 0u, 0u, 0u);
         }
         if (has_q) *reinterpret_cast<uint4 *>(&qrow_sh[qg][qp * 8]) = qv;
+        if (g0 == 0 && tid == 0) s_sticky = sticky;
         __syncthreads();
 #pragma unroll
         for (int x = 0; x < QL; ++x) {
@@ -847,7 +852,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         __builtin_amdgcn_sched_barrier(0);
     }
     DS_PRIO(3);
-    if (sticky != 0u) {
+    if (s_sticky != 0u) {
         if (c == 0) poison_out();
         return;
     }
@@ -1169,7 +1174,9 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         DS_TR1(8);
         DS_PRIO(3);
     }
-    // (no barrier: a wavefront goes on as soon as the list is complete; what is already on its way stays so)
+    // (no barrier: a wavefront goes on as soon as the list is complete; what is already on its way stays so.
+    //  The flag comes: wavefront 0 is in the workgroup whenever the others are, waits for other workgroups a bounded
+    //  number of times, and raises it on every way out of them.)
     uint32_t ready;
     while ((ready = __hip_atomic_load(&s_ready, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP)) == 0u) __builtin_amdgcn_s_sleep(1);
     ready = (uint32_t)__builtin_amdgcn_readfirstlane((int)ready);

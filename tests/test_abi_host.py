@@ -2,6 +2,7 @@
 symbol the header declares, validates arguments before touching the device, and
 its offline calibration agrees with the oracle."""
 import ctypes
+import glob
 import os
 import re
 
@@ -208,3 +209,20 @@ def test_handed_over_arrays_are_never_read_with_plain_loads():
                     continue                     # a store
                 bad.append(f"{fn}:{ln}: {line.strip()}")
     assert not bad, "plain reads of in-launch hand-over arrays:\n" + "\n".join(bad)
+
+
+def test_error_words_are_read_by_one_thread_for_its_workgroup():
+    """Host only, over the kernels: a unit's error word can be raised by another workgroup at any time, so a
+    workgroup must not let each of its wavefronts act on a read of its own.  Every read is made by thread 0
+    and reaches the others through LDS."""
+    csrc = os.path.join(ROOT, "paper_2408_07092_amd", "csrc")
+    reads = 0
+    for path in sorted(glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "ds_*_core.h"))):
+        src = re.sub(r"//[^\n]*", "", open(path).read())
+        for m in re.finditer(r"(?<!&)\b(?:a\.)?ctl(?:_rw)?(?:\[\w+\]\.|->)err\b", src):
+            reads += 1
+            line = src[src.rfind("\n", 0, m.start()):m.start()]
+            block = src[src.rfind("if (tid == 0) {", 0, m.start()):m.start()]
+            in_block = block and "}" not in block and re.search(r"\bs_\w+ = $", line)
+            assert "if (tid == 0)" in line or in_block, f"{os.path.basename(path)}: {src[m.start() - 40:m.end()]!r}"
+    assert reads == 2
