@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
     uint32_t mdef[2] = {0u, 0u}, mcan[2] = {0u, 0u};
     __syncthreads();  // the keys were stored by other threads
     if (s_sticky != 0u) {
-        if (c == 0) poison_out();
+        poison_out();  // (whichever workgroup leaves here: without it none of the unit's is the last, which would write)
         return;
     }
     {

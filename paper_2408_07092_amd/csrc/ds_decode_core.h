@@ -853,7 +853,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     }
     DS_PRIO(3);
     if (s_sticky != 0u) {
-        if (c == 0) poison_out();
+        poison_out();  // (whichever workgroup leaves here: without it none of the unit's is the last, which would write)
         return;
     }
     __syncthreads();

@@ -10,7 +10,7 @@ import paper_2408_07092_amd as ds
 from oracle import ds_oracle as O
 from tests.parity_util import Case, check_output, full_parity, to_dev
 from tests.test_plans_host import q4_plan, smallest_workspace
-from workloads import Workload, make_layer_numpy
+from workloads import Workload, make_layer_numpy, make_layer_torch
 
 pytestmark = pytest.mark.gpu
 
@@ -451,3 +451,45 @@ def test_append_kv_equals_the_cache_built_in_one_go(n, r, inter):
     assert np.array_equal(label[:, :, 50:L].cpu().numpy().view(np.uint16), np.ascontiguousarray(ref[:, :, 50:L]).view(np.uint16))
     for x, v in ((Kc, 5.0), (Vc, 5.0), (label, -7.0)):
         assert (x[:, :, :50] == v).all() and (x[:, :, L:] == v).all()
+
+
+@pytest.mark.parametrize("cus,Hq,Hkv,L,r", [(2048, 40, 40, 131072, 8), (2048, 120, 40, 131072, 8), (0, 100, 100, 70000, 40)])
+def test_workgroups_that_start_late_leave_no_old_output(cus, Hq, Hkv, L, r):
+    """More workgroups than the device holds (the planner is told of a larger one) and a poll limit of
+    one: the first workgroups of a unit give up and raise its error word, others start only then and leave
+    at once.  The unit's output is all NaN then -- no number of an earlier call stays in it -- and every other
+    unit's is right."""
+    k = L // 16
+    w = Workload("t", 1, Hq, Hkv, 128, L, r, k, 1)
+    t = make_layer_torch(w, "cuda", layer=0)
+    ch = to_dev(rand_channels(Hkv, r, seed=L + r))
+    shp = ds.shape(1, Hq, Hkv, 128, L, L, r, k)
+    label = torch.empty((1, Hkv, L, r), dtype=torch.float16, device="cuda")
+    ds.ds_build_label(t["K"], ch, label, shp)
+
+    def decode(ws):
+        out = torch.full((1, Hq, 128), 7.0, dtype=torch.float32, device="cuda")
+        ds.ds_sparse_decode(t["q"], label, t["K"], t["V"], ch, out, None, ws, shp)
+        torch.cuda.synchronize()
+        return out.cpu().numpy()
+
+    good = decode(ds.ds_workspace_alloc(shp))
+    try:
+        if cus:
+            ds.ds_pretend_device(cus, 8, 160 << 10)
+        plan = ds.ds_plan_describe(shp)
+        assert plan["workgroups"] > (2 if r <= 32 else 4) * 256 and plan["workgroups_per_unit"] > 1 and plan["scores_itself"] == (r <= 32)
+        ws = ds.ds_workspace_alloc(shp)
+        ds.ds_tune_set(5, 1)
+        bad = decode(ws)
+        ds.ds_tune_set(5, 0)
+        n_failed, _ = ds.ds_workspace_errors(ws, shp)
+    finally:
+        ds.ds_tune_set(5, 0)
+        ds.ds_pretend_device(0, 0, 0)
+    failed = np.isnan(bad.reshape(Hkv, -1)).all(axis=1)
+    assert int(failed.sum()) == n_failed and (n_failed > 0 or r > 32)
+    assert not (bad == 7.0).any()
+    ok = np.repeat(~failed, Hq // Hkv)
+    if ok.any():
+        check_output(bad[0][ok], good[0][ok].astype(np.float64), "units that did not fail")
