@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
         }
     } else if constexpr (RMODE == -3) {
         const int W = (r + 7) / 8;
-        const uint32_t *cu = reinterpret_cast<const uint32_t *>(label) + (size_t)u * L_max * W;
+        const uint32_t *codes_u = reinterpret_cast<const uint32_t *>(label) + (size_t)u * L_max * W;
         auto nib = [](uint32_t word, int i) { return (float)(((int32_t)(word << (28 - 4 * i))) >> 28); };
         // One or two words per token: 16-byte loads of four or two tokens, four loads in flight;
         // w[j] = 0 beyond r (a product of zero leaves the sum as it is).
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
                 uint4 cv[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    cv[i] = stream_load(reinterpret_cast<const uint4 *>(cu + (size_t)min(t0 + i * kWG * TPL, t_lastq) * WW));
+                    cv[i] = stream_load(reinterpret_cast<const uint4 *>(codes_u + (size_t)min(t0 + i * kWG * TPL, t_lastq) * WW));
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const uint32_t c4[4] = {cv[i].x, cv[i].y, cv[i].z, cv[i].w};
@@ -210,7 +210,7 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
             for (int t = t_begin + tid; t < t_end; t += kWG) {
                 float acc = 0.0f;
                 for (int w = 0; w < W; ++w) {
-                    const uint32_t word = cu[(size_t)t * W + w];
+                    const uint32_t word = codes_u[(size_t)t * W + w];
                     for (int i = 0; i < 8 && w * 8 + i < r; ++i)
                         acc = __builtin_fmaf(qs_sh[w * 8 + i], nib(word, i), acc);
                 }

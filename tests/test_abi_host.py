@@ -191,13 +191,14 @@ def test_handed_over_arrays_are_never_read_with_plain_loads():
     through ld_dev (device-scope loads).  A plain
     indexed read -- `x = cu[i]`, `... hu[i] + ...` -- could be served from a stale cache line.
     Allowed forms: the address taken for an atomic (`&hu[i]`), a clearing store (`hu[i] = 0`)."""
-    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    csrc = os.path.join(root, "paper_2408_07092_amd", "csrc")
+    csrc = os.path.join(ROOT, "paper_2408_07092_amd", "csrc")
     names = r"(?:cu|hu|cuh|a\.cand|a\.ndef|a\.offs_rw|a\.part|a\.hist|a\.coarse|po|pg|part_unit|ph|pc|am)"
-    bad = []
-    for fn in ("ds_attend.hip", "ds_attend_core.h", "ds_misc.hip"):
-        for ln, line in enumerate(open(os.path.join(csrc, fn)), 1):
+    bad, seen = [], set()
+    for path in sorted(glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "*.h"))):
+        fn = os.path.basename(path)
+        for ln, line in enumerate(open(path), 1):
             code = line.split("//")[0]
+            seen.update((fn, n) for n in re.findall(r"ld_dev\([^;]*?\b(cu|cuh|hu|a\.ndef|pc|am)\b", code))
             for m in re.finditer(r"(?<![\w.&])" + names + r"\s*\[", code):
                 rest = code[m.end():]
                 depth, i = 1, 0
@@ -209,6 +210,9 @@ def test_handed_over_arrays_are_never_read_with_plain_loads():
                     continue                     # a store
                 bad.append(f"{fn}:{ln}: {line.strip()}")
     assert not bad, "plain reads of in-launch hand-over arrays:\n" + "\n".join(bad)
+    # (the files that hold the hand-overs are among those looked at)
+    assert {("ds_decode_core.h", n) for n in ("cu", "cuh", "hu", "a.ndef", "pc")} <= seen
+    assert {("ds_attend.hip", "cu"), ("ds_attend.hip", "a.ndef"), ("ds_misc.hip", "am")} <= seen, seen
 
 
 def test_error_words_are_read_by_one_thread_for_its_workgroup():
