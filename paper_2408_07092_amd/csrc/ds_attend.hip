@@ -755,9 +755,6 @@ static RaFn decode_kernel(int gt, int smode, DecodeVariant v)
     }
 }
 
-// Whether a chunk's keys fit LDS besides its list, with as many workgroups to a compute unit as the plans count on.
-static bool keys_in_lds(const Plan &p) { return p.ch <= (p.G <= 2 ? 8192 : p.G <= 8 ? 4096 : 2048); }
-
 // smode: 0 = keys and threshold bin come from the scoring launch; 4 .. 32 = fp16 labels of that
 // many channels scored here; -8 / -16 = 4-bit labels of up to that many channels scored here.
 static RaKernel ra_kernel(const Plan &p, const ds_shape_t &s, int smode)
@@ -775,8 +772,7 @@ static RaKernel ra_kernel(const Plan &p, const ds_shape_t &s, int smode)
         }
     }
     const DecodeVariant v = decode_variant(p, s);
-    return {decode_kernel(gt, smode, v), v == DECODE_NARROW ? 256 : 512,
-            (size_t)(p.ch + 7) / 8 * 16 + (keys_in_lds(p) ? (size_t)p.ch * 4 : 0)};
+    return {decode_kernel(gt, smode, v), v == DECODE_NARROW ? 256 : 512, (size_t)(p.ch + 7) / 8 * 16};
 }
 
 // 0 when the labels cannot be scored in the attention launch
@@ -883,7 +879,6 @@ hipError_t launch_refine_attend(const void *q, const void *K, const void *V, voi
     a.amax = amax;
     a.r = s.r;
     a.k_share = (float)p.k_eff / (float)s.L;
-    a.keys_in_lds = keys_in_lds(p);
     const int smode = ra_smode(s, score_label != nullptr, amax != nullptr);
     if (score_label && smode == 0) return hipErrorInvalidValue;
     const RaKernel k = ra_kernel(p, s, smode);

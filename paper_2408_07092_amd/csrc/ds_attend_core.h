@@ -40,7 +40,6 @@ struct AttendArgs {
     const int32_t *channels;   // [Hkv][r]
     uint32_t *hist, *coarse;   // unit histograms (4096 / 256 bins), zero between calls
     const float *amax;         // 4-bit label cache: [units][r] largest magnitude per channel
-    int keys_in_lds;           // whether the launch has LDS for its chunks' keys
     float k_share;             // k_eff / L
     int r;                     // label channels (4-bit label cache; fp16 labels have it in the kernel's type)
 };

@@ -230,3 +230,16 @@ def test_error_words_are_read_by_one_thread_for_its_workgroup():
             in_block = block and "}" not in block and re.search(r"\bs_\w+ = $", line)
             assert "if (tid == 0)" in line or in_block, f"{os.path.basename(path)}: {src[m.start() - 40:m.end()]!r}"
     assert reads == 2
+
+
+def test_every_launch_argument_is_read_by_a_kernel():
+    """Host only: an argument of the attention launches that no kernel reads any more is likely to have left
+    something behind on the host -- LDS set aside for it, say, which costs residency and nobody sees."""
+    csrc = os.path.join(ROOT, "paper_2408_07092_amd", "csrc")
+    src = "\n".join(re.sub(r"//[^\n]*", "", open(p).read())
+                    for p in sorted(glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "*.h"))))
+    body = re.search(r"struct AttendArgs \{(.*?)\n\};", src, re.S).group(1)
+    fields = [n.strip(" *") for decl in body.split(";") for n in re.sub(r"^\s*(?:const )?\w+ ", "", decl).split(",") if n.strip()]
+    assert {"q", "V", "cand", "label", "r", "k_share"} <= set(fields) and len(fields) > 25
+    unread = [f for f in fields if not re.search(r"\ba\." + f + r"\b(?!\s*=[^=])", src)]
+    assert not unread
