@@ -13,7 +13,7 @@ LIB = os.path.join(HERE, "libdsattn.so")
 LIB_TRACE = os.path.join(HERE, "libdsattn_trace.so")
 SOURCES = ["ds_select.hip", "ds_attend.hip", "ds_misc.hip", "ds_decode_g1.hip", "ds_decode_g2.hip", "ds_decode_g4.hip",
            "ds_decode_g8.hip", "ds_decode_g16.hip", "ds_api.cpp"]
-HEADERS = ["ds_internal.h", "ds_device.h", "ds_attend_core.h", "ds_decode_core.h"]
+HEADERS = ["ds_internal.h", "ds_device.h", "ds_attend_core.h", "ds_bins.h", "ds_decode_core.h"]
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

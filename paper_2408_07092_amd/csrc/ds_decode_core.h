@@ -19,7 +19,7 @@
 //   - A wavefront issues an instruction every 8 clocks at best, two to a SIMD fill that: 512 threads. With 1024, and
 //     every wavefront running the list work, one layer of 4K tokens took 12.6, with 512 9.2.
 //   - One wavefront does what needs no more; the others never wait at its barriers (31.1 -> 26.5 with the next two).
-//   - Bins of 1/128 octave instead of 1/8: 70 candidates in a unit where there were 1100, so that every workgroup settles
+//   - Bins of 1/128 octave instead of 1/8 (see ds_bins.h): 70 candidates in a unit where there were 1100, so that every workgroup settles
 //     the threshold alone; one that did it for the unit held the others up until 10 us after the last had arrived.
 //   - No more row loads in flight than memory needs: a workgroup's hand-over queues behind them. Eight rows per slot 34.6,
 //     four 33.1, two 32.0 (with the settling workgroup).
@@ -29,6 +29,7 @@
 #pragma once
 
 #include "ds_attend_core.h"
+#include "ds_bins.h"
 
 namespace ds {
 
@@ -171,28 +172,6 @@ __device__ __forceinline__ bool wave_settle(Held &c, uint32_t krem, uint32_t lo_
     T = read_lane(mine.x, l);
     tcut = (int)read_lane(mine.y, l);
     return true;
-}
-
-// First-level bins.  A score falls into one of 4096 bins of 1/128 octave: 16 octaves of either sign, around
-// the label query's largest value, which every workgroup of a unit knows; what lies beyond is in the end
-// bins.  Any non-decreasing map of scores to bins keeps the selection exact.  (With the top 12 bits of the key,
-// bins of 1/8 octave, a unit of 64K tokens had 1100 keys in the threshold bin; it has 70.)
-constexpr uint32_t kSideBins = kHistBins / 2, kBinShift = 16;
-// first bin's place on the scale of |score| bits >> kBinShift
-__device__ __forceinline__ uint32_t bin_base(float magnitude)
-{
-    const int e = (int)(__float_as_uint(magnitude) >> 23 & 255u);
-    return (uint32_t)min(max(e - 7, 0), 254 - 16) << 7;
-}
-// keys of bin b: [lo, hi]
-__device__ __forceinline__ void bin_keys(uint32_t b, uint32_t base, uint32_t &lo, uint32_t &hi)
-{
-    const bool neg = b < kSideBins;
-    const uint32_t m = neg ? kSideBins - 1u - b : b - kSideBins;
-    const uint32_t a = m == 0u ? 0u : (base + m) << kBinShift;
-    const uint32_t z = m == kSideBins - 1u ? 0x7fffffffu : ((base + m + 1u) << kBinShift) - 1u;
-    lo = neg ? ~(0x80000000u | z) : 0x80000000u | a;
-    hi = neg ? ~(0x80000000u | a) : 0x80000000u | z;
 }
 
 // Threshold bin of a complete histogram of kHistBins counts in LDS: the bin holding the kth key from the top
@@ -790,7 +769,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
             magnitude = fmaxf(magnitude, fabsf(qs[j]));
         }
     }
-    const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)bin_base(magnitude));
+    const BinScale bins(__builtin_amdgcn_readfirstlane(__float_as_int(magnitude)));
     typedef uint32_t KeyVec __attribute__((ext_vector_type(kKeys)));
     KeyVec key;
     auto nib = [](uint32_t word, int i) { return (float)(((int32_t)(word << (28 - 4 * i))) >> 28); };
@@ -829,13 +808,13 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
                         sgn = ~(uint32_t)((int32_t)key[i] >> 31);
                         bits = key[i] ^ sgn;
                     } else {
+                        // (never -0, which would have to tie with +0: a sum that starts from +0 becomes -0 only where a tiny
+                        //  negative number is rounded, and sums of such products are 0 or above 2^-80)
                         bits = __float_as_uint(acc);
-                        if (bits == 0x80000000u) bits = 0u;  // (-0 and +0 tie)
                         sgn = (uint32_t)((int32_t)bits >> 31);
                         key[i] = bits ^ (sgn | 0x80000000u);
                     }
-                    const uint32_t m = min(max((bits >> kBinShift) & 0x7fffu, base), base + kSideBins - 1u) - base;
-                    atomicAdd(&pool[kSideBins + (m ^ sgn)], 1u);
+                    atomicAdd(&pool[kSideBins + (bins.bin(bits) ^ sgn)], 1u);
                 }
             }
         }
@@ -977,7 +956,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     // One look at each key: which of the thread's keys are definite and which are candidates goes into
     // bit masks (bit j <-> key n_seen - 1 - j); the writes walk the set bits, few as they are.
     uint32_t lo_key, hi_key;
-    bin_keys((uint32_t)__builtin_amdgcn_readfirstlane((int)bstar), base, lo_key, hi_key);
+    bins.keys((uint32_t)__builtin_amdgcn_readfirstlane((int)bstar), lo_key, hi_key);
     lo_key = max(lo_key, 1u);  // (dead keys are zero)
     const int span = hi_key > lo_key ? 32 - __builtin_clz(hi_key - lo_key) : 0;
     uint32_t mdef = 0, mcan = 0;
