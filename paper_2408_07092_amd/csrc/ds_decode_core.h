@@ -36,7 +36,8 @@ namespace ds {
 constexpr int kKeys = 32;               // tokens of a thread at most
 constexpr int kQRow = kD + 8;           // halves from one query row in LDS to the next (spreads the matrix cores' reads over the banks)
 constexpr uint32_t kCandLds = 512;      // candidates of a workgroup that LDS holds; the others go through memory
-constexpr uint32_t kWaveSettles = 8192; // more candidates than this are settled by the whole workgroup
+// More candidates than these are settled by the whole workgroup: see wave_settle.  (One workgroup per unit, several.)
+constexpr uint32_t kWaveSettlesOwn = 384, kWaveSettlesUnit = 1024;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 __device__ __forceinline__ uint32_t read_lane(uint32_t x, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)x, l); }
@@ -107,27 +108,44 @@ struct HeldCands {
     }
 };
 
-// Exact k-th key of a unit among its candidates, whose keys less lo_key are below 2^span, by one
-// wavefront: the krem-th in the order key descending, token ascending.  No more than 64 are ranked
-// among themselves.  Of more, one lane is a radix bin, six key bits at a time, as often as it takes
-// to be left with 64.  lh: 64 words of LDS; small: room for 64 candidates.
-// False when more than 64 equal keys are left, or the counts do not add up (a workspace that was not
-// cleared): the workgroup then takes the long way.
+// A candidate's place in the order key descending, token ascending, as a number, larger = earlier: the key less
+// lo_key, the key of a bin's first, and the token inverted in its tb bits.
+__device__ __forceinline__ unsigned long long place_of(uint2 e, uint32_t lo_key, int tb)
+{
+    return (unsigned long long)(e.x - lo_key) << tb | (e.y ^ ((1u << tb) - 1u));
+}
+// Threshold that the places from `place` on pass.
+__device__ __forceinline__ void threshold_at(unsigned long long place, uint32_t lo_key, int tb, uint32_t &T, int &tcut)
+{
+    const uint32_t mask = (1u << tb) - 1u;
+    T = lo_key + (uint32_t)(place >> tb);
+    tcut = (int)(((uint32_t)place & mask) ^ mask);
+}
+
+// Exact k-th key of a unit among its candidates, whose keys less lo_key are below 2^span and whose tokens
+// below 2^tb, by one wavefront: the krem-th in the order key descending, token ascending.  No more than 64 are
+// ranked among themselves.  Of more, one lane is a radix bin, six bits of the place at a time, as often as
+// it takes to be left with 64, or with none but selected ones.  lh: 64 words of LDS; small: room for 64 candidates.
+// False when the counts do not add up (a workspace that was not cleared): the workgroup then takes the long way.
+// Up to how many candidates it is tried: what its registers hold for a unit's one workgroup (128 units of 6000 tokens, 600 equal
+// keys: 21.9 us with a limit of 384, 26.5 with 1024); for several workgroups, whose lists are in memory and whose row
+// wavefronts are still busy, some more (32 units of 64K tokens, 550 candidates: 28.4 us with 1024, 30.8 with 384).
 template <class Held>
-__device__ __forceinline__ bool wave_settle(Held &c, uint32_t krem, uint32_t lo_key, int span, uint32_t *lh, uint2 *small,
+__device__ __forceinline__ bool wave_settle(Held &c, uint32_t krem, uint32_t lo_key, int span, int tb, uint32_t *lh, uint2 *small,
                                             uint32_t &T, int &tcut)
 {
     const uint32_t lane = (uint32_t)lane_id();
-    uint32_t m = c.n, pre = 0;  // (pre: the settled prefix, at its place in key - lo_key)
-    int sh = span;
+    uint32_t m = c.n;
+    unsigned long long pre = 0;  // the settled bits of the place
+    int sh = span + tb;
     while (m > 64u && sh > 0) {
         const int nb = min(sh, 6);
         sh -= nb;
         lh[lane] = 0u;
         wave_lds_sync();
         c.each([&](uint2 e, bool have) {
-            const uint32_t x = (e.x - lo_key) ^ pre;
-            if (have && (x >> sh) >> nb == 0u) atomicAdd(&lh[63u - (x >> sh)], 1u);
+            const unsigned long long x = (place_of(e, lo_key, tb) ^ pre) >> sh;
+            if (have && x >> nb == 0ull) atomicAdd(&lh[63u - (uint32_t)x], 1u);
         });
         wave_lds_sync();
         const uint32_t cnt = lh[lane];
@@ -135,9 +153,13 @@ __device__ __forceinline__ bool wave_settle(Held &c, uint32_t krem, uint32_t lo_
         const unsigned long long own = __ballot(incl - cnt < krem && incl >= krem);
         if (own == 0ull) return false;
         const int l = __builtin_ctzll(own);
-        pre |= (63u - (uint32_t)l) << sh;
+        pre |= (unsigned long long)(63u - (uint32_t)l) << sh;
         krem -= read_lane(incl - cnt, l);
         m = read_lane(cnt, l);
+        if (m == krem) {
+            threshold_at(pre, lo_key, tb, T, tcut);
+            return true;
+        }
         wave_lds_sync();
     }
     if (m > 64u) return false;
@@ -149,7 +171,7 @@ __device__ __forceinline__ bool wave_settle(Held &c, uint32_t krem, uint32_t lo_
     } else {
         uint32_t got = 0;
         c.each([&](uint2 e, bool have) {
-            const bool hit = have && (((e.x - lo_key) ^ pre) >> sh) == 0u;
+            const bool hit = have && (place_of(e, lo_key, tb) ^ pre) >> sh == 0ull;
             const unsigned long long hm = __ballot(hit);
             if (hm) {
                 const uint32_t pos = got + bits_below(hm);
@@ -211,52 +233,54 @@ __device__ __forceinline__ void find_bin(const uint32_t *hist, uint32_t kth, uin
     __syncthreads();
 }
 
-// The same by the whole workgroup and for any number of candidates: radix passes of 10 key bits, then
-// of 8 + 10 + 10 index bits among equal keys.  Sets T and tcut in every thread.
+// f of each of n candidates, by the whole workgroup; eight loads of a thread are in flight.
+template <int WGT, class At, class F>
+__device__ __forceinline__ void wg_each(uint32_t n, At at, F f)
+{
+    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 8u * WGT) {
+        uint2 v[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) v[x] = at(min(i0 + (uint32_t)(x * WGT), n - 1u));
+#pragma unroll
+        for (int x = 0; x < 8; ++x)
+            if (i0 + (uint32_t)(x * WGT) < n) f(v[x]);
+    }
+}
+
+// wave_settle's task by the whole workgroup, for any number of candidates, ten bits of the place at a time.  Sets T and
+// tcut in every thread.  Equal keys, of which there can be thousands, share a radix bin: a wavefront's candidates that
+// fall into the first one's are counted with one add (64 adds to one word of LDS wait for each other).
 template <int NW, class At>
-__device__ __forceinline__ void wg_settle(uint32_t n, At at, uint32_t krem, uint32_t lo_key, int span, uint32_t *lh, uint32_t *s_w,
-                                          uint32_t *s_res, uint32_t &T, int &tcut)
+__device__ __forceinline__ void wg_settle(uint32_t n, At at, uint32_t krem, uint32_t lo_key, int span, int tb, uint32_t *lh,
+                                          uint32_t *s_w, uint32_t *s_res, uint32_t &T, int &tcut)
 {
     constexpr int WGT = 64 * NW, PER = 1024 / WGT;
     const uint32_t tid = threadIdx.x;
-    auto each = [&](auto f) {
-        for (uint32_t i0 = tid; i0 < n; i0 += 8u * WGT) {
-            uint2 v[8];
-#pragma unroll
-            for (int x = 0; x < 8; ++x) v[x] = at(min(i0 + (uint32_t)(x * WGT), n - 1u));
-#pragma unroll
-            for (int x = 0; x < 8; ++x)
-                if (i0 + (uint32_t)(x * WGT) < n) f(v[x]);
-        }
-    };
-    uint32_t pre = 0, ties = 0, rank = krem;
-    for (int sh = span; sh > 0;) {
+    unsigned long long pre = 0;
+    uint32_t rank = krem;
+    for (int sh = span + tb; sh > 0;) {
         const int nb = min(sh, 10);
         sh -= nb;
-        svc_radix_pass<PER, true, NW>(each, [&](uint2 e) { return ((((e.x - lo_key) ^ pre) >> sh) >> nb) == 0u; },
-                                      [&](uint2 e) { return ((e.x - lo_key) >> sh) & 1023u & ((1u << nb) - 1u); }, rank, lh, s_w, s_res);
-        pre |= s_res[0] << sh;
-        rank = s_res[1];
-        ties = lh[s_res[0]];
+        for (uint32_t i = tid; i < 1024u; i += WGT) lh[i] = 0u;
         __syncthreads();
+        wg_each<WGT>(n, at, [&](uint2 e) {
+            const unsigned long long p = (place_of(e, lo_key, tb) ^ pre) >> sh;
+            if (p >> nb == 0ull) {
+                const uint32_t d = (uint32_t)p, d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+                const unsigned long long same = __ballot(d == d0);
+                if (d != d0) atomicAdd(&lh[d], 1u);
+                else if (bits_below(same) == 0u) atomicAdd(&lh[d0], (uint32_t)__builtin_popcountll(same));
+            }
+        });
+        __syncthreads();
+        hist_select<PER, true, NW>([&](int bin) { return lh[bin]; }, rank, s_w, s_res);
+        pre |= (unsigned long long)s_res[0] << sh;
+        rank = s_res[1];
+        const uint32_t m = lh[s_res[0]];
+        __syncthreads();
+        if (m == rank) break;  // (none but selected ones are left)
     }
-    T = lo_key + pre;
-    tcut = 0x7fffffff;
-    if (span == 0) ties = n;
-    if (rank < ties) {
-        const uint32_t Tk = T;
-        uint32_t at_bits = 0;
-#pragma unroll 1
-        for (int p = 0; p < 3; ++p) {
-            const int sh = 20 - 10 * p;
-            svc_radix_pass<PER, false, NW>(each, [&](uint2 e) { return e.x == Tk && (p == 0 || (e.y >> (sh + 10)) == at_bits >> (sh + 10)); },
-                                           [&](uint2 e) { return (e.y >> sh) & 1023u; }, rank, lh, s_w, s_res);
-            at_bits |= s_res[0] << sh;
-            rank = s_res[1];
-            __syncthreads();
-        }
-        tcut = (int)at_bits;
-    }
+    threshold_at(pre, lo_key, tb, T, tcut);
 }
 
 // Rows of single heads and pairs.  The RW row wavefronts' 16-lane slots take the list's rows in turn, HB rows a
@@ -958,7 +982,8 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     uint32_t lo_key, hi_key;
     bins.keys((uint32_t)__builtin_amdgcn_readfirstlane((int)bstar), lo_key, hi_key);
     lo_key = max(lo_key, 1u);  // (dead keys are zero)
-    const int span = hi_key > lo_key ? 32 - __builtin_clz(hi_key - lo_key) : 0;
+    const int span = hi_key > lo_key ? 32 - __builtin_clz(hi_key - lo_key) : 0;  // <= 31
+    const int tb = 32 - __builtin_clz(max(a.L - 1, 1));  // <= 24
     uint32_t mdef = 0, mcan = 0;
     int n_seen = 0;
 #pragma unroll
@@ -1065,7 +1090,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
         uint32_t T = 0xffffffffu;
         int tcut = -1;
         if (single) {
-            big = n > kWaveSettles || !wave_settle(own, krem, lo_key, span, lh, small_sh, T, tcut);
+            big = n > kWaveSettlesOwn || !wave_settle(own, krem, lo_key, span, tb, lh, small_sh, T, tcut);
         } else {
             // the candidates of all of the unit's workgroups meet in its list in memory, and every workgroup
             // settles the threshold by itself
@@ -1099,7 +1124,7 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
                 uint32_t before = 0;
                 if (want_off)
                     for (int i = lane; i < c; i += 64) before += ld_dev(a.ndef + (size_t)u * a.n_ch + i);
-                big = n > kWaveSettles || !wave_settle(all, krem, lo_key, span, lh, small_sh, T, tcut);
+                big = n > kWaveSettlesUnit || !wave_settle(all, krem, lo_key, span, tb, lh, small_sh, T, tcut);
                 if (want_off && !big) {
                     // selected tokens in front of this chunk
                     all.each([&](uint2 e, bool have) {
@@ -1161,27 +1186,32 @@ __device__ __forceinline__ void decode_unit(const AttendArgs &a)
     ready = (uint32_t)__builtin_amdgcn_readfirstlane((int)ready);
     if (ready == 2u) {
         __syncthreads();
-        // (thousands of candidates, or dozens of equal ones: all wavefronts together)
+        // (hundreds of candidates: all wavefronts together)
         uint32_t T, n_sel = 0, total;
         int tcut;
         const uint32_t n = s_n;
         auto unit_at = [&](uint32_t i) { return single ? own_cand(i) : ld_dev(cu + i); };
-        wg_settle<NW>(n, unit_at, krem, lo_key, span, lh, s_w, s_res, T, tcut);
+        wg_settle<NW>(n, unit_at, krem, lo_key, span, tb, lh, s_w, s_res, T, tcut);
         if (want_off) {
             uint32_t before = 0;
             for (int i = tid; i < c; i += WGT) before += ld_dev(a.ndef + (size_t)u * a.n_ch + i);
-            for (uint32_t i = tid; i < n; i += WGT) {
-                const uint2 e = unit_at(i);
-                before += (int)e.y < t0 && is_selected(e.x, (int)e.y, T, tcut) ? 1u : 0u;
-            }
+            wg_each<WGT>(n, unit_at, [&](uint2 e) { before += (int)e.y < t0 && is_selected(e.x, (int)e.y, T, tcut) ? 1u : 0u; });
             block_exclusive_scan<NW>(before, s_w, &total);
             if (tid == 0) s_off = total;
         }
-        for (uint32_t i0 = 0; i0 < n_cand; i0 += WGT) {
-            const uint2 e = own_cand(min(i0 + (uint32_t)tid, n_cand - 1u));
-            const bool hit = i0 + (uint32_t)tid < n_cand && e.y - (uint32_t)t0 < (uint32_t)n_tok && is_selected(e.x, (int)e.y, T, tcut);
-            const uint32_t ex = block_exclusive_scan<NW>(hit ? 1u : 0u, s_w, &total);
-            if (hit) sel[n_def + (int)(n_sel + ex)] = (uint16_t)(e.y - (uint32_t)t0);
+        for (uint32_t i0 = 0; i0 < n_cand; i0 += 8u * WGT) {
+            uint2 v[8];
+            uint32_t hits = 0;
+#pragma unroll
+            for (int x = 0; x < 8; ++x) v[x] = own_cand(min(i0 + (uint32_t)(x * WGT + tid), n_cand - 1u));
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+                if (i0 + (uint32_t)(x * WGT + tid) < n_cand && v[x].y - (uint32_t)t0 < (uint32_t)n_tok && is_selected(v[x].x, (int)v[x].y, T, tcut))
+                    hits |= 1u << x;
+            uint32_t at = (uint32_t)n_def + n_sel + block_exclusive_scan<NW>((uint32_t)__builtin_popcount(hits), s_w, &total);
+#pragma unroll
+            for (int x = 0; x < 8; ++x)
+                if (hits >> x & 1u) sel[at++] = (uint16_t)(v[x].y - (uint32_t)t0);
             n_sel += total;
         }
         if (tid == 0) s_nsel = n_sel;

@@ -363,12 +363,12 @@ def test_decode_in_the_smallest_workspace(r):
     (1, 12000, 800, 0.0, SEVERAL),      # every key the same: 12000 candidates, the tie cut among them all
     (2, 20000, 9000, 1e-3, SEVERAL),    # a few keys of many tokens each
     (4, 9000, 500, 1e-3, SEVERAL),      # matrix-core variant
-    (1, 4000, 2900, 1e-3, ONE),         # one workgroup per unit, more candidates than it ranks at once
+    (1, 4000, 2900, 1e-3, ONE),         # one workgroup per unit
     (1, 5000, 3100, 1e-3, SEVERAL),
 ])
 def test_decode_many_candidates(Hq, L, k, step, one):
-    """Thousands of keys in the threshold bin: the refinement reads those beyond the first 2048 again
-    in every pass; the index list is the oracle's, ties to the lowest token."""
+    """Thousands of keys in the threshold bin, most of them equal: the whole workgroup settles the threshold, from
+    lists that LDS does not hold; the index list is the oracle's, ties to the lowest token."""
     w = Workload("t", 1, Hq, 1, 128, L, 8, k, 1)
     t = make_layer_numpy(w)
     ch = rand_channels(1, 8, seed=L)
@@ -493,3 +493,29 @@ def test_workgroups_that_start_late_leave_no_old_output(cus, Hq, Hkv, L, r):
     ok = np.repeat(~failed, Hq // Hkv)
     if ok.any():
         check_output(bad[0][ok], good[0][ok].astype(np.float64), "units that did not fail")
+
+
+@pytest.mark.parametrize("ties", [True, False])
+@pytest.mark.parametrize("L,n,one", [(4000, 64, ONE), (4000, 65, ONE), (4000, 384, ONE), (4000, 385, ONE), (4000, 512, ONE),
+                                     (4000, 513, ONE), (6000, 4097, ONE), (20000, 64, SEVERAL), (20000, 65, SEVERAL),
+                                     (20000, 385, SEVERAL), (20000, 1024, SEVERAL), (20000, 1025, SEVERAL)])
+def test_decode_settles_any_number_of_candidates(L, n, one, ties):
+    """n keys in the threshold bin, equal or not, on both sides of what one lane ranks, one wavefront settles,
+    LDS holds and the workgroup reads at a time; the threshold lies in the middle, at the first and at the last of them."""
+    rng = np.random.default_rng(L + n)
+    t = make_layer_numpy(Workload("t", 1, 1, 1, 128, L, 8, 1, 1))
+    ch = rand_channels(1, 8, seed=n)
+    # scores 2 (100 tokens), 1 .. 1 + 2^-9 (n tokens), and 1/4
+    t["q"][0, 0][ch[0]] = 0.0
+    t["q"][0, 0][ch[0][0]], t["q"][0, 0][ch[0][1]] = 1.0, 2.0 ** -9
+    lab = np.zeros((L, 8), np.float16)
+    lab[:, 0] = 0.25
+    where = rng.permutation(L)
+    lab[where[:100], 0] = 2.0
+    lab[where[100:100 + n], 0] = 1.0
+    if not ties:
+        lab[where[100:100 + n], 1] = rng.integers(0, 1024, n) / 1024
+    t["K"][0, 0][:, ch[0]] = lab
+    for k in (101, 100 + n // 2, 100 + n):
+        assert (ds.ds_plan_describe(ds.shape(1, 1, 1, 128, L, L, 8, k))["workgroups_per_unit"] == 1) == one or k * 16 > L
+        full_parity(Case(t["q"], t["K"], t["V"], ch, L, k), check_dense=False, what=f"{n} candidates of {L}, k {k}")
