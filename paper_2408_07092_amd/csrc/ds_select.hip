@@ -61,15 +61,23 @@ __device__ __forceinline__ float label_dot(const _Float16 *__restrict__ row, con
 
 // BINS: the launch also finds the unit's threshold bin (for the launches that select from it: k_cand, or
 // this one's own tail).  k_refine_attend bins the keys by itself and wants nothing but them.
+// Scores from K rows (RMODE -2): a lane has a row of 256 bytes to itself and picks r halves out of it, so a load
+// touches 64 lines, which are found again by the next ones only while they are in the compute unit's first-level
+// cache.  Eight channels of a lane's four rows are asked for at once, a row's together, before the first is used: 32
+// registers for them, and no more than five wavefronts to a SIMD.  (Left to the compiler, which aims at eight
+// wavefronts where no bins take up LDS, the loads of the rows alternate and wait for each other: 256 units of
+// 8000 tokens, 16 channels 188 us, with the bins 98, now 86; 1024 of 4096, 16 channels 643, 199, 179; 32 of 64K tokens,
+// 8 channels, with the bins 79 -> 69.)
 template <int RMODE, bool BINS>
-__global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
-                                               const _Float16 *__restrict__ label,
-                                               const int32_t *__restrict__ channels,
-                                               const float *__restrict__ amax,
-                                               uint32_t *__restrict__ keys, uint32_t *hist,
-                                               uint32_t *coarse, UnitCtl *ctl, uint32_t *offs, int Hq, int Hkv,
-                                               int G, int L, int L_max, int r, int key_stride, int sc_chunk,
-                                               int k_eff, int tail_refine, int want_offsets, int ch, int n_ch)
+__global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(1, RMODE == -2 ? 5 : 8)))
+void k_score(const _Float16 *__restrict__ q,
+             const _Float16 *__restrict__ label,
+             const int32_t *__restrict__ channels,
+             const float *__restrict__ amax,
+             uint32_t *__restrict__ keys, uint32_t *hist,
+             uint32_t *coarse, UnitCtl *ctl, uint32_t *offs, int Hq, int Hkv,
+             int G, int L, int L_max, int r, int key_stride, int sc_chunk,
+             int k_eff, int tail_refine, int want_offsets, int ch, int n_ch)
 {
     extern __shared__ uint32_t cnt_sh[];  // n_ch words, used by the refining tail
     __shared__ uint32_t lh[kHistBins];
@@ -226,13 +234,22 @@ __global__ __launch_bounds__(kWG) void k_score(const _Float16 *__restrict__ q,
             float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int i = 0; i < 4; ++i) row[i] = Ku + (size_t)min(t0 + i * kWG, t_end - 1) * kD;
-#pragma unroll 8
-            for (int j = 0; j < r; ++j) {
-                const int cj = ch_sh[j];
-                const float qj = qs_sh[j];
+            int j0 = 0;
+            for (; j0 + 8 <= r; j0 += 8) {
+                _Float16 x[4][8];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(qj, (float)row[i][cj], acc[i]);
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[i][e] = row[i][ch_sh[j0 + e]];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(qs_sh[j0 + e], (float)x[i][e], acc[i]);
             }
+            for (int j = j0; j < r; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(qs_sh[j], (float)row[i][ch_sh[j]], acc[i]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int t = t0 + i * kWG;
@@ -645,12 +662,8 @@ hipError_t launch_score(const void *q, const void *label, const int32_t *channel
     auto *offs = reinterpret_cast<uint32_t *>(wsp(ws, p.off_offs));
     const auto *qh = static_cast<const _Float16 *>(q);
     const auto *lh = static_cast<const _Float16 *>(label);
-    // (K rows without the bins take as much LDS as with them: with more workgroups to a compute unit its first-level
-    //  cache, in which a row's channels are found again, is too small: 97.8 -> 208 us for six units of 137K tokens, 16
-    //  channels)
-    const size_t shmem = (size_t)p.n_ch * 4 + (!bins && src.kind == SRC_K_ROWS ? (24u << 10) : 0u);
 #define DS_SCORE(MODE)                                                                            \
-    DS_LAUNCH(KID_SCORE, (bins ? k_score<MODE, true> : k_score<MODE, false>), grid, block, shmem, st, qh, lh, channels, src.amax, keys, hist, \
+    DS_LAUNCH(KID_SCORE, (bins ? k_score<MODE, true> : k_score<MODE, false>), grid, block, (size_t)p.n_ch * 4, st, qh, lh, channels, src.amax, keys, hist, \
                        coarse, ctl, offs, s.Hq, s.Hkv, p.G, s.L, s.L_max, s.r, p.key_stride, p.sc_chunk,       \
                        p.k_eff, tail_refine ? 1 : 0, want_offsets ? 1 : 0, p.ch, p.n_ch)
     if (src.kind == SRC_Q4) DS_SCORE(-3);

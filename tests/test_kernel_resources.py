@@ -70,6 +70,13 @@ def test_q4_build_is_limited_by_its_tile_alone(kernels):
     assert k[".vgpr_count"] + k.get(".agpr_count", 0) <= 64 and k[".group_segment_fixed_size"] <= 1280
 
 
+def test_k_row_scoring_keeps_its_loads_in_flight(kernels):
+    """32 loads of a lane at once, with or without the bins: more registers than the compiler would give them if
+    it aimed at eight wavefronts to a SIMD, and no more than five of these wavefronts leave."""
+    found = {n: k[".vgpr_count"] + k.get(".agpr_count", 0) for n, k in kernels.items() if "k_scoreILin2ELb" in n}
+    assert len(found) == 2 and all(64 < v <= 96 for v in found.values()), found
+
+
 def test_vector_attention_kernels_leave_room_for_four_workgroups(kernels):
     """What the plans count on: four workgroups of 256 threads to a compute unit (128 registers) for the
     streaming kernels of single heads and pairs, three (168) for those on the matrix cores."""
