@@ -63,11 +63,13 @@ __device__ __forceinline__ float label_dot(const _Float16 *__restrict__ row, con
 // this one's own tail).  k_refine_attend bins the keys by itself and wants nothing but them.
 // Scores from K rows (RMODE -2): a lane has a row of 256 bytes to itself and picks r halves out of it, so a load
 // touches 64 lines, which are found again by the next ones only while they are in the compute unit's first-level
-// cache.  Eight channels of a lane's four rows are asked for at once, a row's together, before the first is used: 32
-// registers for them, and no more than five wavefronts to a SIMD.  (Left to the compiler, which aims at eight
+// cache.  Below 32 channels, eight of a lane's four rows are asked for at once, a row's together, before the first is
+// used: 32 registers for them, and four or five wavefronts to a SIMD.  (Left to the compiler, which aims at eight
 // wavefronts where no bins take up LDS, the loads of the rows alternate and wait for each other: 256 units of
 // 8000 tokens, 16 channels 188 us, with the bins 98, now 86; 1024 of 4096, 16 channels 643, 199, 179; 32 of 64K tokens,
-// 8 channels, with the bins 79 -> 69.)
+// 8 channels, with the bins 79 -> 69.)  From 32 on, where a row's lines are used many times over, the loads of one eight
+// must not end before the next begin, and the compiler's order stays: in eights 488 units of 482 tokens, 64 channels took
+// 52.5 -> 62.7 us, 352 of 8904, 32 channels 477 -> 564.
 template <int RMODE, bool BINS>
 __global__ __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(1, RMODE == -2 ? 5 : 8)))
 void k_score(const _Float16 *__restrict__ q,
@@ -234,22 +236,32 @@ void k_score(const _Float16 *__restrict__ q,
             float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int i = 0; i < 4; ++i) row[i] = Ku + (size_t)min(t0 + i * kWG, t_end - 1) * kD;
-            int j0 = 0;
-            for (; j0 + 8 <= r; j0 += 8) {
-                _Float16 x[4][8];
+            if (r < 32) {
+                int j = 0;
+                for (; j + 8 <= r; j += 8) {
+                    _Float16 x[4][8];
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+                    for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) x[i][e] = row[i][ch_sh[j0 + e]];
-                __builtin_amdgcn_sched_barrier(0);
+                        for (int e = 0; e < 8; ++e) x[i][e] = row[i][ch_sh[j + e]];
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
+                    for (int e = 0; e < 8; ++e)
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(qs_sh[j0 + e], (float)x[i][e], acc[i]);
+                        for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(qs_sh[j + e], (float)x[i][e], acc[i]);
+                }
+                for (; j < r; ++j)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(qs_sh[j], (float)row[i][ch_sh[j]], acc[i]);
+            } else {
+#pragma unroll 8
+                for (int j = 0; j < r; ++j) {
+                    const int cj = ch_sh[j];
+                    const float qj = qs_sh[j];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(qj, (float)row[i][cj], acc[i]);
+                }
             }
-            for (int j = j0; j < r; ++j)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] = __builtin_fmaf(qs_sh[j], (float)row[i][ch_sh[j]], acc[i]);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int t = t0 + i * kWG;

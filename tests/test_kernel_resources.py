@@ -72,9 +72,9 @@ def test_q4_build_is_limited_by_its_tile_alone(kernels):
 
 def test_k_row_scoring_keeps_its_loads_in_flight(kernels):
     """32 loads of a lane at once, with or without the bins: more registers than the compiler would give them if
-    it aimed at eight wavefronts to a SIMD, and no more than five of these wavefronts leave."""
+    it aimed at eight wavefronts to a SIMD, and few enough for four."""
     found = {n: k[".vgpr_count"] + k.get(".agpr_count", 0) for n, k in kernels.items() if "k_scoreILin2ELb" in n}
-    assert len(found) == 2 and all(64 < v <= 96 for v in found.values()), found
+    assert len(found) == 2 and all(64 < v <= 104 for v in found.values()), found
 
 
 def test_vector_attention_kernels_leave_room_for_four_workgroups(kernels):
