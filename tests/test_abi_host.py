@@ -217,8 +217,8 @@ def test_handed_over_arrays_are_never_read_with_plain_loads():
 
 def test_error_words_are_read_by_one_thread_for_its_workgroup():
     """Host only, over the kernels: a unit's error word can be raised by another workgroup at any time, so a
-    workgroup must not let each of its wavefronts act on a read of its own.  Every read is made by thread 0
-    and reaches the others through LDS."""
+    workgroup must not let each of its wavefronts act on a read of its own.  Every read is made by thread 0, or its
+    copy is the only one that is used, and reaches the others through LDS."""
     csrc = os.path.join(ROOT, "paper_2408_07092_amd", "csrc")
     reads = 0
     for path in sorted(glob.glob(os.path.join(csrc, "*.hip")) + glob.glob(os.path.join(csrc, "ds_*_core.h"))):
@@ -228,7 +228,12 @@ def test_error_words_are_read_by_one_thread_for_its_workgroup():
             line = src[src.rfind("\n", 0, m.start()):m.start()]
             block = src[src.rfind("if (tid == 0) {", 0, m.start()):m.start()]
             in_block = block and "}" not in block and re.search(r"\bs_\w+ = $", line)
-            assert "if (tid == 0)" in line or in_block, f"{os.path.basename(path)}: {src[m.start() - 40:m.end()]!r}"
+            own = re.search(r"const uint32_t (\w+) = $", line)
+            if own:
+                uses = re.findall(r"[^\n]*(?<!\w)" + own.group(1) + r"(?!\w)[^\n]*", src)
+                assert len(uses) == 2 and re.fullmatch(r"\s*if \(tid == 0\) s_\w+ = " + own.group(1) + ";", uses[1]), uses
+            else:
+                assert in_block, f"{os.path.basename(path)}: {src[m.start() - 40:m.end()]!r}"
     assert reads == 2
 
 
