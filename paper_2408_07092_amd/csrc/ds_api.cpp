@@ -83,25 +83,39 @@ static bool shape_ok(const ds_shape_t &s, bool need_rk)
     return true;
 }
 
-// Workgroups of the refine-and-attend kernel that one CU holds when the kernel scores as well
-// (matrix-core variants, query groups of 3+ heads): LDS is what limits them -- the chunk's keys and
-// row list (6 bytes a token), the chunk histogram or the wavefront partials, whichever is larger,
-// and about 3 KiB of small arrays -- and registers allow three.
-static int group_wgs_per_cu(int G, int ch, int n_ch, const DeviceCaps &caps)
+// Workspace of a decode that scores itself with several workgroups per unit: room for the partials and counters of
+// as many chunks as this many tokens make, which is also the most that choose_chunks may pick.  What a caller sees
+// of it is ds_workspace_bytes and which shapes the static scratch takes, so it is a rule by itself and not
+// the number that the launch ends up with: chunks for w = 4 workgroups to a compute unit (groups of three heads and
+// more: 3), or fewer, until w times 6 bytes a token and about 26 KiB (groups: the wavefronts' partials) are within the
+// compute unit's LDS; in up to four shares of the units where even one workgroup each is too many.
+// 0: no such number; the room is then that of the chunks behind a scoring launch.
+static int room_chunk(int units, int L, int G, const DeviceCaps &caps)
 {
+    const bool single = G <= 2;
     const int gt = G <= 4 ? 4 : G <= 8 ? 8 : 16;
-    const size_t lds = (size_t)ch * 6 + (size_t)n_ch * 4 + 512 + 3072 +
-                       4 * (size_t)std::max(kHistBins, 4 * gt * kPartStride);
-    return (int)std::min<size_t>(3, (size_t)caps.lds_per_cu / lds);
+    const size_t fixed = single ? 26u << 10 : 512 + 3072 + 4 * (size_t)std::max(kHistBins, 4 * gt * kPartStride);
+    for (int g = 1; g <= 4; ++g) {
+        const int units_g = (units + g - 1) / g;
+        for (int w = single ? 4 : 3; w >= 1; --w) {
+            const int n = std::min((caps.cus * w) / units_g, kMaxChunks);
+            if (n < (single ? 2 : 1)) continue;
+            const int c = std::max(single ? 1024 : 2048, (((L + n - 1) / n) + 63) & ~63);
+            const size_t lds = (size_t)c * 6 + (size_t)((L + c - 1) / c) * 4 + fixed;
+            if (c <= (single ? 16384 : 8192) && lds * w <= (size_t)caps.lds_per_cu) return c;
+        }
+    }
+    return 0;
 }
 
 // Chunks of a decode launch that scores itself with several workgroups per unit, whose whole grid has to be
 // resident: two workgroups of 512 threads to a compute unit by registers and LDS; for groups of more than
-// eight heads, whose kernels take more registers, one, or three of 256 threads and half the tokens.  The number of chunks per unit with the least estimated time, and in how many
-// launches of a share of the units each:
+// eight heads, whose kernels take more registers, one, or three of 256 threads and half the tokens.
+// The number of chunks per unit with the least estimated time, and in how many launches of a share of the units each:
 //   - the busiest compute unit's tokens, scored and their rows attended: about 53 GB/s (48 bytes a token with 8
-//     channels and a sixteenth of the rows: 0.9 us a thousand) by one workgroup, 61 by two, whose idle stretches fill each other's (128 single heads of 32K tokens 43.6 us with
-//     one, 42.8 with two; 96 of 30K, one 35.7, two 32.1; but 32 of 64K 26.9 and 28.3);
+//     channels and a sixteenth of the rows: 0.9 us a thousand) by one workgroup, 61 by two, whose idle
+//     stretches fill each other's (128 single heads of 32K tokens 43.6 us with one, 42.8 with two; 96 of 30K, one
+//     35.7, two 32.1; but 32 of 64K 26.9 and 28.3);
 //   - 0.25 us for each of a unit's workgroups, which meet at the same few lines of memory (one unit of 256K tokens
 //     39.7 us with 256 chunks, 28.0 with 128, 21.9 with 64; 32 units of 16K 21.7 with 2, 18.5 with 4, 17.7 with 8,
 //     20.8 with 16);
@@ -133,6 +147,9 @@ static bool choose_chunks(int units, int L, int G, double token_bytes, int cus, 
     return found;
 }
 
+// (4-bit labels, a quarter of it or a half, are counted as if they were fp16: the lines of decode_variant lie better for
+//  them that way.  With their own size, 120 random shapes of 16 to 44 MiB lost the streaming mark and took 1.01 of the
+//  time, 0.89 to 1.06; nine with few units 0.985.)
 size_t decode_bytes(const Plan &p, const ds_shape_t &s)
 {
     return (size_t)p.units * ((size_t)s.L * s.r * 2 + (size_t)p.k_eff * 2 * kD * 2);
@@ -180,13 +197,13 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
     p->n_sc = (s.L + sc - 1) / sc;
 
     // Launch shape of ds_sparse_decode: units of more than 8K tokens refine the threshold behind
-    // the attention (two launches).  Short units get one workgroup each, which refines and attends
-    // the whole unit out of LDS and writes the result itself (and scores it too when the label
+    // the attention (one launch where it can score as well, else two).  Short units get one workgroup each, which
+    // refines and attends the whole unit and writes the result itself (and scores it too when the label
     // cache allows it): everything between workgroups -- keys in memory,
     // histograms, arrival counting, partials -- costs more than it spreads at that size.  "Short"
-    // is 4K tokens; 8K when there are enough units (256) to fill the device; 16K for a workgroup
-    // that scores its unit itself, single heads or pairs, with 192 units or more (one 96 KiB
-    // workgroup per CU).  Units of 4K to 8K tokens that are too few for that take the long units'
+    // is 4K tokens; 8K when there are enough units (256) to fill the device; 16K, what a workgroup's registers
+    // hold, for single heads or pairs that it scores itself, with 192 units or more.
+    // Units of 4K to 8K tokens that are too few for that take the long units'
     // path when the attention launch can score, with one workgroup or several (see below); what is
     // left refines the threshold in the scoring launch's tail.
     const bool one_wg_units =
@@ -200,67 +217,24 @@ bool make_plan(const ds_shape_t &s, Plan *p, PlanFor purpose, bool q4)
     int ch = tune_get(1), ch_room = 0;
     p->chunks_score = false;
     p->unit_groups = 1;
-    if (ch == 0 && p->refine_attend && !one_wg_units && p->G > 2 && purpose == PLAN_DECODE_SCORING) {
-        // Query groups: one launch that scores as well pays off when all of its workgroups are
-        // resident at once (a workgroup waits for the others of its unit twice).  Most
-        // workgroups per CU first: the largest number of chunks per unit that still fits.
-        // (units that do not fit at once even with one workgroup per CU go in two to four launches
-        //  of a share of the units each)
-        for (int g = 1; g <= 4 && ch == 0; ++g) {
-            const int units_g = (p->units + g - 1) / g;
-            for (int w = 3; w >= 1 && ch == 0; --w) {
-                const int n = std::min((caps.cus * w) / units_g, kMaxChunks);
-                if (n < 1) continue;
-                const int c = std::max(2048, (((s.L + n - 1) / n) + 63) & ~63);  // (no point in tiny chunks)
-                if (c <= 8192 && group_wgs_per_cu(p->G, c, (s.L + c - 1) / c, caps) >= w) {
-                    ch = c;
-                    p->unit_groups = g;
-                }
-            }
-        }
-    }
+    if (ch == 0 && p->refine_attend && !one_wg_units && purpose == PLAN_DECODE_SCORING)
+        ch = room_chunk(p->units, s.L, p->G, caps);  // (choose_chunks below decides about the launch)
     if (ch != 0) {
-        // (set by the knob or just above)
+        // (set by the knob, or the workspace's room)
     } else if (p->refine_attend && one_wg_units) {
         ch = (s.L + 255) & ~255;
     } else if (p->refine_attend) {
         // every workgroup resident at once (registers allow four per CU on the vector path, three on
         // the matrix cores) when chunks of up to 4096 / 6144 tokens allow it
         if (p->G <= 2) {
-            // A launch that scores as well needs its whole grid resident, and LDS decides how many
-            // workgroups a CU holds (6 bytes a token for keys and row list, about 26 KiB of fixed
-            // arrays): the largest number of chunks per unit that gives four, else three, two, one
-            // workgroup per CU.  (Fixed chunks of up to 4096 tokens left 128 units of 32K tokens
-            // with 1024 workgroups of which 768 fit: scoring became a launch of its own, 55 us per
-            // layer against 46.5 with four chunks of 8192 tokens in one launch.)
-            // Units that do not fit at once even so (256 units of 32K tokens) go in two to four
-            // launches of a share of the units each, every one of them resident at once (two
-            // launches of 128 units: 93 us per layer against 105 with scoring as a launch of its own).
-            if (purpose == PLAN_DECODE_SCORING) {
-                for (int g = 1; g <= 4 && ch == 0; ++g) {
-                    const int units_g = (p->units + g - 1) / g;
-                    for (int w = 4; w >= 1 && ch == 0; --w) {
-                        const int n = std::min((caps.cus * w) / units_g, kMaxChunks);
-                        if (n < 2) continue;
-                        const int c = std::max(1024, (((s.L + n - 1) / n) + 63) & ~63);
-                        const size_t lds = (size_t)c * 6 + (size_t)((s.L + c - 1) / c) * 4 + (26u << 10);
-                        if (c <= 16384 && lds * w <= (size_t)caps.lds_per_cu) {
-                            ch = c;
-                            p->unit_groups = g;
-                        }
-                    }
-                }
-            }
             // Behind a scoring launch: a second round of workgroups for the few that do not fit costs far
             // more than chunks of twice the size (scores from K rows, 17 single heads of 64K tokens, 1088
             // workgroups 104.4 us, 544 93.3; 48 of 32K 113.0 and 103.6; pairs 107.0 and 95.1; 64
             // fp16 channels 78.9 and 67.9; below that line 40 single heads of 16K tokens in 640 or 320, 59.7 and 59.0).
-            if (ch == 0) {
-                ch = 1024;
-                while (ch < 4096 && (int64_t)p->units * ((s.L + ch - 1) / ch) > 6 * caps.cus) ch *= 2;
-                ch_room = ch;  // (the workspace keeps the room of six per CU)
-                while (ch < 4096 && (int64_t)p->units * ((s.L + ch - 1) / ch) > 4 * caps.cus) ch *= 2;
-            }
+            ch = 1024;
+            while (ch < 4096 && (int64_t)p->units * ((s.L + ch - 1) / ch) > 6 * caps.cus) ch *= 2;
+            ch_room = ch;  // (the workspace keeps the room of six per CU)
+            while (ch < 4096 && (int64_t)p->units * ((s.L + ch - 1) / ch) > 4 * caps.cus) ch *= 2;
         } else {
             ch = 2048;
             while (ch < 6144 && ch < s.L && (int64_t)p->units * ((s.L + ch - 1) / ch) > 3 * caps.cus) ch += 256;
@@ -481,7 +455,7 @@ const char *ds_strerror(ds_status_t status)
     return "unknown status";
 }
 
-int ds_version(void) { return 111; }
+int ds_version(void) { return 112; }
 
 ds_status_t ds_calibrate_channels(const uint16_t *q_calib, const uint16_t *k_calib, int32_t N,
                                   int32_t Hq, int32_t Hkv, int32_t d, int32_t r,
@@ -695,9 +669,9 @@ static bool label_may_score(const ds_shape_t &s, ScoreSrcKind kind)
 
 // Whether the attention launch of a decode call scores as well: a unit with one workgroup always
 // can; several workgroups per unit wait for each other before all of them have started, so the
-// whole grid has to be resident at once -- single heads and pairs: four workgroups per compute
-// unit; larger query groups: when the plan found chunks that make it so.  Knob 4 = 2 forces it,
-// 1 forbids it.  (The launcher checks the grid against the occupancy the runtime reports.)
+// whole grid has to be resident at once -- as choose_chunks made it, or, with another number of chunks (knob 1; a
+// part of a device), single heads and pairs at four workgroups per compute unit, what the 256-thread form allows.
+// Knob 4 = 2 forces it, 1 forbids it.  (The launcher checks the grid against the occupancy the runtime reports.)
 static bool plan_scores_itself(const Plan &p, bool may_score)
 {
     return may_score && (p.n_ch == 1 || tune_get(4) == 2 ||
@@ -737,11 +711,9 @@ static ds_status_t sparse_decode_impl(const void *q, const void *label, const vo
     // (a workspace shared by calls of different shapes: counters, histograms and error words start
     //  from zero whatever the last call left there -- a fill kernel, so that the call can be captured)
     if (clear_first) DS_TRY(launch_init(workspace, p.off_keys, st));
-    // a workgroup that may score its tokens itself: one launch, keys never leave LDS
-    // ... and so can several workgroups per unit (their chunk histograms meet in memory and the
-    // threshold bin is published to them) as long as the whole grid is resident at once: single
-    // heads and pairs, four workgroups per CU; larger query groups when the plan found chunks that
-    // make it so (up to three workgroups per CU).  Knob 4 = 2 forces it, 1 forbids it.
+    // a workgroup that may score its tokens itself: one launch, keys never leave its registers
+    // ... and so can several workgroups per unit (their chunk histograms meet in memory, where each finds
+    // the threshold bin) as long as the whole grid is resident at once
     bool scores_itself = plan_scores_itself(p, may_score);
     const bool q4 = src.kind == SRC_Q4;
     if (p.refine_attend && refine_attend_ok(p, scores_itself)) {

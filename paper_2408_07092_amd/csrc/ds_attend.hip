@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
     };
     int n_def = 0;
     uint32_t n_cand = 0;
-    uint32_t early_base = 0;  // (thread 0, several workgroups per unit, lists made by the single scan)
+    uint32_t early_base = 0;  // (thread 0)
     // Each thread owns n_pass groups of four consecutive keys (group p of thread t: keys
     // 4 (p WGT + t) ..: a wavefront's loads then cover the LDS banks evenly).  One look at each key:
     // which of the thread's keys are definite and which are candidates goes into bit masks, and the
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
         const uint32_t ex = block_exclusive_scan<NW>(packed, s_w, &total);
         DS_TR(13);
         // the chunk's place in the unit's candidate list is fetched while the lists are written
-        if (gridDim.x != 1 && tid == 0 && (total >> 16))
+        if (tid == 0 && (total >> 16))
             early_base = (uint32_t)__hip_atomic_fetch_add(cand_arrive, (unsigned long long)(total >> 16), __ATOMIC_RELAXED,
                                                           __HIP_MEMORY_SCOPE_AGENT);
         n_def = (int)(total & 0xffffu);
@@ -324,29 +324,24 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
     }
     // where the chunk's i-th candidate waits in the row list: behind the definite rows
     auto cand_slot = [&](uint32_t i) { return n_def + (int)i; };
-    // A unit with this one workgroup keeps everything in LDS: no candidate list in memory, no
-    // arrival, nothing to publish.
-    const bool single = gridDim.x == 1;
-    if (!single && tid == 0) {
+    if (tid == 0) {
         // candidate count of the unit (low word) and arrivals (high word) share one 64-bit counter
         s_base = early_base;
         if (a.idx_out) st_dev(a.ndef + (size_t)u * a.n_ch + c, (uint32_t)n_def);
     }
     __syncthreads();
-    if (!single) {
-        // (a unit has L candidates at most; a base beyond that means the workspace was not cleared)
-        const uint32_t base = s_base;
-        if (base + n_cand <= (uint32_t)a.L) {
-            for (uint32_t i = tid; i < n_cand; i += WGT) {
-                const int lt = sel[cand_slot(i)];
-                st_dev(cu + base + i, make_uint2(keys_sh[lt], (uint32_t)(t0 + lt)));
-            }
-        } else if (tid == 0) {
-            raise_err(8u);
+    // (a unit has L candidates at most; a base beyond that means the workspace was not cleared)
+    const uint32_t base = s_base;
+    if (base + n_cand <= (uint32_t)a.L) {
+        for (uint32_t i = tid; i < n_cand; i += WGT) {
+            const int lt = sel[cand_slot(i)];
+            st_dev(cu + base + i, make_uint2(keys_sh[lt], (uint32_t)(t0 + lt)));
         }
+    } else if (tid == 0) {
+        raise_err(8u);
     }
     DS_TR(1);
-    bool have_T = single ? true : last_arrival_sum(cand_arrive, gridDim.x, &s_flag, &s_base);
+    bool have_T = last_arrival_sum(cand_arrive, gridDim.x, &s_flag, &s_base);
     DS_TR(2);
     uint32_t T = 0;
     int tcut = 0x7fffffff;
@@ -356,20 +351,11 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
         // candidates (eight per thread) stay in registers; what lies beyond is read again by every
         // pass, eight loads in flight.  (One load at a time, the 4400 candidates of a unit of 256K
         // tokens took 16.5 us of the launch's 55, and every workgroup of the unit waited for them.)
-        const uint32_t n = single ? n_cand : min(s_base, (uint32_t)a.L);  // the completed count came with the arrival
-        // candidate i of the unit: out of the list in memory, or (single workgroup) the i-th
-        // staged token of this chunk
-        auto cand_at = [&](uint32_t i) {
-            if (single) {
-                const int lt = sel[cand_slot(i)];
-                return make_uint2(keys_sh[lt], (uint32_t)(t0 + lt));
-            }
-            return ld_dev(cu + i);
-        };
+        const uint32_t n = min(s_base, (uint32_t)a.L);  // the completed count came with the arrival
         uint2 ce[8];
         auto read8 = [&](uint2 (&v)[8], uint32_t i0) {
 #pragma unroll
-            for (int x = 0; x < 8; ++x) v[x] = cand_at(min(i0 + (uint32_t)(x * WGT), n - 1));
+            for (int x = 0; x < 8; ++x) v[x] = ld_dev(cu + min(i0 + (uint32_t)(x * WGT), n - 1));
         };
         if (n) read8(ce, tid);
         auto each = [&](auto f) {
@@ -488,7 +474,7 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
                 __syncthreads();
             }
         }
-        if (a.idx_out && !single) {
+        if (a.idx_out) {
             // selected tokens per chunk = keys above b* + selected candidates; prefix -> offsets
             for (int i = tid; i < a.n_ch; i += WGT) cnt[i] = ld_dev(a.ndef + (size_t)u * a.n_ch + i);
             __syncthreads();
@@ -510,7 +496,7 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
             __syncthreads();
         }
         DS_TR(15);
-        if (!single && tid == 0) {
+        if (tid == 0) {
             st_dev(ready, make_uint2(T, (uint32_t)tcut | 0x80000000u));
             __hip_atomic_store(cand_arrive, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -556,7 +542,7 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
             have_T = true;
         }
         DS_TR(4);
-        const uint32_t off = (a.idx_out && !single) ? ld_dev(a.offs_rw + (size_t)u * a.n_ch + c) : 0u;
+        const uint32_t off = a.idx_out ? ld_dev(a.offs_rw + (size_t)u * a.n_ch + c) : 0u;
         int32_t *io = a.idx_out ? a.idx_out + (size_t)u * a.k : nullptr;
         int all_base = 0;
         // the row list in thread-major order (any fixed order will do); an index list, if wanted,
@@ -609,7 +595,6 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
 
     for (int g0 = 0; g0 < a.G; g0 += GT) {
         float *po = a.part + (((size_t)u * a.G + g0) * a.n_ch + c) * kPartStride;
-        float *od = single ? a.out + ((size_t)u * a.G + g0) * kD : nullptr;
         const _Float16 *q0 = a.q + ((size_t)b * a.Hq + (size_t)h * a.G + g0) * kD;
         __syncthreads();
         if constexpr (GT >= 4) {
@@ -628,7 +613,7 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
             attend_rows_mfma<false>(Ku, Vu, row_bytes, n_def - n_first + n_sel, row_rest, qreg, st, sc_sh[tid >> 6]);
             DS_PRIO(3);
             DS_TR(5);
-            wg_store_partial_mfma<GT>(st, wpart, n_heads, po, (size_t)a.n_ch * kPartStride, od);
+            wg_store_partial_mfma<GT>(st, wpart, n_heads, po, (size_t)a.n_ch * kPartStride, nullptr);
         } else {
             // (the query rows have been in LDS since the kernel's first steps, barriers passed)
             RowState<GT> st;
@@ -641,12 +626,11 @@ __global__ __launch_bounds__(kWG, ST ? (GT == 1 ? 4 : 3) : 2) void k_attend_behi
             attend_rows<GT, kRowsInFlight, ST>(Ku, Vu, row_bytes, n_def - n_first + n_sel, row_rest, qsh, st);
             DS_PRIO(3);
             DS_TR(5);
-            wg_store_partial<GT, NW>(st, wpart, po, (size_t)a.n_ch * kPartStride, od);
+            wg_store_partial<GT, NW>(st, wpart, po, (size_t)a.n_ch * kPartStride, nullptr);
         }
     }
 
     // ---- last workgroup of the unit: merge the chunk partials, leave the control words clean
-    if (single) return;
     {
         // (the arrival count in the low half of the word; a workgroup whose wait ran out adds a
         //  mark in the high half, which the last one to arrive sees without another load)

@@ -30,18 +30,18 @@ struct AttendArgs {
     int Hq, Hkv, G, L, L_max, key_stride, ch, n_ch, k, k_eff, n_rows;
     int kv_stride;       // halves from one token's K (V) row to the next: d, or 2d when K|V interleave
     int unit0;           // k_refine_attend: first unit of this launch (a launch may take a share of the units)
-    // k_refine_attend only
-    uint2 *cand;         // [units][L] (key, token) of the keys in bin b*, unordered
-    uint32_t *ndef;      // [units][n_ch] keys above bin b* per chunk
-    uint32_t *offs_rw;   // [units][n_ch] offset of the chunk in the ascending index list
+    // k_refine_attend and k_attend_behind_scoring, units of several workgroups
+    uint2 *cand;         // [units][L] (key, token) of the keys in the threshold bin, unordered
+    uint32_t *ndef;      // [units][n_ch] keys above the threshold bin per chunk
+    uint32_t *offs_rw;   // k_attend_behind_scoring: [units][n_ch] offset of the chunk in the ascending index list
     uint32_t spin_limit;
-    // k_refine_attend with the scoring done in the same launch (one workgroup per unit)
-    const _Float16 *label;     // [units][L_max][r]
+    // k_refine_attend only
+    const _Float16 *label;     // [units][L_max][r], or 4-bit codes; unused where a scoring launch has left the keys
     const int32_t *channels;   // [Hkv][r]
-    uint32_t *hist, *coarse;   // unit histograms (4096 / 256 bins), zero between calls
+    uint32_t *hist, *coarse;   // unit histograms (4096 / 256 bins), zero between calls; units of several workgroups
     const float *amax;         // 4-bit label cache: [units][r] largest magnitude per channel
     float k_share;             // k_eff / L
-    int r;                     // label channels (4-bit label cache; fp16 labels have it in the kernel's type)
+    int r;                     // label channels
 };
 using RaFn = void (*)(AttendArgs);
 

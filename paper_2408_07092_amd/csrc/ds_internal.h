@@ -147,7 +147,7 @@ bool refine_attend_ok(const Plan &p, bool scores_itself);
 // without the streaming mark besides (calls of a few MiB); 256 threads.
 enum DecodeVariant { DECODE_WIDE, DECODE_DEEP, DECODE_LIGHT, DECODE_NARROW };
 DecodeVariant decode_variant(const Plan &p, const ds_shape_t &s);
-size_t decode_bytes(const Plan &p, const ds_shape_t &s);  // label and K/V rows that a sparse decode call reads
+size_t decode_bytes(const Plan &p, const ds_shape_t &s);  // label and K/V rows of a sparse decode call, labels as fp16
 constexpr size_t kStreamBytes = 16u << 20;                // from here on they are marked as streaming
 // Returned by launch_refine_attend (nothing enqueued) when the launch would wait for workgroups
 // that the device cannot hold at the same time as the waiting ones.
