@@ -381,7 +381,7 @@ def test_decode_many_candidates(Hq, L, k, step, one):
 
 
 @pytest.mark.parametrize("Hq,Hkv,L,r,k,cus,scores", [
-    # end bins: scores far below and far above the label query's size all fall into one bin
+    # scores far below and far above the label query's size: coarse bins
     (1, 1, 3000, 8, 187, 0, "tiny"), (2, 1, 12000, 16, 750, 0, "tiny"), (4, 1, 9000, 12, 563, 0, "tiny"),
     (1, 1, 3000, 8, 187, 0, "huge"), (3, 1, 9000, 8, 563, 0, "huge"), (1, 1, 12000, 4, 750, 0, "huge"),
     # thresholds on the negative side, and at either end of the list
@@ -402,9 +402,9 @@ def test_decode_many_candidates(Hq, L, k, step, one):
     (64, 64, 6144, 32, 384, 0, "plain"),
 ])
 def test_decode_bins_lists_and_variants(Hq, Hkv, L, r, k, cus, scores):
-    """The decode launch at the edges of its first-level bins (16 octaves of either sign around the
-    label query's largest value, the rest in the end bins), of its candidate lists and of the rules
-    that choose its form: index lists equal to the oracle's, outputs within the parity bounds."""
+    """The decode launch at the edges of its first-level bins (fine ones around the label query's largest
+    value, coarse ones far from it), of its candidate lists and of the rules that choose its form: index
+    lists equal to the oracle's, outputs within the parity bounds."""
     t = make_layer_numpy(Workload("t", 1, Hq, Hkv, 128, L, r, k, 1))
     ch = rand_channels(Hkv, r, seed=L + r)
     rng = np.random.default_rng(L + k)
